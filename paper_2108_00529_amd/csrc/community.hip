@@ -35,6 +35,7 @@
 #include "block_scan.h"
 #include "common.h"
 #include "community_jump.h"
+#include "volume_sum.h"
 
 namespace bgv {
 
@@ -130,12 +131,17 @@ template <int kRecInts>
 __global__ void __launch_bounds__(kCdThreads) k_cd_finish(const int32_t *__restrict__ st, int32_t n,
                                                            int32_t *__restrict__ labels, int32_t *__restrict__ degree,
                                                            unsigned long long *__restrict__ volume) {
+    __shared__ VolumeTable tab;
+    if (volume) vs_clear(tab);
+    __syncthreads();
     for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
         const int2 s = *reinterpret_cast<const int2 *>(st + kRecInts * v);
         labels[v] = s.y;
         degree[v] = s.x;
-        if (volume && s.x) atomicAdd(&volume[s.y], (unsigned long long)s.x);
+        if (volume && s.x) vs_add(tab, volume, s.y, (unsigned long long)s.x);
     }
+    __syncthreads();
+    if (volume) vs_flush(tab, volume);
 }
 
 // ------------------------------------------------------------ bucketed path -------
@@ -193,12 +199,17 @@ __global__ void __launch_bounds__(kCdThreads) k_cd_finish_b(const int32_t *__res
                                                              int32_t *__restrict__ labels,
                                                              int32_t *__restrict__ degree,
                                                              unsigned long long *__restrict__ volume) {
+    __shared__ VolumeTable tab;
+    if (volume) vs_clear(tab);
+    __syncthreads();
     for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
         const int32_t d = cnt[v], l = lab[v];
         labels[v] = l;
         degree[v] = d;
-        if (volume && d) atomicAdd(&volume[l], (unsigned long long)d);
+        if (volume && d) vs_add(tab, volume, l, (unsigned long long)d);
     }
+    __syncthreads();
+    if (volume) vs_flush(tab, volume);
 }
 
 // Endpoints of the non-loop edges of tile `tile` of chunk [cs, ce), grouped by bucket:
@@ -637,12 +648,17 @@ __global__ void __launch_bounds__(kCdThreads) k_vr_apply(NodeState *__restrict__
 __global__ void __launch_bounds__(kCdThreads) k_vr_finish(const NodeState *__restrict__ st, int32_t n, int32_t passes,
                                                           int32_t *__restrict__ labels, int32_t *__restrict__ degree,
                                                           unsigned long long *__restrict__ volume) {
+    __shared__ VolumeTable tab;
+    if (volume) vs_clear(tab);
+    __syncthreads();
     for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
         const int32_t d = st[v].cnt / passes, l = st[v].label;
         labels[v] = l;
         degree[v] = d;
-        if (volume && d) atomicAdd(&volume[l], (unsigned long long)d);
+        if (volume && d) vs_add(tab, volume, l, (unsigned long long)d);
     }
+    __syncthreads();
+    if (volume) vs_flush(tab, volume);
 }
 
 struct VrWs {
@@ -804,7 +820,7 @@ static bgv_status cd_run_bucketed(int32_t n, int64_t m, const int2 *e2, const bg
     if (ptiles > 0)
         BGV_LAUNCH(k_cd_resolve_props, dim3(cd_resolve_grid(nb)), dim3(kCdResolveThreads), 0, s, w.cnt, w.lab, n, nb,
                    w.props, w.ptab, ptiles, w.ends, w.etab, 0, cd_resolve_lanes(ptiles, nb), cnt8, cnt16);
-    BGV_LAUNCH(k_cd_finish_b, dim3(grid_for(n, kCdThreads, 65536)), dim3(kCdThreads), 0, s, w.cnt, w.lab, n,
+    BGV_LAUNCH(k_cd_finish_b, dim3(vs_grid(n)), dim3(kCdThreads), 0, s, w.cnt, w.lab, n,
                labels, degree, reinterpret_cast<unsigned long long *>(volume));
     return BGV_OK;
 }
@@ -902,7 +918,7 @@ static bgv_status cd_run(int32_t n, int64_t m, const int32_t *edges, const bgv_c
         BGV_LAUNCH(k_cd_apply_hist, dim3(grid_for(pe - ps, kCdThreads * 4, 16384)), dim3(kCdThreads), 0, s,
                            st, e2, prop, ps, pe, (int64_t)0, (int64_t)0);
     }
-    BGV_LAUNCH(k_cd_finish<4>, dim3(grid_for(n, kCdThreads, 65536)), dim3(kCdThreads), 0, s,
+    BGV_LAUNCH(k_cd_finish<4>, dim3(vs_grid(n)), dim3(kCdThreads), 0, s,
                reinterpret_cast<const int32_t *>(st), n, labels, degree,
                reinterpret_cast<unsigned long long *>(volume));
     return BGV_OK;
@@ -938,7 +954,7 @@ static bgv_status vr_run(int32_t n, int64_t m, const int32_t *edges, const bgv_c
             BGV_LAUNCH(k_cd_copy_labels, dim3(gn), dim3(kCdThreads), 0, s, reinterpret_cast<const int32_t *>(w.st) + 1,
                        4, n, pass_labels + (int64_t)pass * n);
     }
-    BGV_LAUNCH(k_vr_finish, dim3(gn), dim3(kCdThreads), 0, s, w.st, n, p->passes, labels, degree,
+    BGV_LAUNCH(k_vr_finish, dim3(vs_grid(n)), dim3(kCdThreads), 0, s, w.st, n, p->passes, labels, degree,
                reinterpret_cast<unsigned long long *>(volume));
     return BGV_OK;
 }

@@ -27,6 +27,7 @@
 
 #include "common.h"
 #include "community_jump.h"
+#include "volume_sum.h"
 
 namespace bgv {
 
@@ -347,13 +348,18 @@ __global__ void __launch_bounds__(kSqThreads) k_sq_labels(const KT *__restrict__
     }
 }
 
-__global__ void __launch_bounds__(kSqThreads) k_sq_volume(const int32_t *__restrict__ labels,
-                                                          const int32_t *__restrict__ degree, int32_t n,
-                                                          unsigned long long *__restrict__ volume) {
+__global__ void __launch_bounds__(1024) k_sq_volume(const int32_t *__restrict__ labels,
+                                                    const int32_t *__restrict__ degree, int32_t n,
+                                                    unsigned long long *__restrict__ volume) {
+    __shared__ VolumeTable tab;
+    vs_clear(tab);
+    __syncthreads();
     SQ_LOOP(v, n) {
         const int32_t d = degree[v];
-        if (d) atomicAdd(&volume[labels[v]], (unsigned long long)d);
+        if (d) vs_add(tab, volume, labels[v], (unsigned long long)d);
     }
+    __syncthreads();
+    vs_flush(tab, volume);
 }
 
 // ------------------------------------------------------------------- driver ----
@@ -438,7 +444,7 @@ bgv_status sq_run(int32_t n, int64_t m, const int32_t *edges, const bgv_cd_param
     else
         BGV_TRY(sq_events<uint32_t>(e2, n, m, p, w, labels, pass_labels, first, lab0, s));
     if (volume)
-        BGV_LAUNCH(k_sq_volume, dim3(gn), dim3(kSqThreads), 0, s, labels, degree, n,
+        BGV_LAUNCH(k_sq_volume, dim3(vs_grid(n)), dim3(1024), 0, s, labels, degree, n,
                    reinterpret_cast<unsigned long long *>(volume));
     return BGV_OK;
 }

@@ -248,6 +248,26 @@ __device__ __forceinline__ void cd_group_tile(const int2 *__restrict__ edges, in
     for (uint32_t k = threadIdx.x; k < total; k += kCdThreads) out[k] = stage[k];
 }
 
+// Writes a decide tile's proposals grouped by the target's bucket: target (or -1), label
+// and rank in its bucket of each of the thread's edges, hist[] the buckets' counts (the
+// last increment not yet behind a barrier).
+template <int kB>
+__device__ __forceinline__ void cd_write_props(const int32_t *target, const int32_t *lab, const uint32_t *rank,
+                                               int64_t t0, int32_t tile, int32_t nb, uint3 *__restrict__ props,
+                                               uint32_t *__restrict__ ptab, uint32_t *hist, uint3 *stage) {
+    __syncthreads();
+    const uint32_t total = cd_offsets(hist, nb, ptab + (int64_t)tile * (nb + 1));
+#pragma unroll
+    for (int j = 0; j < kCdItems; ++j)
+        if (target[j] >= 0)
+            stage[hist[target[j] >> kB] + rank[j]] =
+                make_uint3((uint32_t)(target[j] & ((1 << kB) - 1)),
+                           (uint32_t)(t0 + j * kCdThreads + threadIdx.x), (uint32_t)lab[j]);
+    __syncthreads();
+    uint3 *out = props + (int64_t)tile * kCdTile;
+    for (uint32_t k = threadIdx.x; k < total; k += kCdThreads) out[k] = stage[k];
+}
+
 // Decide, tile `tile` of chunk [cs, ce): the rule above (counters as in the atomic
 // path's decide: pass-0 values stored per edge in c1 when more passes follow,
 // p * d(v) + c1 in later passes), each proposal (offset of the target in its bucket,
@@ -339,17 +359,7 @@ __device__ __forceinline__ void cd_decide_tile(const CT *__restrict__ cnt, const
             }
         }
     }
-    __syncthreads();
-    const uint32_t total = cd_offsets(hist, nb, ptab + (int64_t)tile * (nb + 1));
-#pragma unroll
-    for (int j = 0; j < kCdItems; ++j)
-        if (target[j] >= 0)
-            stage[hist[target[j] >> kB] + rank[j]] =
-                make_uint3((uint32_t)(target[j] & ((1 << kB) - 1)),
-                           (uint32_t)(t0 + j * kCdThreads + threadIdx.x), (uint32_t)lab[j]);
-    __syncthreads();
-    uint3 *out = props + (int64_t)tile * kCdTile;
-    for (uint32_t k = threadIdx.x; k < total; k += kCdThreads) out[k] = stage[k];
+    cd_write_props<kB>(target, lab, rank, t0, tile, nb, props, ptab, hist, stage);
 }
 
 // One launch per chunk: decide chunk [cs, ce) (kMode >= 0) and, in pass 0, group the
@@ -418,6 +428,34 @@ __device__ __forceinline__ void cd_segment(const uint32_t *__restrict__ tab, int
     *q1 = row[b + 1];
 }
 
+// Lane `sub` of L lanes' share of a tile's proposals [p0, p1) to a bucket, and of its
+// endpoints [e0, e1) there, batches loaded before they are applied.
+__device__ __forceinline__ void cd_min_props(const uint3 *__restrict__ ps, uint32_t p0, uint32_t p1, uint32_t sub,
+                                             uint32_t L, unsigned long long *win) {
+    for (uint32_t q = p0 + sub; q < p1; q += 4 * L) {
+        uint3 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (q + u * L < p1) v[u] = ps[q + u * L];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (q + u * L < p1) atomicMin(&win[v[u].x], ((unsigned long long)v[u].y << 32) | v[u].z);
+    }
+}
+
+__device__ __forceinline__ void cd_add_ends(const uint16_t *__restrict__ es, uint32_t e0, uint32_t e1, uint32_t sub,
+                                            uint32_t L, uint32_t *inc) {
+    for (uint32_t q = e0 + sub; q < e1; q += 8 * L) {
+        uint32_t v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (q + u * L < e1) v[u] = es[q + u * L];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (q + u * L < e1) atomicAdd(&inc[v[u]], 1u);
+    }
+}
+
 // kEnds: the launch also adds grouped endpoint increments (pass 0); without them the
 // workgroup needs no increment array and two fit a compute unit's LDS.
 template <int kB, bool kEnds>
@@ -445,27 +483,8 @@ __global__ void __launch_bounds__(kCdResolveThreads) k_cd_resolve(int32_t *__res
         uint32_t p0 = 0, p1 = 0, e0 = 0, e1 = 0;
         if (t < ptiles) cd_segment(ptab, nb, t, b, &p0, &p1);
         if (t < etiles) cd_segment(etab, nb, t, b, &e0, &e1);
-        const uint3 *ps = props + (int64_t)t * kCdTile;
-        for (uint32_t q = p0 + sub; q < p1; q += 4 * L) {
-            uint3 v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (q + u * L < p1) v[u] = ps[q + u * L];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (q + u * L < p1) atomicMin(&win[v[u].x], ((unsigned long long)v[u].y << 32) | v[u].z);
-        }
-        if (!kEnds) continue;
-        const uint16_t *es = ends + (int64_t)t * (2 * kCdTile);
-        for (uint32_t q = e0 + sub; q < e1; q += 8 * L) {
-            uint32_t v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (q + u * L < e1) v[u] = es[q + u * L];
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (q + u * L < e1) atomicAdd(&inc[v[u]], 1u);
-        }
+        cd_min_props(props + (int64_t)t * kCdTile, p0, p1, sub, L, win);
+        if (kEnds) cd_add_ends(ends + (int64_t)t * (2 * kCdTile), e0, e1, sub, L, inc);
     }
     __syncthreads();
     const int64_t base = (int64_t)b << kB;
@@ -550,15 +569,27 @@ static size_t cd_layout(Carver &c, int32_t n, int64_t m, const bgv_cd_params *p,
 }
 
 // ------------------------------------------------------------ volume rule ----
-// SCoDA's community-volume rule, batch-synchronous, on the per-node records plus
+// SCoDA's community-volume rule, batch-synchronous, on per-node counters and labels plus
 // V[label] (64-bit): per chunk
-//   inc     counters and V of the chunk-start labels of both endpoints (atomics)
+//   inc     counters and V of the chunk-start labels of both endpoints
 //   decide  both counters at most D and labels different: the endpoint whose
-//           community has the smaller or equal V moves; proposals by a 64-bit
-//           atomicMin keyed by the stream index
+//           community has the smaller or equal V moves; the proposal of smallest stream
+//           index to a node wins
 //   apply   winners take their label and carry their counter from the old V to the new
-// Integer atomics only, so the result does not depend on timing.  Counters are raised
+// Integer sums only, so the result does not depend on timing.  Counters are raised
 // in every pass (V needs the increments), so a counter ends at passes * d(v).
+//
+// Grouped (n <= 2^24 and chunks that are not tiny beside the nodes, vr_grouped): the
+// bucketed form's tiles and buckets, two launches per chunk.  One workgroup per bucket
+// takes the winners of the previous chunk and this chunk's increments in LDS, so the
+// counters need no atomics, and the bucket's changes of V meet in a small LDS table
+// before they reach memory (volume_sum.h).  What bounds it are the decide's gathers and
+// the segment reads, as for the degree rule.
+// Atomic (the rest): per-node records, one device atomic per endpoint and counter, V by
+// one atomic per wave and label, proposals by a 64-bit atomicMin keyed by the stream
+// index; V's atomics on a few giant communities bound it.
+// 1M nodes, 10M edges, 3 passes, chunks of 2^20 (volumes included): 1.66 ms grouped, 17.5
+// ms atomic.
 // Adds `v` to vol[key] for the active lanes of a wave with one atomic per distinct key
 // (a few giant communities would otherwise serialise most of a chunk's atomics on a
 // handful of addresses).  Called by every lane of the wave that is still running.
@@ -645,14 +676,17 @@ __global__ void __launch_bounds__(kCdThreads) k_vr_apply(NodeState *__restrict__
     }
 }
 
-__global__ void __launch_bounds__(kCdThreads) k_vr_finish(const NodeState *__restrict__ st, int32_t n, int32_t passes,
+// Records kRecInts int32 apart ({counter, label} first).
+template <int kRecInts>
+__global__ void __launch_bounds__(kCdThreads) k_vr_finish(const int32_t *__restrict__ rec, int32_t n, int32_t passes,
                                                           int32_t *__restrict__ labels, int32_t *__restrict__ degree,
                                                           unsigned long long *__restrict__ volume) {
     __shared__ VolumeTable tab;
     if (volume) vs_clear(tab);
     __syncthreads();
     for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t d = st[v].cnt / passes, l = st[v].label;
+        const int2 r = *reinterpret_cast<const int2 *>(rec + kRecInts * v);
+        const int32_t d = r.x / passes, l = r.y;
         labels[v] = l;
         degree[v] = d;
         if (volume && d) vs_add(tab, volume, l, (unsigned long long)d);
@@ -661,18 +695,151 @@ __global__ void __launch_bounds__(kCdThreads) k_vr_finish(const NodeState *__res
     if (volume) vs_flush(tab, volume);
 }
 
+// Decide, tile `tile` of chunk [cs, ce), by community volume: rec[v] = {counter, label}.
+template <int kB>
+__device__ __forceinline__ void vr_decide_tile(const int2 *__restrict__ rec, const unsigned long long *__restrict__ vol,
+                                               const int2 *__restrict__ edges, int64_t cs, int64_t ce, int32_t D,
+                                               int32_t tile, int32_t nb, uint3 *__restrict__ props,
+                                               uint32_t *__restrict__ ptab, uint32_t *hist, uint3 *stage) {
+    for (int32_t b = threadIdx.x; b < nb; b += kCdThreads) hist[b] = 0;
+    __syncthreads();
+    const int64_t t0 = cs + (int64_t)tile * kCdTile;
+    int32_t target[kCdItems], lab[kCdItems];
+    uint32_t rank[kCdItems];
+#pragma unroll
+    for (int j = 0; j < kCdItems; ++j) {
+        const int64_t i = t0 + j * kCdThreads + threadIdx.x;
+        target[j] = -1;
+        if (i < ce) {
+            const int2 e = edges[i];
+            if (e.x != e.y) {
+                const int2 su = rec[e.x], sv = rec[e.y];
+                if (su.x <= D && sv.x <= D && su.y != sv.y) {
+                    const bool u_moves = vol[su.y] <= vol[sv.y];
+                    target[j] = u_moves ? e.x : e.y;
+                    lab[j] = u_moves ? sv.y : su.y;
+                    rank[j] = atomicAdd(&hist[target[j] >> kB], 1u);
+                }
+            }
+        }
+    }
+    cd_write_props<kB>(target, lab, rank, t0, tile, nb, props, ptab, hist, stage);
+}
+
+// One launch per chunk: decide chunk [cs, ce) (when it is not empty) and group the
+// endpoints of the chunk [gs, ge) whose increments come next.
+template <int kB>
+__global__ void __launch_bounds__(kCdThreads) k_vr_step(const int2 *__restrict__ rec,
+                                                        const unsigned long long *__restrict__ vol,
+                                                        const int2 *__restrict__ edges, int64_t cs, int64_t ce,
+                                                        int32_t D, int32_t nb, uint3 *__restrict__ props,
+                                                        uint32_t *__restrict__ ptab, int64_t gs, int64_t ge,
+                                                        uint16_t *__restrict__ ends, uint32_t *__restrict__ etab) {
+    __shared__ uint32_t hist[kCdMaxBuckets];
+    __shared__ uint3 pstage[kCdTile];
+    __shared__ uint16_t estage[2 * kCdTile];
+    const int32_t tile = (int32_t)blockIdx.x;
+    if (cs + (int64_t)tile * kCdTile < ce)  // uniform over the workgroup
+        vr_decide_tile<kB>(rec, vol, edges, cs, ce, D, tile, nb, props, ptab, hist, pstage);
+    if (gs + (int64_t)tile * kCdTile < ge) {
+        __syncthreads();  // hist is reused
+        cd_group_tile<kB>(edges, gs, ge, tile, nb, ends, etab, hist, estage);
+    }
+}
+
+// One workgroup per bucket (as k_cd_resolve): the winners of the previous chunk from
+// ptiles decide tiles take their labels and carry their counters between V's, then the
+// increments of etiles grouped tiles raise the counters and the V of the labels.
+template <int kB>
+__global__ void __launch_bounds__(kCdResolveThreads) k_vr_resolve(int2 *__restrict__ rec, unsigned long long *vol,
+                                                                  int32_t n, int32_t nb,
+                                                                  const uint3 *__restrict__ props,
+                                                                  const uint32_t *__restrict__ ptab, int32_t ptiles,
+                                                                  const uint16_t *__restrict__ ends,
+                                                                  const uint32_t *__restrict__ etab, int32_t etiles,
+                                                                  int32_t lanes) {
+    __shared__ unsigned long long win[1 << kB];
+    __shared__ uint32_t inc[1 << kB];
+    __shared__ VolumeTable tab;
+    const int32_t b = cd_resolve_bucket((int32_t)blockIdx.x, nb);
+    if (b >= nb) return;  // the grid is rounded up to a multiple of the XCD count
+    for (int32_t k = threadIdx.x; k < (1 << kB); k += kCdResolveThreads) {
+        win[k] = ~0ull;
+        inc[k] = 0u;
+    }
+    vs_clear(tab);
+    __syncthreads();
+    const int32_t tiles = max(ptiles, etiles);
+    const int32_t groups = kCdResolveThreads / lanes;
+    const uint32_t sub = threadIdx.x % lanes, L = (uint32_t)lanes;
+    for (int32_t t = threadIdx.x / lanes; t < tiles; t += groups) {
+        uint32_t p0 = 0, p1 = 0, e0 = 0, e1 = 0;
+        if (t < ptiles) cd_segment(ptab, nb, t, b, &p0, &p1);
+        if (t < etiles) cd_segment(etab, nb, t, b, &e0, &e1);
+        cd_min_props(props + (int64_t)t * kCdTile, p0, p1, sub, L, win);
+        cd_add_ends(ends + (int64_t)t * (2 * kCdTile), e0, e1, sub, L, inc);
+    }
+    __syncthreads();
+    const int64_t base = (int64_t)b << kB;
+    const int32_t span = min(1 << kB, n - (b << kB));
+    for (int32_t k = threadIdx.x; k < span; k += kCdResolveThreads) {
+        const unsigned long long w = win[k];
+        const uint32_t c = inc[k];
+        if (w == ~0ull && c == 0u) continue;
+        int2 r = rec[base + k];
+        if (w != ~0ull) {
+            const int32_t nw = (int32_t)(uint32_t)w;
+            vs_add(tab, vol, r.y, 0ull - (unsigned long long)r.x);
+            vs_add(tab, vol, nw, (unsigned long long)r.x + c);
+            r.y = nw;
+        } else {
+            vs_add(tab, vol, r.y, (unsigned long long)c);
+        }
+        r.x += (int32_t)c;
+        rec[base + k] = r;
+    }
+    __syncthreads();
+    vs_flush(tab, vol);
+}
+
+// Whether a call takes the grouped form.  Per chunk it costs two launches, of which the
+// resolve clears and sweeps every bucket's LDS: up to 2^20 nodes that is one round of
+// workgroups, and it is faster at every chunk (1M nodes, us per chunk, grouped / atomic:
+// 65,536 edges 31 / 410, 16 edges 11 / 25, one edge 9.6 / 10.3); with more nodes, from a
+// chunk of n / 8192 edges on (8M nodes: 8,192 edges 59 / 570, 1,024 edges 31 / 153), and
+// smaller chunks, whose atomics take less than that sweep, keep the atomic form.
+static bool vr_grouped(int32_t n, int64_t m, const bgv_cd_params *p) {
+    const int64_t b = p->chunk < m ? p->chunk : m;
+    return cd_bucketed(n) && (n <= (1 << 20) || b * 8192 >= n);
+}
+
 struct VrWs {
-    NodeState *st;
     unsigned long long *vol;
+    NodeState *st;  // atomic form
     int32_t *prop;
+    int2 *rec;      // grouped form: {counter, label}
+    uint3 *props;
+    uint16_t *ends;
+    uint32_t *ptab, *etab;
 };
 
 static size_t vr_layout(Carver &c, int32_t n, int64_t m, const bgv_cd_params *p, VrWs *w) {
     const int64_t b = p->chunk < m ? p->chunk : m;
-    VrWs t;
-    t.st = c.take<NodeState>((size_t)n);
+    const size_t bb = (size_t)(b > 0 ? b : 1);
+    VrWs t{};
     t.vol = c.take<unsigned long long>((size_t)n);
-    t.prop = c.take<int32_t>((size_t)(b > 0 ? b : 1));
+    if (vr_grouped(n, m, p)) {
+        const size_t tiles = (bb + kCdTile - 1) / kCdTile;
+        const size_t nb = (size_t)cd_buckets(n, cd_bucket_bits(n));
+        t.rec = c.take<int2>((size_t)n);
+        t.props = c.take<uint3>(tiles * kCdTile);
+        t.ends = c.take<uint16_t>(tiles * 2 * kCdTile);
+        t.ptab = c.take<uint32_t>(tiles * (nb + 1));
+        t.etab = c.take<uint32_t>(tiles * (nb + 1));
+    } else {
+        t.st = c.take<NodeState>((size_t)n);
+        t.prop = c.take<int32_t>(bb);
+    }
     if (w) *w = t;
     return c.size();
 }
@@ -924,6 +1091,74 @@ static bgv_status cd_run(int32_t n, int64_t m, const int32_t *edges, const bgv_c
     return BGV_OK;
 }
 
+__global__ void __launch_bounds__(kCdThreads) k_vr_init(int2 *__restrict__ rec, unsigned long long *__restrict__ vol,
+                                                        int32_t n, const int32_t *__restrict__ lab0) {
+    for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
+        rec[v] = make_int2(0, lab0 ? lab0[v] : (int32_t)v);
+        vol[v] = 0ull;
+    }
+}
+
+template <int kB>
+static bgv_status vr_run_grouped(int32_t n, int64_t m, const int2 *e2, const bgv_cd_params *p, const VrWs &w,
+                                 int32_t *labels, int32_t *degree, int64_t *volume, int32_t *pass_labels,
+                                 int32_t first, const int32_t *lab0, hipStream_t s) {
+    const int64_t B = p->chunk;
+    const int64_t nchunk = (m + B - 1) / B;
+    const int32_t nb = cd_buckets(n, kB);
+    const unsigned gn = grid_for(n, kCdThreads, 65536);
+    const auto k_vr_step = bgv::k_vr_step<kB>;  // one profiler name per kernel
+    const auto k_vr_resolve = bgv::k_vr_resolve<kB>;
+    auto tiles_of = [&](int64_t k) {
+        const int64_t len = (k + 1) * B < m ? B : m - k * B;
+        return (int32_t)((len + kCdTile - 1) / kCdTile);
+    };
+    int32_t ptiles = 0;  // decide tiles whose proposals are not yet resolved
+    int32_t etiles = 0;  // grouped endpoint tiles whose increments are not yet added
+    auto resolve = [&](int32_t et) -> bgv_status {
+        BGV_LAUNCH(k_vr_resolve, dim3(cd_resolve_grid(nb)), dim3(kCdResolveThreads), 0, s, w.rec, w.vol, n, nb,
+                   w.props, w.ptab, ptiles, w.ends, w.etab, et, cd_resolve_lanes(std::max(ptiles, et), nb));
+        ptiles = 0;
+        return BGV_OK;
+    };
+    BGV_LAUNCH(k_vr_init, dim3(gn), dim3(kCdThreads), 0, s, w.rec, w.vol, n, lab0);
+    if (nchunk > 0) {
+        etiles = tiles_of(0);
+        BGV_LAUNCH(k_vr_step, dim3(etiles), dim3(kCdThreads), 0, s, w.rec, w.vol, e2, (int64_t)0, (int64_t)0, 0, nb,
+                   w.props, w.ptab, (int64_t)0, std::min<int64_t>(B, m), w.ends, w.etab);
+    }
+    // A resumed run: after `first` passes every counter is first * d(v) and V[c] the sum of
+    // the counters labelled c; `first` sweeps that only add the increments, with the labels
+    // held at lab0, build exactly that.
+    for (int32_t pass = 0; pass < p->passes; ++pass) {
+        const bool counting = pass < first;
+        const int32_t D = counting ? 0 : pass_threshold(p->threshold, p->growth, pass);
+        for (int64_t k = 0; k < nchunk; ++k) {
+            const int64_t cs = k * B, ce = cs + B < m ? cs + B : m;
+            BGV_TRY(resolve(etiles));
+            const int32_t tiles = counting ? 0 : tiles_of(k);
+            const bool last = k + 1 == nchunk && pass + 1 == p->passes;
+            const int64_t next = k + 1 < nchunk ? k + 1 : 0;
+            const int64_t gs = last ? 0 : next * B, ge = last ? 0 : std::min<int64_t>(gs + B, m);
+            etiles = last ? 0 : tiles_of(next);
+            if (std::max(tiles, etiles) > 0)
+                BGV_LAUNCH(k_vr_step, dim3((unsigned)std::max(tiles, etiles)), dim3(kCdThreads), 0, s, w.rec, w.vol,
+                           e2, counting ? (int64_t)0 : cs, counting ? (int64_t)0 : ce, D, nb, w.props, w.ptab, gs, ge,
+                           w.ends, w.etab);
+            ptiles = tiles;
+        }
+        if (pass_labels) {
+            if (ptiles > 0) BGV_TRY(resolve(0));
+            BGV_LAUNCH(k_cd_copy_labels, dim3(gn), dim3(kCdThreads), 0, s, reinterpret_cast<const int32_t *>(w.rec) + 1,
+                       2, n, pass_labels + (int64_t)pass * n);
+        }
+    }
+    if (ptiles > 0) BGV_TRY(resolve(0));
+    BGV_LAUNCH(k_vr_finish<2>, dim3(vs_grid(n)), dim3(kCdThreads), 0, s, reinterpret_cast<const int32_t *>(w.rec), n,
+               p->passes, labels, degree, reinterpret_cast<unsigned long long *>(volume));
+    return BGV_OK;
+}
+
 static bgv_status vr_run(int32_t n, int64_t m, const int32_t *edges, const bgv_cd_params *p, int32_t *labels,
                          int32_t *degree, int64_t *volume, int32_t *pass_labels, int32_t first,
                          const int32_t *lab0, void *ws, hipStream_t s) {
@@ -931,6 +1166,10 @@ static bgv_status vr_run(int32_t n, int64_t m, const int32_t *edges, const bgv_c
     VrWs w;
     vr_layout(c, n, m, p, &w);
     const int2 *e2 = reinterpret_cast<const int2 *>(edges);
+    if (vr_grouped(n, m, p))
+        return cd_bucket_bits(n) == 13
+                   ? vr_run_grouped<13>(n, m, e2, p, w, labels, degree, volume, pass_labels, first, lab0, s)
+                   : vr_run_grouped<12>(n, m, e2, p, w, labels, degree, volume, pass_labels, first, lab0, s);
     const unsigned gn = grid_for(n, kCdThreads, 65536);
     BGV_LAUNCH(k_cd_init, dim3(gn), dim3(kCdThreads), 0, s, w.st, n, lab0);
     BGV_TRY(fill<uint64_t>(reinterpret_cast<uint64_t *>(w.vol), 0ull, n, s));
@@ -954,7 +1193,7 @@ static bgv_status vr_run(int32_t n, int64_t m, const int32_t *edges, const bgv_c
             BGV_LAUNCH(k_cd_copy_labels, dim3(gn), dim3(kCdThreads), 0, s, reinterpret_cast<const int32_t *>(w.st) + 1,
                        4, n, pass_labels + (int64_t)pass * n);
     }
-    BGV_LAUNCH(k_vr_finish, dim3(vs_grid(n)), dim3(kCdThreads), 0, s, w.st, n, p->passes, labels, degree,
+    BGV_LAUNCH(k_vr_finish<4>, dim3(vs_grid(n)), dim3(kCdThreads), 0, s, reinterpret_cast<const int32_t *>(w.st), n, p->passes, labels, degree,
                reinterpret_cast<unsigned long long *>(volume));
     return BGV_OK;
 }

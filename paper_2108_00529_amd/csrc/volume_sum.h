@@ -1,16 +1,18 @@
 // Sums of per-node values by community label (volumes), for kernels whose workgroups
 // each hold many nodes: a small table in LDS gathers the values of the labels that came
-// first to its slots, and every slot leaves as one device atomic.
+// first to its slots (four probes each), and every slot leaves as one device atomic.
 //
 // What bounds such sums is the rate of device atomics on one address (about 12 ns each):
 // a few giant communities hold most nodes of some streams, and one atomic per node then
 // takes n * 12 ns.  A label that is frequent in a workgroup's nodes is almost surely among
-// the first to reach its slot; rare labels that find their slot taken go straight to
-// memory, where they do not collide.  Integer sums: the order does not matter.
-// One atomic per node -> this table: 11.7 ms -> under 0.05 ms on 1M nodes after three
-// passes of the volume rule (most nodes in a few communities), 212 -> 48 us on the same
-// nodes after the sequential rule, 224 -> 133 us on 3.2M nodes of 172,000 communities
-// (there the rare labels' atomics, about 25 per ns, set the pace).
+// the first to reach one of its slots (with one probe, a rare label that came first to a
+// giant one's slot cost that workgroup thousands of serial atomics: 1.8 or 16 ms per call
+// of the volume rule, by the nodes' names); rare labels that find their slots taken go
+// straight to memory, where they do not collide.  Integer sums: the order does not matter.
+// One atomic per node -> this table: 11.7 ms -> 12 us on 1M nodes after three passes of
+// the volume rule (97% of them in one community), 212 -> 28 us on the same nodes after
+// the sequential rule, 224 -> 120 us on 3.2M nodes of 172,000 communities (there the
+// rare labels' atomics, about 25 per ns, set the pace).
 #pragma once
 #include "common.h"
 
@@ -18,6 +20,7 @@ namespace bgv {
 
 constexpr int kVsBits = 11;
 constexpr int kVsSlots = 1 << kVsBits;
+constexpr int kVsProbes = 4;
 
 struct VolumeTable {
     unsigned long long sum[kVsSlots];
@@ -33,14 +36,19 @@ __device__ __forceinline__ void vs_clear(VolumeTable &t) {
 
 // Adds v at label lab (>= 0).
 __device__ __forceinline__ void vs_add(VolumeTable &t, unsigned long long *vol, int32_t lab, unsigned long long v) {
-    const uint32_t q = ((uint32_t)lab * 2654435761u) >> (32 - kVsBits);
-    int32_t k = __hip_atomic_load(&t.key[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    if (k < 0) {
-        k = atomicCAS(&t.key[q], -1, lab);
-        if (k < 0) k = lab;
+    uint32_t q = ((uint32_t)lab * 2654435761u) >> (32 - kVsBits);
+    for (int probe = 0; probe < kVsProbes; ++probe, q = (q + 1) & (kVsSlots - 1)) {
+        int32_t k = __hip_atomic_load(&t.key[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (k < 0) {
+            k = atomicCAS(&t.key[q], -1, lab);
+            if (k < 0) k = lab;
+        }
+        if (k == lab) {
+            atomicAdd(&t.sum[q], v);
+            return;
+        }
     }
-    if (k == lab) atomicAdd(&t.sum[q], v);
-    else atomicAdd(&vol[lab], v);
+    atomicAdd(&vol[lab], v);
 }
 
 // After a barrier behind the last vs_add.

@@ -370,10 +370,7 @@ __global__ void __launch_bounds__(NT) k_batched(BtArgs a) {
                 float rx = 0.f, ry = 0.f, sx = 0.f, sy = 0.f;
                 for (uint32_t j0 = 0; j0 < K; j0 += NT) {
                     const uint32_t j = j0 + t;
-                    if (j < K) {
-                        const float2 xj = pos[j];
-                        tile[t] = make_float4(xj.x, xj.y, mass[j], 0.f);
-                    }
+                    tile[t] = j < K ? fa2_body(pos[j], mass[j]) : fa2_no_body();
                     __syncthreads();
                     const uint32_t c = min((uint32_t)NT, K - j0);
                     for (uint32_t q0 = 0; q0 < c;) {
@@ -389,9 +386,7 @@ __global__ void __launch_bounds__(NT) k_batched(BtArgs a) {
                             sx = sy = 0.f;
                         }
                         const uint32_t q1 = min(c, (jj / (uint32_t)kRepSegment + 1u) * (uint32_t)kRepSegment - j0);
-                        const uint32_t n8 = (q1 - q0) & ~7u;  // groups of eight LDS reads in flight
-                        fa2_rep_run(xi, tile + q0, (int)n8, sx, sy);
-                        for (uint32_t q = q0 + n8; q < q1; ++q) fa2_rep_term(xi, tile[q], sx, sy);
+                        fa2_rep_run(xi, tile + q0, (int)((q1 - q0 + 7u) & ~7u), sx, sy);
                         q0 = q1;
                     }
                     __syncthreads();
@@ -543,19 +538,14 @@ __device__ __forceinline__ void bt_wave_repulsion(int32_t wt, int32_t sgm, int32
     const float2 xi = live ? pos[i] : make_float2(0.f, 0.f);
     const int32_t jb = sgm * kRepSegment, je = min(K, jb + kRepSegment);
     float fx = 0.f, fy = 0.f;
+    // the next bodies are loaded while these are used
+    float4 next = jb + lane < je ? fa2_body(pos[jb + lane], mass[jb + lane]) : fa2_no_body();
     for (int32_t t0 = jb; t0 < je; t0 += kWave) {
-        const int32_t j = t0 + lane;
-        if (j < je) {
-            const float2 xj = pos[j];
-            slab[lane] = make_float4(xj.x, xj.y, mass[j], 0.f);
-        }
+        slab[lane] = next;
+        const int32_t j = t0 + kWave + lane;
+        next = j < je ? fa2_body(pos[j], mass[j]) : fa2_no_body();
         __builtin_amdgcn_wave_barrier();
-        const int cnt = min(kWave, je - t0);
-        if (cnt == kWave) {
-            fa2_rep_run(xi, slab, kWave, fx, fy);
-        } else {
-            for (int q = 0; q < cnt; ++q) fa2_rep_term(xi, slab[q], fx, fy);
-        }
+        fa2_rep_run(xi, slab, min(kWave, (je - t0 + 7) & ~7), fx, fy);
         __builtin_amdgcn_wave_barrier();
     }
     if (live) seg[(int64_t)sgm * K + i] = make_float2(fx, fy);

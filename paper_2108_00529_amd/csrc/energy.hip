@@ -28,23 +28,22 @@ __device__ __forceinline__ double block_sum(double v) {
     return r;
 }
 
-// Upper-triangular tile pairs (I <= J): block b -> (I, J).
+// Pairs of a row tile (R x kEnThreads bodies, R per thread) and a column tile (kEnThreads
+// bodies) that hold some j > i: row tile I takes column tiles J = R I .. T - 1.  Block b
+// -> (I, J).
+__device__ __forceinline__ int64_t en_row_start(int64_t I, int64_t T, int R) { return I * T - R * (I * (I - 1) / 2); }
+
+template <int R>
 __device__ __forceinline__ void tri_index(int64_t b, int T, int &I, int &J) {
-    // row I holds T - I tiles; find I by walking (T is small: <= 2^23/256)
-    int64_t rem = b;
-    int i = 0;
-    // closed form start, then fix up
-    double tt = (double)T + 0.5;
-    double est = tt - sqrt(tt * tt - 2.0 * (double)b);
-    i = (int)est;
-    if (i < 0) i = 0;
-    if (i > T - 1) i = T - 1;
-    auto start = [&](int r) { return (int64_t)r * T - (int64_t)r * (r - 1) / 2; };
-    while (i > 0 && start(i) > b) --i;
-    while (i < T - 1 && start(i + 1) <= b) ++i;
-    rem = b - start(i);
+    // closed form start (the root of I (T + R/2) - R I^2 / 2 = b), then fix up
+    const int rows = (T + R - 1) / R;
+    const double tt = (double)T + 0.5 * R;
+    int i = (int)((tt - sqrt(fmax(0.0, tt * tt - 2.0 * R * (double)b))) / R);
+    i = max(0, min(i, rows - 1));
+    while (i > 0 && en_row_start(i, T, R) > b) --i;
+    while (i < rows - 1 && en_row_start(i + 1, T, R) <= b) ++i;
     I = i;
-    J = i + (int)rem;
+    J = R * i + (int)(b - en_row_start(i, T, R));
 }
 
 constexpr double kLn2 = 0.693147180559945309417232121458176568;
@@ -52,54 +51,88 @@ constexpr double kLn2 = 0.693147180559945309417232121458176568;
 // m_j log2 |x_i - x_j|^2 (none for coincident bodies), with the hardware base-2
 // logarithm (within one ulp); subnormal d^2 is scaled by 2^64 first, since the
 // instruction takes normal inputs.  The caller scales by ln 2.
-__device__ __forceinline__ float en_log_term(float2 xi, float4 p) {
-    const float dx = xi.x - p.x, dy = xi.y - p.y;
-    const float d2 = dx * dx + dy * dy;
+__device__ __forceinline__ float en_log_term(float d2, float m) {
     const bool sub = d2 < 1.17549435e-38f;
     const float l = __builtin_amdgcn_logf(sub ? d2 * 18446744073709551616.0f : d2) - (sub ? 64.0f : 0.0f);
-    return d2 > 0.f ? p.z * l : 0.f;
+    return d2 > 0.f ? m * l : 0.f;
 }
 
 // Block x takes tile pairs x, x + grid, ... (one pair per block up to kEnPairBlocks
-// pairs, i.e. up to about 740k supernodes; a fixed assignment and order either way).
-__global__ void __launch_bounds__(kEnThreads) k_energy_pairs(int32_t K, int T, int64_t ntri,
+// pairs, i.e. up to about a million supernodes; a fixed assignment and order either way).
+// Bound by vector issue: per pair two differences, d^2 in two, the logarithm, one fma and
+// half an instruction of a minimum over eight d^2 by which whole groups skip the tests
+// for coincident bodies and subnormal d^2 (50,000 bodies: 416 -> 255 us, 3.0e12 -> 4.9e12
+// pairs/s).
+template <int R>
+__global__ void __launch_bounds__(kEnThreads) k_energy_pairs(int32_t K, int T, int64_t npair,
                                                               const float2 *__restrict__ pos,
                                                               const float *__restrict__ mass,
                                                               double *__restrict__ part) {
     __shared__ float4 tile[kEnThreads];
     double acc = 0.0;
-    for (int64_t pb = blockIdx.x; pb < ntri; pb += gridDim.x) {  // uniform over the workgroup
-    int I, J;
-    tri_index(pb, T, I, J);
-    const int32_t i = I * kEnThreads + threadIdx.x;
-    const int32_t j0 = J * kEnThreads;
-    if (pb != blockIdx.x) __syncthreads();  // the previous pair's reads of the tile are done
-    if (j0 + (int)threadIdx.x < K) {
-        const float2 p = pos[j0 + threadIdx.x];
-        tile[threadIdx.x] = make_float4(p.x, p.y, mass[j0 + threadIdx.x], 0.f);
-    }
-    __syncthreads();
-    if (i < K) {
-        const float2 xi = pos[i];
+    for (int64_t pb = blockIdx.x; pb < npair; pb += gridDim.x) {  // uniform over the workgroup
+        int I, J;
+        tri_index<R>(pb, T, I, J);
+        const int32_t i0 = I * (R * kEnThreads) + threadIdx.x;
+        const int32_t j0 = J * kEnThreads;
+        if (pb != blockIdx.x) __syncthreads();  // the previous pair's reads of the tile are done
+        const int32_t j = j0 + threadIdx.x;
+        tile[threadIdx.x] = j < K ? fa2_body(pos[j], mass[j]) : fa2_no_body();
+        __syncthreads();
+        float2 xi[R];
+        float mi[R], s[R];  // s = sum of m_j log2(d^2) over the tile's j above i
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int32_t i = i0 + r * kEnThreads;
+            xi[r] = i < K ? pos[i] : make_float2(0.f, 0.f);
+            mi[r] = i < K ? mass[i] : 0.f;
+            s[r] = 0.f;
+        }
         const int cnt = min(kEnThreads, K - j0);
-        float s = 0.f;
-        // s = sum of m_j log2(d^2) over the tile's j above i; scaled by ln 2 below
-        if (J > I && cnt == kEnThreads) {  // every j of the tile is above i
+        const bool above = j0 >= (I + 1) * (R * kEnThreads);  // every j of the tile is above every i
+        if (above && cnt == kEnThreads) {
             for (int q = 0; q < kEnThreads; q += 8) {
                 float4 b[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) b[u] = tile[q + u];
+                float d2[R][8];
+                uint32_t least = ~0u;
 #pragma unroll
-                for (int u = 0; u < 8; ++u) s += en_log_term(xi, b[u]);
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        d2[r][u] = fa2_norm2(xi[r].x - b[u].x, xi[r].y - b[u].y);
+                        least = min(least, __float_as_uint(d2[r][u]));
+                    }
+                if (__any(least < 0x00800000u)) {  // below the smallest normal number
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) s[r] += en_log_term(d2[r][u], b[u].z);
+                } else {
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+#pragma unroll
+                        for (int u = 0; u < 8; ++u)
+                            s[r] = __builtin_fmaf(b[u].z, __builtin_amdgcn_logf(d2[r][u]), s[r]);
+                }
             }
         } else {
-            for (int q = 0; q < cnt; ++q) {
-                const float v = en_log_term(xi, tile[q]);
-                s += j0 + q > i ? v : 0.f;
+            for (int q = 0; q < cnt; q += 8) {  // the tile's end is padded with bodies that add nothing
+                float4 b[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) b[u] = tile[q + u];
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const float v = en_log_term(fa2_norm2(xi[r].x - b[u].x, xi[r].y - b[u].y), b[u].z);
+                        s[r] += j0 + q + u > i0 + r * kEnThreads ? v : 0.f;
+                    }
             }
         }
-        acc += 0.5 * kLn2 * (double)mass[i] * (double)s;
-    }
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc += 0.5 * kLn2 * (double)mi[r] * (double)s[r];
     }
     acc = block_sum(acc);
     if (threadIdx.x == 0) part[blockIdx.x] = acc;
@@ -148,33 +181,36 @@ __global__ void __launch_bounds__(kEnThreads) k_energy_final(const double *__res
     if (threadIdx.x == 0) *out = a - (double)kr * r + (double)kg * g;
 }
 
-// Partial repulsion sums of the i tile over j split `blockIdx.y`.
+// Partial repulsion sums of the i tile (256 R bodies, R per thread) over j split
+// `blockIdx.y`.  Vector issue bounds it (50,000 bodies: 709 us with one body per thread,
+// 633 with two; 16,384 the same either way).
+template <int R>
 __global__ void __launch_bounds__(kEnThreads) k_grad_rep(int32_t K, int jtiles_per_split,
                                                           const float2 *__restrict__ pos,
                                                           const float *__restrict__ mass,
                                                           float2 *__restrict__ prep) {
     __shared__ float4 tile[kEnThreads];
-    const int32_t i = blockIdx.x * kEnThreads + threadIdx.x;
-    const float2 xi = i < K ? pos[i] : make_float2(0.f, 0.f);
-    float fx = 0.f, fy = 0.f;
+    const int32_t i = blockIdx.x * (kEnThreads * R) + threadIdx.x;
+    float2 xi[R];
+    float fx[R], fy[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        xi[r] = i + r * kEnThreads < K ? pos[i + r * kEnThreads] : make_float2(0.f, 0.f);
+        fx[r] = fy[r] = 0.f;
+    }
     const int jt0 = blockIdx.y * jtiles_per_split;
     for (int jt = jt0; jt < jt0 + jtiles_per_split; ++jt) {
         const int32_t j0 = jt * kEnThreads;
         if (j0 >= K) break;
-        if (j0 + (int)threadIdx.x < K) {
-            const float2 p = pos[j0 + threadIdx.x];
-            tile[threadIdx.x] = make_float4(p.x, p.y, mass[j0 + threadIdx.x], 0.f);
-        }
+        const int32_t j = j0 + threadIdx.x;
+        tile[threadIdx.x] = j < K ? fa2_body(pos[j], mass[j]) : fa2_no_body();
         __syncthreads();
-        const int cnt = min(kEnThreads, K - j0);
-        if (cnt == kEnThreads) {
-fa2_rep_run(xi, tile, kEnThreads, fx, fy);
-        } else {
-            for (int q = 0; q < cnt; ++q) fa2_rep_term(xi, tile[q], fx, fy);
-        }
+        fa2_rep_run(xi, tile, min(kEnThreads, (K - j0 + 7) & ~7), fx, fy);
         __syncthreads();
     }
-    if (i < K) prep[(int64_t)blockIdx.y * K + i] = make_float2(fx, fy);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (i + r * kEnThreads < K) prep[(int64_t)blockIdx.y * K + i + r * kEnThreads] = make_float2(fx[r], fy[r]);
 }
 
 // grad_i = -g * (kr m_i sum_splits rep + attraction + gravity)
@@ -198,7 +234,7 @@ __global__ void __launch_bounds__(kEnThreads) k_grad_final(int32_t K, int nsplit
         const float2 a = fa2_att_combine(att, item_of, i);
         fx += a.x;
         fy += a.y;
-        const float r = sqrtf(xi.x * xi.x + xi.y * xi.y);
+        const float r = sqrtf(fa2_norm2(xi.x, xi.y));
         if (r > 0.f) {
             const float g = kg * mi / r;
             fx -= g * xi.x;
@@ -216,9 +252,13 @@ struct EnWs {
 };
 
 static int en_tiles(int32_t K) { return (K + kEnThreads - 1) / kEnThreads; }
+// Rows per thread of the pair kernel: two, so that each LDS read serves two pairs, from the
+// size on where that shortens the call (one row / two: 16,000 bodies 47 / 56 us, 20,480
+// 66 / 65, 24,000 86 / 81, 50,000 311 / 244).
+static int en_rows(int32_t K) { return K >= 20480 ? 2 : 1; }
 static int64_t en_tri_pairs(int32_t K) {
-    const int64_t T = en_tiles(K);
-    return T * (T + 1) / 2;
+    const int64_t T = en_tiles(K), R = en_rows(K), rows = (T + R - 1) / R;
+    return rows * T - R * (rows * (rows - 1) / 2);
 }
 // larger supergraphs share their tile pairs out over this grid (4M workgroups of 256:
 // under the 2^32 work-items a launch may have)
@@ -226,8 +266,8 @@ constexpr int64_t kEnPairBlocks = (int64_t)1 << 22;
 static int64_t en_tri_blocks(int32_t K) { return std::min(en_tri_pairs(K), kEnPairBlocks); }
 static int en_edge_blocks(int64_t E) { return (int)grid_for(E, kEnThreads * 8, 2048); }
 static int en_grav_blocks(int32_t K) { return (int)grid_for(K, kEnThreads * 8, 2048); }
-static int en_splits(int32_t K) {
-    const int T = en_tiles(K);
+static int en_splits(int32_t K) {  // about 2,048 workgroups of k_grad_rep
+    const int T = K >= kRepTwoMin ? (en_tiles(K) + 1) / 2 : en_tiles(K);
     int s = (2048 + T - 1) / T;
     if (s > T) s = T;
     if (s < 1) s = 1;
@@ -275,8 +315,14 @@ extern "C" bgv_status bgv_fa2_energy(int32_t K, int64_t E, const int32_t *edges,
     if (!m) BGV_TRY(build_csr(K, E, edges, attr_w, nullptr, w.csr, s, &m));
     const float2 *x = reinterpret_cast<const float2 *>(pos);
     const int64_t ntri = en_tri_blocks(K);
-    BGV_LAUNCH(k_energy_pairs, dim3((unsigned)ntri), dim3(kEnThreads), 0, s, K, en_tiles(K), en_tri_pairs(K), x, m,
-               w.prep);
+    const auto k_energy_pairs1 = k_energy_pairs<1>;
+    const auto k_energy_pairs2 = k_energy_pairs<2>;
+    if (en_rows(K) == 2)
+        BGV_LAUNCH(k_energy_pairs2, dim3((unsigned)ntri), dim3(kEnThreads), 0, s, K, en_tiles(K), en_tri_pairs(K), x,
+                   m, w.prep);
+    else
+        BGV_LAUNCH(k_energy_pairs1, dim3((unsigned)ntri), dim3(kEnThreads), 0, s, K, en_tiles(K), en_tri_pairs(K), x,
+                   m, w.prep);
     const int ne = en_edge_blocks(E), ng = en_grav_blocks(K);
     BGV_LAUNCH(k_energy_edges, dim3(ne), dim3(kEnThreads), 0, s, E, reinterpret_cast<const int2 *>(edges),
                        attr_w, x, w.patt);
@@ -305,7 +351,12 @@ extern "C" bgv_status bgv_fa2_grad(int32_t K, int64_t E, const int32_t *edges, c
     const float2 *x = reinterpret_cast<const float2 *>(pos);
     const int T = en_tiles(K), ns = en_splits(K);
     const int per = (T + ns - 1) / ns;
-    BGV_LAUNCH(k_grad_rep, dim3(T, ns), dim3(kEnThreads), 0, s, K, per, x, m, w.gsplit);
+    const auto k_grad_rep1 = k_grad_rep<1>;
+    const auto k_grad_rep2 = k_grad_rep<2>;
+    if (K >= kRepTwoMin)
+        BGV_LAUNCH(k_grad_rep2, dim3((T + 1) / 2, ns), dim3(kEnThreads), 0, s, K, per, x, m, w.gsplit);
+    else
+        BGV_LAUNCH(k_grad_rep1, dim3(T, ns), dim3(kEnThreads), 0, s, K, per, x, m, w.gsplit);
     BGV_TRY(attraction(K, x, w.csr, w.att, s));
     BGV_LAUNCH(k_grad_final, dim3(grid_for(K, kEnThreads, 65536)), dim3(kEnThreads), 0, s, K, ns, w.gsplit, x, m,
                w.att, w.csr.item_of, kr, kg, grad_out, reinterpret_cast<float2 *>(grad));

@@ -648,14 +648,14 @@ bgv_status attraction(int32_t K, const float2 *pos, const CsrWs &csr, float2 *A,
 // kSegmented is false), bodies staged through LDS 256 at a time.  With one segment the
 // kernel finishes the force (attraction, gravity, swing, traction and the block's FP64
 // partials); with several it stores the segment sums for k_force_combine.
-template <bool kSegmented>
+template <bool kSegmented, int R>
 __global__ void __launch_bounds__(kFaThreads) k_force_exact(int32_t K, const float2 *__restrict__ pos,
                                                              const float *__restrict__ mass,
                                                              const float2 *__restrict__ att,
                                                              const uint32_t *__restrict__ item_of, float kr, float kg,
                                                              const float2 *__restrict__ fprev, float2 *__restrict__ F,
                                                              double2 *__restrict__ part, float2 *__restrict__ seg) {
-    fa2_exact_force_tile<kSegmented>((int32_t)blockIdx.x, (int32_t)blockIdx.y, K, pos, mass, att, item_of, kr, kg,
+    fa2_exact_force_tile<kSegmented, R>((int32_t)blockIdx.x, (int32_t)blockIdx.y, K, pos, mass, att, item_of, kr, kg,
                                      fprev, F, part, seg);
 }
 
@@ -676,12 +676,19 @@ static bgv_status exact_forces(int32_t K, const float2 *pos, const float *mass, 
                                double2 *part, float2 *seg, hipStream_t s) {
     const unsigned nb = (unsigned)((K + kFaThreads - 1) / kFaThreads);
     const int32_t nseg = fa2_rep_segments(K);
+    const auto k_force_exact1 = k_force_exact<false, 1>;
+    const auto k_force_exact_seg = k_force_exact<true, 1>;
+    const auto k_force_exact_seg2 = k_force_exact<true, 2>;
     if (nseg <= 1) {
-        BGV_LAUNCH(k_force_exact<false>, dim3(nb), dim3(kFaThreads), 0, s, K, pos, mass, A, item_of, kr, kg, fprev,
+        BGV_LAUNCH(k_force_exact1, dim3(nb), dim3(kFaThreads), 0, s, K, pos, mass, A, item_of, kr, kg, fprev,
                    F, part, seg);
     } else {
-        BGV_LAUNCH(k_force_exact<true>, dim3(nb, (unsigned)nseg), dim3(kFaThreads), 0, s, K, pos, mass, A, item_of,
-                   kr, kg, fprev, F, part, seg);
+        if (K >= kRepTwoMin)
+            BGV_LAUNCH(k_force_exact_seg2, dim3((nb + 1) / 2, (unsigned)nseg), dim3(kFaThreads), 0, s, K, pos, mass, A,
+                       item_of, kr, kg, fprev, F, part, seg);
+        else
+            BGV_LAUNCH(k_force_exact_seg, dim3(nb, (unsigned)nseg), dim3(kFaThreads), 0, s, K, pos, mass, A, item_of,
+                       kr, kg, fprev, F, part, seg);
         BGV_LAUNCH(k_force_combine, dim3(nb), dim3(kFaThreads), 0, s, K, nseg, seg, pos, mass, A, item_of, kr, kg,
                    fprev, F, part);
     }
@@ -1222,7 +1229,7 @@ __device__ __forceinline__ bool bh_force_block(int32_t blk, int32_t K, const flo
                     bool o = r >= f && r <= l;
                     if (!o) {
                         const float dx = xi.x - A.x, dy = xi.y - A.y;
-                        const float d2 = dx * dx + dy * dy;
+                        const float d2 = fa2_norm2(dx, dy);
                         if (d2 > 0.f && A.w < theta2 * d2) {
                             const float fr = A.z * __builtin_amdgcn_rcpf(d2);
                             fx += fr * dx;

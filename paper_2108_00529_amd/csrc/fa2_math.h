@@ -7,17 +7,24 @@
 
 namespace bgv {
 
+// x^2 + y^2 with y^2 the product that is rounded on its own: written out, so that every
+// kernel that inlines it gives the same bits.
+__device__ __forceinline__ float fa2_norm2(float x, float y) { return __builtin_fmaf(x, x, y * y); }
+
 // Repulsion from one body p = (x, y, mass): (x_i - x_j) * m_j / |x_i - x_j|^2, none if
-// coincident.  The caller scales the sum by kr * m_i.  Branch-free so that unrolled
-// loops keep several LDS reads in flight; 1/d^2 is the hardware reciprocal (within one
-// ulp), the quotient's rounding being far below the layout's tolerance.
+// coincident.  The caller scales the sum by kr * m_i.  1/d^2 is the hardware reciprocal
+// (within one ulp), the quotient's rounding being far below the layout's tolerance.
 __device__ __forceinline__ void fa2_rep_term(float2 xi, float4 p, float &fx, float &fy) {
     const float dx = xi.x - p.x, dy = xi.y - p.y;
-    const float d2 = dx * dx + dy * dy;
+    const float d2 = fa2_norm2(dx, dy);
     const float f = d2 > 0.f ? p.z * __builtin_amdgcn_rcpf(d2) : 0.f;
-    fx += f * dx;
-    fy += f * dy;
+    fx = __builtin_fmaf(f, dx, fx);
+    fy = __builtin_fmaf(f, dy, fy);
 }
+
+// A body as the loops over all pairs stage it in LDS, and one that adds nothing.
+__device__ __forceinline__ float4 fa2_body(float2 x, float m) { return make_float4(x.x, x.y, m, 0.f); }
+__device__ __forceinline__ float4 fa2_no_body() { return make_float4(0.f, 0.f, 0.f, 0.f); }
 
 // fa2_rep_term over n consecutive LDS bodies in ascending order, n a multiple of 8: each
 // group of eight is read before any of it is used, so the reads overlap.
@@ -31,6 +38,56 @@ __device__ __forceinline__ void fa2_rep_run(float2 xi, const float4 *tile, int n
     }
 }
 
+// The same sums on R bodies per lane, so that each LDS read serves R pairs.  With enough
+// bodies the loop is bound by vector issue, so the test for coincident bodies is taken
+// once per group: the smallest of its d^2 (as bit patterns: they are not negative) by
+// three-operand minima, and the per-pair test and select only where some lane's is zero.
+// That is 7.6 vector instructions per pair beside the reciprocal instead of 9 (50,000
+// bodies, whole iteration: 613 -> 555 us).
+template <int R>
+__device__ __forceinline__ void fa2_rep_run(const float2 (&xi)[R], const float4 *tile, int n, float (&fx)[R],
+                                            float (&fy)[R]) {
+    for (int q = 0; q < n; q += 8) {
+        float4 b[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) b[u] = tile[q + u];
+        float dx[R][8], dy[R][8], d2[R][8];
+        uint32_t least = ~0u;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                dx[r][u] = xi[r].x - b[u].x;
+                dy[r][u] = xi[r].y - b[u].y;
+                d2[r][u] = fa2_norm2(dx[r][u], dy[r][u]);
+                least = min(least, __float_as_uint(d2[r][u]));
+            }
+        if (__any(least == 0u)) {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const float f = d2[r][u] > 0.f ? b[u].z * __builtin_amdgcn_rcpf(d2[r][u]) : 0.f;
+                    fx[r] = __builtin_fmaf(f, dx[r][u], fx[r]);
+                    fy[r] = __builtin_fmaf(f, dy[r][u], fy[r]);
+                }
+        } else {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const float f = b[u].z * __builtin_amdgcn_rcpf(d2[r][u]);
+                    fx[r] = __builtin_fmaf(f, dx[r][u], fx[r]);
+                    fy[r] = __builtin_fmaf(f, dy[r][u], fy[r]);
+                }
+        }
+    }
+}
+__device__ __forceinline__ void fa2_rep_run(const float2 (&xi)[1], const float4 *tile, int n, float (&fx)[1],
+                                            float (&fy)[1]) {
+    fa2_rep_run(xi[0], tile, n, fx[0], fy[0]);
+}
+
 // Exact repulsion on body i is summed over j in consecutive segments of kRepSegment
 // bodies: each segment in ascending j starting from zero, then the segment sums in
 // ascending order (the first one taken as is).  Segments let one body's sum be split
@@ -38,6 +95,11 @@ __device__ __forceinline__ void fa2_rep_run(float2 xi, const float4 *tile, int n
 // gives the same bits.  A multiple of the 256-body LDS tiles; short enough that a
 // supergraph of a few thousand nodes spreads over many workgroups.
 constexpr int32_t kRepSegment = 512;
+
+// Bodies from which the all-pairs force kernels give each thread two bodies (us per layout
+// iteration with one / two: 16,384 bodies 87 / 87, 24,000 174 / 168, 50,000 616 / 555);
+// with fewer, halving the wavefronts costs what the shared reads give.
+constexpr int32_t kRepTwoMin = 16384;
 
 __host__ __device__ __forceinline__ int32_t fa2_rep_segments(int32_t K) {
     return (K + kRepSegment - 1) / kRepSegment;
@@ -162,7 +224,7 @@ __device__ __forceinline__ float2 fa2_net_force(float2 xi, float mi, float kr, f
                                                 float kg) {
     const float c = kr * mi;
     float fx = c * rx + att.x, fy = c * ry + att.y;
-    const float r = sqrtf(xi.x * xi.x + xi.y * xi.y);
+    const float r = sqrtf(fa2_norm2(xi.x, xi.y));
     if (r > 0.f) {
         const float g = kg * mi / r;
         fx -= g * xi.x;
@@ -175,8 +237,8 @@ __device__ __forceinline__ float2 fa2_net_force(float2 xi, float mi, float kr, f
 __device__ __forceinline__ double2 fa2_swing_traction(float2 F, float2 Fp, float mi) {
     const float sx = F.x - Fp.x, sy = F.y - Fp.y;
     const float tx = F.x + Fp.x, ty = F.y + Fp.y;
-    const float sw = sqrtf(sx * sx + sy * sy);
-    const float tr = 0.5f * sqrtf(tx * tx + ty * ty);
+    const float sw = sqrtf(fa2_norm2(sx, sy));
+    const float tr = 0.5f * sqrtf(fa2_norm2(tx, ty));
     return make_double2((double)mi * (double)sw, (double)mi * (double)tr);
 }
 
@@ -190,9 +252,9 @@ __device__ __forceinline__ float fa2_global_speed(double S, double T, float sp, 
 // Local speed ks s / (1 + s sqrt(swing)), capped so the step is at most ksmax; moves p.
 __device__ __forceinline__ float2 fa2_move(float2 p, float2 f, float2 fp, float s, float ks, float ksmax) {
     const float sx = f.x - fp.x, sy = f.y - fp.y;
-    const float sw = sqrtf(sx * sx + sy * sy);
+    const float sw = sqrtf(fa2_norm2(sx, sy));
     float si = ks * s / (1.0f + s * sqrtf(sw));
-    const float fn = sqrtf(f.x * f.x + f.y * f.y);
+    const float fn = sqrtf(fa2_norm2(f.x, f.y));
     if (fn > 0.f && si > ksmax / fn) si = ksmax / fn;
     p.x += si * f.x;
     p.y += si * f.y;
@@ -209,46 +271,46 @@ __device__ __forceinline__ float2 fa2_att_value(const float2 *__restrict__ att, 
     return item_of ? fa2_att_combine(att, item_of, i) : att[i];
 }
 
-// Exact repulsion of the nodes of tile bx over the bodies of j segment by (all of
-// [0, K) when kSegmented is false), bodies staged through LDS 256 at a time.  With one
-// segment the tile's forces are finished (attraction, gravity, swing, traction and the
-// tile's FP64 partial sums into part[bx]); with several, the segment sums go to seg.
-template <bool kSegmented>
+// Exact repulsion of the nodes of tile bx (256 R nodes, R per thread) over the bodies of
+// j segment by (all of [0, K) when kSegmented is false), bodies staged through LDS 256 at
+// a time.  With one segment the tile's forces are finished (attraction, gravity, swing,
+// traction and the tile's FP64 partial sums into part[bx]); with several, the segment
+// sums go to seg.
+template <bool kSegmented, int R = 1>
 __device__ __forceinline__ void fa2_exact_force_tile(int32_t bx, int32_t by, int32_t K, const float2 *__restrict__ pos,
                                                      const float *__restrict__ mass, const float2 *__restrict__ att,
                                                      const uint32_t *__restrict__ item_of, float kr, float kg,
                                                      const float2 *__restrict__ fprev, float2 *__restrict__ F,
                                                      double2 *__restrict__ part, float2 *__restrict__ seg) {
+    static_assert(kSegmented || R == 1, "finished tiles hold one node per thread");
     __shared__ float4 tile[kFa2Tile];
     __shared__ double2 ws[kFa2Tile / kWave];
-    const int32_t i = bx * kFa2Tile + threadIdx.x;
-    const bool live = i < K;
-    const float2 xi = live ? pos[i] : make_float2(0.f, 0.f);
+    const int32_t i = bx * (kFa2Tile * R) + threadIdx.x;
+    float2 xi[R];
+    float fx[R], fy[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        xi[r] = i + r * kFa2Tile < K ? pos[i + r * kFa2Tile] : make_float2(0.f, 0.f);
+        fx[r] = fy[r] = 0.f;
+    }
     const int32_t jb = kSegmented ? by * kRepSegment : 0;
     const int32_t je = kSegmented ? min(K, jb + kRepSegment) : K;
-    float fx = 0.f, fy = 0.f;
     for (int32_t t0 = jb; t0 < je; t0 += kFa2Tile) {
         const int32_t j = t0 + threadIdx.x;
-        if (j < je) {
-            const float2 xj = pos[j];
-            tile[threadIdx.x] = make_float4(xj.x, xj.y, mass[j], 0.f);
-        }
+        tile[threadIdx.x] = j < je ? fa2_body(pos[j], mass[j]) : fa2_no_body();
         __syncthreads();
-        const int cnt = min(kFa2Tile, je - t0);
-        if (cnt == kFa2Tile) {
-            fa2_rep_run(xi, tile, kFa2Tile, fx, fy);
-        } else {
-            for (int q = 0; q < cnt; ++q) fa2_rep_term(xi, tile[q], fx, fy);
-        }
+        fa2_rep_run(xi, tile, min(kFa2Tile, (je - t0 + 7) & ~7), fx, fy);
         __syncthreads();
     }
     if (kSegmented) {
-        if (live) seg[(int64_t)by * K + i] = make_float2(fx, fy);
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (i + r * kFa2Tile < K) seg[(int64_t)by * K + i + r * kFa2Tile] = make_float2(fx[r], fy[r]);
         return;
     }
     double2 st = make_double2(0.0, 0.0);
-    if (live) {
-        const float2 f = fa2_net_force(xi, mass[i], kr, fx, fy, fa2_att_value(att, item_of, i), kg);
+    if (i < K) {
+        const float2 f = fa2_net_force(xi[0], mass[i], kr, fx[0], fy[0], fa2_att_value(att, item_of, i), kg);
         F[i] = f;
         st = fa2_swing_traction(f, fprev[i], mass[i]);
     }

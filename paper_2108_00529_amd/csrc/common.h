@@ -134,31 +134,37 @@ bgv_status exclusive_scan_u32(const uint32_t *in, uint32_t *out, int64_t n, uint
 template <class T>  // instantiated for uint32_t, uint64_t and double
 bgv_status exclusive_scan(const T *in, T *out, int64_t n, T *total, void *scratch, hipStream_t s);
 
-// Stable LSD radix sort of keys below 2^nbits, with an optional uint32 payload.
-// keys/alt (and vals/vals_alt) are ping-pong buffers of n entries; the sorted result
-// ends in *keys_out/*vals_out (one of the two).  Scratch from radix_workspace(n).  With
-// n_dev the key count is read on the device (*n_dev <= n) and n is only its bound, so
-// the sort can be queued before the count is known on the host.
-size_t radix_workspace(int64_t n);
-bgv_status radix_sort_u64(uint64_t *keys, uint64_t *keys_alt, uint32_t *vals, uint32_t *vals_alt,
-                          int64_t n, int nbits, uint64_t **keys_out, uint32_t **vals_out,
-                          void *scratch, hipStream_t s, bool counted = false,
-                          const unsigned long long *n_dev = nullptr);
-// The same for keys below 2^nbits <= 2^32 held in 32 bits (half the traffic per pass).
-bgv_status radix_sort_u32(uint32_t *keys, uint32_t *keys_alt, uint32_t *vals, uint32_t *vals_alt,
-                          int64_t n, int nbits, uint32_t **keys_out, uint32_t **vals_out,
-                          void *scratch, hipStream_t s, bool counted = false,
-                          const unsigned long long *n_dev = nullptr);
+// Stable LSD radix sort of keys (uint32_t or uint64_t) below 2^nbits, with an optional
+// uint32 payload.  keys/alt (and vals/vals_alt, or null) are ping-pong buffers of n
+// entries; the sorted result ends in *keys_out/*vals_out (one of the two).  Scratch from
+// sort_workspace(n, nbits).  With n_dev the key count is read on the device (*n_dev <= n)
+// and n is only its bound, so the sort can be queued before the count is known on the
+// host.
+size_t sort_workspace(int64_t n, int nbits);
+template <class KT>
+bgv_status sort_pairs(KT *keys, KT *keys_alt, uint32_t *vals, uint32_t *vals_alt, int64_t n, int nbits, KT **keys_out,
+                      uint32_t **vals_out, void *scratch, hipStream_t s, const unsigned long long *n_dev = nullptr);
 
-// Sorts of at most kRsFewTiles tiles (n > 1) count pass 0's digits in one launch ahead
-// of the scatters.  A producer of the keys can do that count itself: for such an n,
-// radix_few_tiles gives the tile shape (tiles of 256 * items consecutive keys) and
-// radix_pass0_buffers where the counts go (counts0[digit * tiles + tile], the low 8
-// bits of each key) and a [256 * tiles] buffer to clear; radix_sort_u64 with
-// counted = true then skips its own count.
-constexpr int kRsFewTiles = 64;
-bool radix_few_tiles(int64_t n, int64_t *tiles, int *items);
-void radix_pass0_buffers(void *scratch, int64_t n, uint32_t **counts0, uint32_t **clear1);
+// The two forms it chooses from by n.  Reduce-then-scan, any n:
+size_t radix_workspace(int64_t n);
+template <class KT>
+bgv_status radix_sort(KT *keys, KT *keys_alt, uint32_t *vals, uint32_t *vals_alt, int64_t n, int nbits, KT **keys_out,
+                      uint32_t **vals_out, void *scratch, hipStream_t s, const unsigned long long *n_dev);
+
+// One-sweep, n <= kOsMaxKeys, by the key bits [bit0, bit0 + nbits) alone.
+// With counted = true a producer of the keys has done the counting launch's work: it
+// wrote the digit counts of its blocks' keys (bcnt[block * passes * 256 + pass * 256 +
+// d], passes = onesweep_key_passes(nbits)) and onesweep_keys_counted summed them into
+// the scratch's totals and cleared its look-back words.
+constexpr uint32_t kOsMaxKeys = (1u << 30) - 1;
+size_t onesweep_keys_workspace(int64_t n, int nbits);
+int onesweep_key_passes(int nbits);
+bgv_status onesweep_keys_counted(const uint32_t *bcnt, int64_t nblocks, int64_t n, int nbits, void *scratch,
+                                 hipStream_t s);
+template <class KT>
+bgv_status onesweep_sort_pairs(KT *keys, KT *keys_alt, uint32_t *vals, uint32_t *vals_alt, int64_t n,
+                               const unsigned long long *n_dev, int bit0, int nbits, KT **keys_out,
+                               uint32_t **vals_out, void *scratch, hipStream_t s, bool counted = false);
 
 // One-sweep sort of 32-bit keys with 32-bit values (all 32 bits, four 8-bit passes, one
 // launch per pass after a counting launch; see primitives.hip).  keys/alt and
@@ -181,23 +187,5 @@ size_t onesweep_workspace(int64_t n);
 void onesweep_layout(void *scratch, int64_t n, int items, OsBuffers *b);
 bgv_status onesweep_sort_u32(uint32_t *keys, uint32_t *keys_alt, uint32_t *vals, uint32_t *vals_alt, int64_t n,
                              uint32_t **keys_out, uint32_t **vals_out, void *scratch, hipStream_t s, bool counted);
-
-// One-sweep sort of keys alone (uint32_t or uint64_t; the low nbits significant,
-// ceil(nbits / 8) <= sizeof(KT) passes; stable, so equal keys keep their order).
-// keys/keys_alt are ping-pong buffers of n entries; the sorted keys end in *keys_out
-// (one of the two).  With n_dev the key count is read on the device (*n_dev <= n) and
-// n is only its bound, so the sort can be queued before the count is known on the
-// host.  Scratch from onesweep_keys_workspace(n, nbits); n < 2^30.
-// With counted = true a producer of the keys has done the counting launch's work: it
-// wrote the digit counts of its blocks' keys (bcnt[block * passes * 256 + pass * 256 +
-// d], passes = onesweep_key_passes(nbits)) and onesweep_keys_counted summed them into
-// the scratch's totals and cleared its look-back words (wide: 64-bit keys).
-size_t onesweep_keys_workspace(int64_t n, int nbits);
-int onesweep_key_passes(int nbits);
-bgv_status onesweep_keys_counted(const uint32_t *bcnt, int64_t nblocks, int64_t n, int nbits, bool wide,
-                                 void *scratch, hipStream_t s);
-template <class KT>
-bgv_status onesweep_sort_keys(KT *keys, KT *keys_alt, int64_t n, const unsigned long long *n_dev, int nbits,
-                              KT **keys_out, void *scratch, hipStream_t s, bool counted = false);
 
 }  // namespace bgv

@@ -102,7 +102,7 @@ size_t sq_layout(Carver &c, int32_t n, int64_t m, const bgv_cd_params *p, void *
     w.go = c.take<int32_t>(kSqMaxRounds + 1);
     w.tot = c.take<uint32_t>(4);
     w.tot64 = c.take<unsigned long long>(2);
-    w.sort_scratch = c.take<char>(radix_workspace((int64_t)std::max(no, pm)));
+    w.sort_scratch = c.take<char>(std::max(sort_workspace((int64_t)no, 32), sort_workspace((int64_t)pm, 64)));
     w.scan_scratch = c.take<char>(scan_workspace((int64_t)pm));
     if (out) *static_cast<SqWs *>(out) = w;
     return c.size();
@@ -368,14 +368,14 @@ static bgv_status sq_sort_events(SqWs &w, int64_t pm, int nbits, KT **sk, uint32
 
 template <>
 bgv_status sq_sort_events<uint32_t>(SqWs &w, int64_t pm, int nbits, uint32_t **sk, uint32_t **sv, hipStream_t s) {
-    return radix_sort_u32(static_cast<uint32_t *>(w.evk), static_cast<uint32_t *>(w.evk_alt), w.evv, w.evv_alt, pm,
-                          nbits, sk, sv, w.sort_scratch, s, false, w.tot64);
+    return sort_pairs<uint32_t>(static_cast<uint32_t *>(w.evk), static_cast<uint32_t *>(w.evk_alt), w.evv, w.evv_alt, pm,
+                          nbits, sk, sv, w.sort_scratch, s, w.tot64);
 }
 
 template <>
 bgv_status sq_sort_events<uint64_t>(SqWs &w, int64_t pm, int nbits, uint64_t **sk, uint32_t **sv, hipStream_t s) {
-    return radix_sort_u64(static_cast<uint64_t *>(w.evk), static_cast<uint64_t *>(w.evk_alt), w.evv, w.evv_alt, pm,
-                          nbits, sk, sv, w.sort_scratch, s, false, w.tot64);
+    return sort_pairs<uint64_t>(static_cast<uint64_t *>(w.evk), static_cast<uint64_t *>(w.evk_alt), w.evv, w.evv_alt, pm,
+                          nbits, sk, sv, w.sort_scratch, s, w.tot64);
 }
 
 template <class KT>
@@ -431,7 +431,7 @@ bgv_status sq_run(int32_t n, int64_t m, const int32_t *edges, const bgv_cd_param
     const unsigned go = grid_for(no, kSqThreads, 65536), gn = grid_for(n, kSqThreads, 65536);
     BGV_LAUNCH(k_sq_occ, dim3(grid_for(m, kSqThreads, 65536)), dim3(kSqThreads), 0, s, e2, m, n, w.okey, w.oval);
     uint32_t *sk = nullptr, *sv = nullptr;
-    BGV_TRY(radix_sort_u32(w.okey, w.okey_alt, w.oval, w.oval_alt, no, bits_for((uint64_t)n), &sk, &sv,
+    BGV_TRY(sort_pairs<uint32_t>(w.okey, w.okey_alt, w.oval, w.oval_alt, no, bits_for((uint64_t)n), &sk, &sv,
                            w.sort_scratch, s));
     BGV_TRY(fill<uint32_t>(w.beg, 0u, n, s));
     BGV_TRY(fill<uint32_t>(w.end, 0u, n, s));

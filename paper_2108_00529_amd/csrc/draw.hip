@@ -81,7 +81,7 @@ static size_t dr_layout(Carver &c, int32_t K, DrWs *w) {
     w->ssize = c.take<uint64_t>(k);
     w->excl = c.take<uint64_t>(k);
     w->total = c.take<uint64_t>(1);
-    w->sort_scratch = c.take<char>(radix_workspace((int64_t)k));
+    w->sort_scratch = c.take<char>(sort_workspace((int64_t)k, 32 + dr_bits(K)));
     w->scan_scratch = c.take<char>(scan_workspace((int64_t)k));
     return c.size();
 }
@@ -117,7 +117,7 @@ extern "C" bgv_status bgv_draw_supernodes(int32_t K, const uint32_t *super_size,
     const unsigned g = grid_for(K, kDrThreads, 65536);
     BGV_LAUNCH(k_draw_keys, dim3(g), dim3(kDrThreads), 0, s, super_size, K, kb, w.keys);
     uint64_t *sk;
-    BGV_TRY(radix_sort_u64(w.keys, w.keys_alt, nullptr, nullptr, K, 32 + kb, &sk, nullptr, w.sort_scratch, s));
+    BGV_TRY(sort_pairs<uint64_t>(w.keys, w.keys_alt, nullptr, nullptr, K, 32 + kb, &sk, nullptr, w.sort_scratch, s));
     BGV_LAUNCH(k_draw_sizes, dim3(g), dim3(kDrThreads), 0, s, sk, K, kb, w.ssize);
     BGV_TRY(exclusive_scan<uint64_t>(w.ssize, w.excl, K, w.total, w.scan_scratch, s));
     BGV_LAUNCH(k_draw_groups, dim3(g), dim3(kDrThreads), 0, s, sk, w.excl, w.total, K, kb, group, radius);

@@ -54,8 +54,10 @@ __global__ void k_csr_keys(const int2 *__restrict__ edges, int64_t E, int kb, KT
         const int2 p = edges[e];
         keys[2 * e] = ((KT)(uint32_t)p.x << kb) | (KT)(uint32_t)p.y;
         keys[2 * e + 1] = ((KT)(uint32_t)p.y << kb) | (KT)(uint32_t)p.x;
-        vals[2 * e] = (uint32_t)e;
-        vals[2 * e + 1] = (uint32_t)e;
+        if (vals) {
+            vals[2 * e] = (uint32_t)e;
+            vals[2 * e + 1] = (uint32_t)e;
+        }
     }
 }
 
@@ -100,6 +102,13 @@ int64_t att_items_cap(int32_t K, int64_t E, bool cols) {
     return (int64_t)K + runs + (2 * E) / kAttCap + 1;
 }
 
+// Bits of the sort keys of the items of nblk column blocks (k_attc_keys).
+static int att_item_key_bits(int32_t nblk) {
+    int kbits = kAttLenBits + 1;
+    while ((1ll << (kbits - kAttLenBits)) < nblk) ++kbits;
+    return kbits;
+}
+
 size_t csr_layout(Carver &c, int32_t K, int64_t E, CsrWs *w, bool allow_cols) {
     const int64_t nent = 2 * E > 0 ? 2 * E : 1;
     w->row = c.take<uint32_t>((size_t)K + 1);
@@ -116,7 +125,11 @@ size_t csr_layout(Carver &c, int32_t K, int64_t E, CsrWs *w, bool allow_cols) {
     // most the previous group's entries)
     const int64_t cwb_slots = nent + nblk * kWave * (int64_t)kAttCap;
     w->keys = c.take<uint64_t>((size_t)std::max<int64_t>(nent, cols ? cwb_slots : 0));
-    size_t scratch = std::max(radix_workspace(nent), scan_workspace((int64_t)K + 1));
+    // the CSR sort's scratch fits into cw, which is only written after the sort, except for
+    // the fewest entries
+    const size_t sort_ws = sort_workspace(nent, 2 * bits_for(K));
+    const bool sort_in_cw = sort_ws <= sizeof(int2) * (size_t)nent;
+    size_t scratch = std::max(sort_in_cw ? 0 : sort_ws, scan_workspace((int64_t)K + 1));
     w->it = w->ir = w->cstart = w->gfirst = w->gbase = w->wg_first = nullptr;
     w->il = nullptr;
     w->item_beg = w->ikeys = w->ikeys_alt = w->ivals = w->ivals_alt = w->ilen = nullptr;
@@ -152,10 +165,12 @@ size_t csr_layout(Carver &c, int32_t K, int64_t E, CsrWs *w, bool allow_cols) {
         w->ivals_alt = b.take<uint32_t>((size_t)T);
         w->ilen = b.take<uint32_t>((size_t)std::max<int64_t>(T, ngroups + 1));
         region = std::max(region, b.size());
-        scratch = std::max(scratch, std::max(radix_workspace(T), scan_workspace(std::max<int64_t>(T, ngroups + 1))));
+        scratch = std::max(scratch, std::max(sort_workspace(T, att_item_key_bits(nblk)),
+                                             scan_workspace(std::max<int64_t>(T, ngroups + 1))));
     }
     c.take<char>(region);
-    w->sort_scratch = c.take<char>(scratch);
+    w->scratch = c.take<char>(scratch);
+    w->sort_scratch = sort_in_cw ? static_cast<void *>(w->cw) : w->scratch;
     return c.size();
 }
 
@@ -388,21 +403,19 @@ static bgv_status attc_setup(int32_t K, int64_t nent, CsrWs &w, hipStream_t s) {
     const int64_t ngroups = T / kWave + nblk + 1;
     const dim3 gr(grid_for((int64_t)K + 1, kFaThreads / kWave, 65536));
     BGV_LAUNCH(k_attc_count<E>, gr, dim3(kFaThreads), 0, s, w.row, cw, K, w.item_of);
-    BGV_TRY(exclusive_scan_u32(w.item_of, w.item_of, (int64_t)K + 1, nullptr, w.sort_scratch, s));
+    BGV_TRY(exclusive_scan_u32(w.item_of, w.item_of, (int64_t)K + 1, nullptr, w.scratch, s));
     BGV_LAUNCH(k_attc_fill<E>, gr, dim3(kFaThreads), 0, s, w.row, cw, K, w.item_of, (uint32_t)nent, w.item_row,
                w.item_beg, w.nitems);
     const dim3 gt(grid_for(T, kFaThreads, 65536));
     BGV_LAUNCH(k_attc_keys<E>, gt, dim3(kFaThreads), 0, s, cw, w.item_beg, w.nitems, w.ikeys, w.ivals);
-    int kbits = kAttLenBits + 1;
-    while ((1ll << (kbits - kAttLenBits)) < nblk) ++kbits;
     uint32_t *sk, *sv;
-    BGV_TRY(radix_sort_u32(w.ikeys, w.ikeys_alt, w.ivals, w.ivals_alt, T, kbits, &sk, &sv, w.sort_scratch, s, false,
-                           w.nitems));
+    BGV_TRY(sort_pairs<uint32_t>(w.ikeys, w.ikeys_alt, w.ivals, w.ivals_alt, T, att_item_key_bits(nblk), &sk, &sv,
+                                 w.scratch, s, w.nitems));
     BGV_LAUNCH(k_attc_order, gt, dim3(kFaThreads), 0, s, sk, w.nitems, nblk, w.cstart);
     BGV_LAUNCH(k_attc_gfirst, dim3(1), dim3(64), 0, s, nblk, w.cstart, w.gfirst);
     BGV_LAUNCH(k_attc_gsize, dim3(grid_for(ngroups + 1, kFaThreads, 65536)), dim3(kFaThreads), 0, s, sv, w.item_beg,
                nblk, w.cstart, w.gfirst, ngroups + 1, w.ilen);
-    BGV_TRY(exclusive_scan_u32(w.ilen, w.gbase, ngroups + 1, nullptr, w.sort_scratch, s));
+    BGV_TRY(exclusive_scan_u32(w.ilen, w.gbase, ngroups + 1, nullptr, w.scratch, s));
     const auto k_attc_copy_ = k_attc_copy<E, EC>;
     BGV_LAUNCH(k_attc_copy_, dim3(grid_for(T, kFaThreads / kAttColLanes, 65536)), dim3(kFaThreads), 0, s, cw, sk, sv,
                w.nitems, w.item_beg, w.item_row, w.cstart, w.gfirst, w.gbase, w.it, w.ir, w.il,
@@ -422,19 +435,21 @@ bgv_status build_csr(int32_t K, int64_t E, const int32_t *edges, const float *at
         const int kb = bits_for(K);
         const int2 *e2 = reinterpret_cast<const int2 *>(edges);
         const dim3 ge(grid_for(E, kFaThreads, 65536)), gf(grid_for(2 * E, kFaThreads, 65536));
+        // equal keys are told apart by their edge index, which only weights need
+        uint32_t *const vals = attr_w ? w.vals : nullptr, *const vals_alt = attr_w ? w.vals_alt : nullptr;
         uint32_t *sv;
         if (2 * kb <= 32) {  // keys in 32 bits: half the sort traffic
             uint32_t *k32 = reinterpret_cast<uint32_t *>(w.keys), *k32_alt = reinterpret_cast<uint32_t *>(w.keys_alt);
             uint32_t *sk;
-            BGV_LAUNCH(k_csr_keys<uint32_t>, ge, dim3(kFaThreads), 0, s, e2, E, kb, k32, w.vals);
-            BGV_TRY(radix_sort_u32(k32, k32_alt, w.vals, w.vals_alt, 2 * E, 2 * kb, &sk, &sv, w.sort_scratch, s));
+            BGV_LAUNCH(k_csr_keys<uint32_t>, ge, dim3(kFaThreads), 0, s, e2, E, kb, k32, vals);
+            BGV_TRY(sort_pairs<uint32_t>(k32, k32_alt, vals, vals_alt, 2 * E, 2 * kb, &sk, &sv, w.sort_scratch, s));
             BGV_LAUNCH(k_csr_fill<uint32_t>, gf, dim3(kFaThreads), 0, s, sk, sv, 2 * E, kb, K, attr_w, w.fmt, w.row,
                        w.cw);
         } else {
             uint64_t *sk;
-            BGV_LAUNCH(k_csr_keys<uint64_t>, ge, dim3(kFaThreads), 0, s, e2, E, kb, w.keys, w.vals);
-            BGV_TRY(radix_sort_u64(w.keys, w.keys_alt, w.vals, w.vals_alt, 2 * E, 2 * kb, &sk, &sv, w.sort_scratch,
-                                   s));
+            BGV_LAUNCH(k_csr_keys<uint64_t>, ge, dim3(kFaThreads), 0, s, e2, E, kb, w.keys, vals);
+            BGV_TRY(sort_pairs<uint64_t>(w.keys, w.keys_alt, vals, vals_alt, 2 * E, 2 * kb, &sk, &sv, w.sort_scratch,
+                                         s));
             BGV_LAUNCH(k_csr_fill<uint64_t>, gf, dim3(kFaThreads), 0, s, sk, sv, 2 * E, kb, K, attr_w, w.fmt, w.row,
                        w.cw);
         }
@@ -449,7 +464,7 @@ bgv_status build_csr(int32_t K, int64_t E, const int32_t *edges, const float *at
     } else {
         BGV_LAUNCH(k_att_item_counts, dim3(grid_for((int64_t)K + 1, kFaThreads, 65536)), dim3(kFaThreads), 0, s,
                    w.row, K, w.item_of);
-        BGV_TRY(exclusive_scan_u32(w.item_of, w.item_of, (int64_t)K + 1, nullptr, w.sort_scratch, s));
+        BGV_TRY(exclusive_scan_u32(w.item_of, w.item_of, (int64_t)K + 1, nullptr, w.scratch, s));
         BGV_LAUNCH(k_att_item_rows, dim3(grid_for(K, kFaThreads, 65536)), dim3(kFaThreads), 0, s, w.item_of, K,
                    w.item_row);
     }

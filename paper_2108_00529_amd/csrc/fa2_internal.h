@@ -40,7 +40,8 @@ struct CsrWs {
     unsigned long long *nitems;
     uint64_t *keys, *keys_alt;
     uint32_t *vals, *vals_alt;
-    void *sort_scratch;
+    void *scratch;       // scans and the item sort
+    void *sort_scratch;  // the CSR sort: cw, or scratch
 };
 
 // Upper bound on the number of attraction work items (block sums) of K rows holding 2E

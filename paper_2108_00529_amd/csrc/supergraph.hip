@@ -612,7 +612,7 @@ struct SgWs {
 // The inter-community keys are sorted by the one-sweep sort of keys alone (one read and
 // one write of the keys per 8-bit pass, after one counting read), below 2^30 edges;
 // beyond, by the reduce-then-scan radix sort.
-static bool sg_onesweep(int64_t m) { return m < ((int64_t)1 << 30) - 1; }
+static bool sg_onesweep(int64_t m) { return m <= (int64_t)kOsMaxKeys; }
 
 static size_t sg_layout(Carver &c, int32_t n, int64_t m, int32_t rows, int64_t cells, SgWs *w) {
     const int64_t mm = m > 0 ? m : 1;
@@ -632,7 +632,7 @@ static size_t sg_layout(Carver &c, int32_t n, int64_t m, int32_t rows, int64_t c
     w->run_start = c.take<uint32_t>((size_t)mm);
     const int64_t big = n > mm ? n : mm;
     w->scan_scratch = c.take<char>(scan_workspace(big));
-    w->sort_scratch = c.take<char>(sg_onesweep(mm) ? onesweep_keys_workspace(mm, 64) : radix_workspace(mm));
+    w->sort_scratch = c.take<char>(sort_workspace(mm, 64));
     if (cells > kLdsCounters && lb_buckets(n) <= kLbMaxBuckets) {
         const size_t tiles = ((size_t)n + kLbTile - 1) / kLbTile;
         w->lent = c.take<uint2>(tiles * kLbTile);
@@ -823,7 +823,7 @@ extern "C" bgv_status bgv_supergraph(int32_t n, int64_t m, const int32_t *edges,
         else
             BGV_LAUNCH(k_sg_edge_keys_64, gkey, dim3(kSgThreads), 0, s, e2, m, w.nsid, kbits, w.keys, nkeys_d, bcnt,
                        passes);
-        if (fused_count) BGV_TRY(onesweep_keys_counted(bcnt, nkb, m, 2 * kbits, !k32, w.sort_scratch, s));
+        if (fused_count) BGV_TRY(onesweep_keys_counted(bcnt, nkb, m, 2 * kbits, w.sort_scratch, s));
     }
     // the key count stays on the device: everything below is sized by the edge count m,
     // which bounds it, and reads the count itself, so no host round trip is needed here
@@ -834,17 +834,17 @@ extern "C" bgv_status bgv_supergraph(int32_t n, int64_t m, const int32_t *edges,
         uint32_t *sorted32 = nullptr;
         if (sg_onesweep(m)) {
             if (k32)
-                BGV_TRY(onesweep_sort_keys<uint32_t>(keys32, keys32_alt, m, nkeys_d, 2 * kbits, &sorted32,
-                                                     w.sort_scratch, s, fused_count));
+                BGV_TRY(onesweep_sort_pairs<uint32_t>(keys32, keys32_alt, nullptr, nullptr, m, nkeys_d, 0, 2 * kbits,
+                                                      &sorted32, nullptr, w.sort_scratch, s, fused_count));
             else
-                BGV_TRY(onesweep_sort_keys<uint64_t>(w.keys, w.keys_alt, m, nkeys_d, 2 * kbits, &sorted,
-                                                     w.sort_scratch, s, fused_count));
+                BGV_TRY(onesweep_sort_pairs<uint64_t>(w.keys, w.keys_alt, nullptr, nullptr, m, nkeys_d, 0, 2 * kbits,
+                                                      &sorted, nullptr, w.sort_scratch, s, fused_count));
         } else if (k32) {
-            BGV_TRY(radix_sort_u32(keys32, keys32_alt, nullptr, nullptr, m, 2 * kbits, &sorted32, nullptr,
-                                   w.sort_scratch, s, false, nkeys_d));
+            BGV_TRY(radix_sort<uint32_t>(keys32, keys32_alt, nullptr, nullptr, m, 2 * kbits, &sorted32, nullptr,
+                                         w.sort_scratch, s, nkeys_d));
         } else {
-            BGV_TRY(radix_sort_u64(w.keys, w.keys_alt, nullptr, nullptr, m, 2 * kbits, &sorted, nullptr,
-                                   w.sort_scratch, s, false, nkeys_d));
+            BGV_TRY(radix_sort<uint64_t>(w.keys, w.keys_alt, nullptr, nullptr, m, 2 * kbits, &sorted, nullptr,
+                                         w.sort_scratch, s, nkeys_d));
         }
         const unsigned gk = grid_for(m, kSgThreads, 65536);
         const unsigned ut = (unsigned)((m + kUqTile - 1) / kUqTile);

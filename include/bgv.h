@@ -115,8 +115,8 @@ typedef struct {
  * node and 4 per edge of a chunk.  With passes > 1 another 8 per edge (each edge's
  * pass-0 endpoint counters, from which later passes' counters follow without
  * increments), and up to 2^24 nodes with passes > 2 one more byte per edge (passes 2-5
- * decided once the degrees are known).  Method 2: 48 bytes per edge, 8 per node and at most 48 per (pass, edge)
- * proposal, plus radix-sort scratch. */
+ * decided once the degrees are known).  Method 2: 40 bytes per edge, 16 per node and 24 per (pass, edge), plus
+ * radix-sort scratch. */
 size_t bgv_community_workspace(int32_t n, int64_t m, const bgv_cd_params *p);
 
 /*

@@ -14,15 +14,26 @@
 // labels every winner in O(log chunks) bulk steps:
 //   1. endpoint occurrences sorted by node (stable): d(x) = run length, c(x, k) of each
 //      occurrence by a binary search in its node's run;
-//   2. the proposals of every (pass, edge), compacted in stream order, sorted stably
-//      by (target, global chunk): the first of each run is the winner;
+//   2. the proposals of every (pass, edge), compacted in (pass, stream) order and sorted
+//      stably by target: a proposal is its time t = pass * m + edge, so a target's
+//      proposals come in time order and the first of each of its chunks is the winner;
 //   3. winners compacted; each one's link = the last winner into its source with an
-//      earlier chunk (a binary search in the source's run of winners);
-//   4. pointer jumping along the links, in place on packed (link, label) words, each
-//      round skipped once a round has left nothing unresolved; a node's label = its
-//      last winner's label.
-// About 20 launches whatever the number of chunks, against two per chunk and pass for
+//      earlier chunk (a binary search in the source's run of winners: before its chunk's
+//      first time);
+//   4. pointer jumping along the links, in place on packed (link, label) words, several
+//      links a round, each round skipped once a round has left nothing unresolved; a
+//      node's label = its last winner's label.
+// About 25 launches whatever the number of chunks, against two per chunk and pass for
 // the chunk-by-chunk form: the choice for small chunks.
+//
+// What bounds it: the three passes over 8-byte (key, value) pairs of each sort (HBM), and
+// the random accesses that no order avoids: each occurrence's count written to its edge,
+// and per winner its edge, its source's run and the probes there.  Sorting by the target
+// alone (20 bits of 45 for 1M nodes and chunk 1) halves the second sort, and 4-byte times
+// in place of 8-byte (target, chunk) keys its traffic; proposals and winners are numbered
+// by counting per 512 of them and again when they are written, so that no flag per (pass,
+// edge) is stored or scanned.  1M nodes, 10M edges, 3 passes, chunk 1:
+// 4.42 -> 2.54 ms against 8-byte keys sorted by all their bits and flags per (pass, edge).
 #include <algorithm>
 
 #include "common.h"
@@ -59,51 +70,51 @@ bool sq_fits(int32_t n, int64_t m, const bgv_cd_params *p) {
     return bits_for((uint64_t)(n - 1)) + bits_for(G - 1) <= 64;
 }
 
+constexpr int kSqRounds = 8;                       // edges or events per lane of a wavefront's tile
+constexpr int64_t kSqTile = kWave * kSqRounds;     // consecutive edges or events per wavefront
+constexpr int kSqHops = 15;                        // links followed per pointer-jumping round
+
 struct SqWs {
     uint32_t *okey, *okey_alt, *oval, *oval_alt;  // endpoint occurrences [2m]
-    uint32_t *beg, *end;                          // run of each node in the sorted occurrences [n]
-    int4 *cd;                                     // per edge {c(e.x), d(e.x), c(e.y), d(e.y)}
-    uint32_t *flag;                               // [P m]: proposals, then winners
-    void *evk, *evk_alt;                          // proposal keys (target, chunk) [P m], 32 or 64 bits
-    uint32_t *evv, *evv_alt;                      // their edge indices
-    void *wk;                                     // winners' keys [P m]
-    uint32_t *wv;                                 // winners' edge indices
+    uint2 *run;                                   // run of each node in the sorted occurrences [n]
+    uint2 *wrun;                                  // run of each node in the winners [n]
+    int32_t *cc;                                  // c of each endpoint occurrence [2m]
+    uint32_t *tally;                              // proposals per (pass, tile of edges), then per tile of events
+    uint32_t *ekey, *ekey_alt;                    // proposals' targets [P m]; the unused one then holds the winners'
+    uint32_t *etime, *etime_alt;                  // their times; likewise
     unsigned long long *jv;                       // per winner: label << 32 | link (link ~0: resolved) [P m]
     int32_t *go;                                  // [kSqMaxRounds + 1]: round r runs if go[r]
-    uint32_t *tot;                                // [4]: proposals, winners
-    unsigned long long *tot64;                    // proposals, as the sort's device count
-    void *sort_scratch, *scan_scratch;
+    uint32_t *tot;                                // [2]: winners
+    unsigned long long *ne;                       // proposals
+    void *osort, *esort, *scan_scratch;
 };
 
-static bool sq_wide(int32_t n, int64_t m, const bgv_cd_params *p) {
-    const int64_t nchunk = (m + p->chunk - 1) / p->chunk;
-    return bits_for((uint64_t)(n - 1)) + bits_for((uint64_t)p->passes * (uint64_t)nchunk - 1) > 32;
-}
+static int64_t sq_tiles(int64_t count) { return (count + kSqTile - 1) / kSqTile; }
 
 size_t sq_layout(Carver &c, int32_t n, int64_t m, const bgv_cd_params *p, void *out) {
     SqWs w{};
     const size_t no = 2 * (size_t)m, pm = (size_t)p->passes * (size_t)m;
-    const size_t kw = sq_wide(n, m, p) ? sizeof(uint64_t) : sizeof(uint32_t);
+    const int nbits = bits_for((uint64_t)n);
+    const int64_t tally = std::max<int64_t>((int64_t)p->passes * sq_tiles(m), sq_tiles((int64_t)pm)) + 1;
     w.okey = c.take<uint32_t>(no);
     w.okey_alt = c.take<uint32_t>(no);
     w.oval = c.take<uint32_t>(no);
     w.oval_alt = c.take<uint32_t>(no);
-    w.beg = c.take<uint32_t>((size_t)n);
-    w.end = c.take<uint32_t>((size_t)n);
-    w.cd = c.take<int4>((size_t)m);
-    w.flag = c.take<uint32_t>(pm);
-    w.evk = c.take<char>(pm * kw);
-    w.evk_alt = c.take<char>(pm * kw);
-    w.evv = c.take<uint32_t>(pm);
-    w.evv_alt = c.take<uint32_t>(pm);
-    w.wk = c.take<char>(pm * kw);
-    w.wv = c.take<uint32_t>(pm);
+    w.run = c.take<uint2>((size_t)n);
+    w.wrun = c.take<uint2>((size_t)n);
+    w.cc = c.take<int32_t>(no);
+    w.tally = c.take<uint32_t>((size_t)tally);
+    w.ekey = c.take<uint32_t>(pm);
+    w.ekey_alt = c.take<uint32_t>(pm);
+    w.etime = c.take<uint32_t>(pm);
+    w.etime_alt = c.take<uint32_t>(pm);
     w.jv = c.take<unsigned long long>(pm);
     w.go = c.take<int32_t>(kSqMaxRounds + 1);
-    w.tot = c.take<uint32_t>(4);
-    w.tot64 = c.take<unsigned long long>(2);
-    w.sort_scratch = c.take<char>(std::max(sort_workspace((int64_t)no, 32), sort_workspace((int64_t)pm, 64)));
-    w.scan_scratch = c.take<char>(scan_workspace((int64_t)pm));
+    w.tot = c.take<uint32_t>(2);
+    w.ne = c.take<unsigned long long>(1);
+    w.osort = c.take<char>(sort_workspace((int64_t)no, nbits));
+    w.esort = c.take<char>(sort_workspace((int64_t)pm, nbits));
+    w.scan_scratch = c.take<char>(scan_workspace(tally));
     if (out) *static_cast<SqWs *>(out) = w;
     return c.size();
 }
@@ -113,26 +124,29 @@ size_t sq_layout(Carver &c, int32_t n, int64_t m, const bgv_cd_params *p, void *
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < (count); i += (int64_t)gridDim.x * blockDim.x)
 
 // Occurrence 2i + s is endpoint s of edge i, keyed by its node (self-loops by n, past
-// every node: they raise no counter).
+// every node: they raise no counter).  Also clears the runs and the rounds' flags (round
+// 0 runs).
 __global__ void __launch_bounds__(kSqThreads) k_sq_occ(const int2 *__restrict__ edges, int64_t m, int32_t n,
-                                                       uint32_t *__restrict__ okey, uint32_t *__restrict__ oval) {
+                                                       uint2 *__restrict__ okey, uint2 *__restrict__ oval,
+                                                       uint2 *__restrict__ run, uint2 *__restrict__ wrun,
+                                                       int32_t *__restrict__ go, int32_t rounds) {
     SQ_LOOP(i, m) {
         const int2 e = edges[i];
         const bool loop = e.x == e.y;
-        okey[2 * i] = loop ? (uint32_t)n : (uint32_t)e.x;
-        okey[2 * i + 1] = loop ? (uint32_t)n : (uint32_t)e.y;
-        oval[2 * i] = (uint32_t)(2 * i);
-        oval[2 * i + 1] = (uint32_t)(2 * i + 1);
+        okey[i] = make_uint2(loop ? (uint32_t)n : (uint32_t)e.x, loop ? (uint32_t)n : (uint32_t)e.y);
+        oval[i] = make_uint2((uint32_t)(2 * i), (uint32_t)(2 * i + 1));
     }
+    SQ_LOOP(v, n) run[v] = wrun[v] = make_uint2(0u, 0u);
+    SQ_LOOP(r, rounds + 1) go[r] = r == 0;
 }
 
 __global__ void __launch_bounds__(kSqThreads) k_sq_runs(const uint32_t *__restrict__ sk, int64_t no, int32_t n,
-                                                        uint32_t *__restrict__ beg, uint32_t *__restrict__ end) {
+                                                        uint2 *__restrict__ run) {
     SQ_LOOP(j, no) {
         const uint32_t x = sk[j];
         if (x >= (uint32_t)n) continue;
-        if (j == 0 || sk[j - 1] != x) beg[x] = (uint32_t)j;
-        if (j + 1 == no || sk[j + 1] != x) end[x] = (uint32_t)(j + 1);
+        if (j == 0 || sk[j - 1] != x) run[x].x = (uint32_t)j;
+        if (j + 1 == no || sk[j + 1] != x) run[x].y = (uint32_t)(j + 1);
     }
 }
 
@@ -140,24 +154,21 @@ __global__ void __launch_bounds__(kSqThreads) k_sq_runs(const uint32_t *__restri
 // the first place in x's run (occurrences in stream order) at or past that end.
 __global__ void __launch_bounds__(kSqThreads) k_sq_counts(const uint32_t *__restrict__ sk,
                                                           const uint32_t *__restrict__ sv, int64_t no, int32_t n,
-                                                          const uint32_t *__restrict__ beg,
-                                                          const uint32_t *__restrict__ end, int64_t m, int64_t B,
-                                                          int4 *__restrict__ cd) {
+                                                          const uint2 *__restrict__ run, uint32_t m, uint32_t B,
+                                                          int32_t *__restrict__ cc) {
     SQ_LOOP(j, no) {
         const uint32_t x = sk[j];
         if (x >= (uint32_t)n) continue;
         const uint32_t o = sv[j];
-        const int64_t i = o >> 1;
-        const int64_t ce = std::min<int64_t>((i / B + 1) * B, m);
-        const uint64_t lim = 2 * (uint64_t)ce;
+        const uint64_t lim = 2 * (uint64_t)min((uint64_t)(o >> 1) / B * B + B, (uint64_t)m);
         // gallop from j (the chunk's run of x is usually short), then bisect
-        const uint32_t e = end[x];
-        uint32_t lo = (uint32_t)j + 1, hi = e;
+        const uint2 r = run[x];
+        uint32_t lo = (uint32_t)j + 1, hi = r.y;
         uint64_t step = 1;
         while (true) {
             const uint64_t probe = (uint64_t)j + step;
-            if (probe >= e || (uint64_t)sv[probe] >= lim) {
-                hi = probe < e ? (uint32_t)probe : e;
+            if (probe >= r.y || (uint64_t)sv[probe] >= lim) {
+                hi = probe < r.y ? (uint32_t)probe : r.y;
                 break;
             }
             lo = (uint32_t)probe + 1;
@@ -168,258 +179,218 @@ __global__ void __launch_bounds__(kSqThreads) k_sq_counts(const uint32_t *__rest
             if ((uint64_t)sv[mid] < lim) lo = mid + 1;
             else hi = mid;
         }
-        // one 8-byte store per occurrence: {c, d} of this endpoint
-        reinterpret_cast<int2 *>(cd + i)[o & 1u] = make_int2((int32_t)(lo - beg[x]), (int32_t)(e - beg[x]));
+        cc[o] = (int32_t)(lo - r.x);
     }
 }
 
-// Target of edge e in pass p (threshold D), or -1: both counters at most D and unequal,
-// the endpoint with the smaller one is the target; equal ones with tie rule 1: e.x.
-__device__ __forceinline__ int32_t sq_target(int2 e, int4 c, int32_t p, int32_t D, int32_t tie) {
+__global__ void __launch_bounds__(kSqThreads) k_sq_init(int32_t n, int32_t rows, int32_t *__restrict__ pass_labels,
+                                                        const uint2 *__restrict__ run, int32_t *__restrict__ degree) {
+    SQ_LOOP(v, n) {
+        degree[v] = (int32_t)(run[v].y - run[v].x);
+        for (int32_t p = 0; p < rows; ++p) pass_labels[(int64_t)p * n + v] = (int32_t)v;
+    }
+}
+
+// Target of an edge with endpoint counts c and degrees d in pass p (threshold D), or -1:
+// both counters at most D and unequal, the endpoint with the smaller one is the target;
+// equal ones with tie rule 1: e.x.
+__device__ __forceinline__ int32_t sq_target(int2 e, int2 c, int2 d, int32_t p, int32_t D, int32_t tie) {
     if (e.x == e.y) return -1;
-    const int32_t cu = p * c.y + c.x, cv = p * c.w + c.z;
+    const int32_t cu = p * d.x + c.x, cv = p * d.y + c.y;
     if (cu <= D && cv <= D && (cu != cv || tie)) return cu <= cv ? e.x : e.y;
     return -1;
 }
 
-// flag[p m + i] = edge i proposes in pass p (passes before `first` propose nothing)
-__global__ void __launch_bounds__(kSqThreads) k_sq_flags(const int2 *__restrict__ edges, const int4 *__restrict__ cd,
-                                                         int64_t m, int32_t P, int32_t D1, int32_t growth,
-                                                         int32_t tie, int32_t first, uint32_t *__restrict__ flag) {
-    SQ_LOOP(t, (int64_t)P * m) {
-        const int32_t p = (int32_t)(t / m);
-        const int64_t i = t - (int64_t)p * m;
-        flag[t] = p >= first && sq_target(edges[i], cd[i], p, sq_threshold(D1, growth, p), tie) >= 0 ? 1u : 0u;
+// A wavefront takes kSqTile consecutive edges through passes first .. P - 1.  Counting:
+// its proposals per pass into tally[pass * tiles + tile].  Writing (tally now holds
+// exclusive sums): proposal (p, i) at its place in (pass, stream) order: its target and
+// its time p m + i.
+template <bool kWrite>
+__global__ void __launch_bounds__(kSqThreads) k_sq_proposals(const int2 *__restrict__ edges,
+                                                             const int2 *__restrict__ cc,
+                                                             const int32_t *__restrict__ degree, int64_t m, int32_t P,
+                                                             int32_t D1, int32_t growth, int32_t tie, int32_t first,
+                                                             int64_t tiles, uint32_t *__restrict__ tally,
+                                                             uint32_t *__restrict__ ekey,
+                                                             uint32_t *__restrict__ etime) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t tile = (blockIdx.x * (int64_t)kSqThreads + threadIdx.x) / kWave;
+    if (tile >= tiles) return;
+    const int64_t i0 = tile * kSqTile + lane;
+    int2 e[kSqRounds], c[kSqRounds], d[kSqRounds];
+#pragma unroll
+    for (int u = 0; u < kSqRounds; ++u) {
+        const int64_t i = i0 + u * kWave;
+        e[u] = i < m ? edges[i] : make_int2(0, 0);
+        c[u] = i < m ? cc[i] : make_int2(0, 0);  // a loop's is not set and not used
     }
-}
-
-// Proposal (p, i) at its place pos[p m + i]: key (target, global chunk), value i.
-template <class KT>
-__global__ void __launch_bounds__(kSqThreads) k_sq_emit(const int2 *__restrict__ edges, const int4 *__restrict__ cd,
-                                                        int64_t m, int32_t P, int32_t D1, int32_t growth,
-                                                        int32_t tie, int32_t first, int64_t B,
-                                                        int64_t nchunk, int gbits, const uint32_t *__restrict__ pos,
-                                                        KT *__restrict__ key, uint32_t *__restrict__ val) {
-    SQ_LOOP(t, (int64_t)P * m) {
-        const int32_t p = (int32_t)(t / m);
-        const int64_t i = t - (int64_t)p * m;
-        if (p < first) continue;
-        const int32_t v = sq_target(edges[i], cd[i], p, sq_threshold(D1, growth, p), tie);
-        if (v < 0) continue;
-        const uint64_t g = (uint64_t)p * (uint64_t)nchunk + (uint64_t)(i / B);
-        const uint32_t q = pos[t];
-        key[q] = (KT)(((uint64_t)v << gbits) | g);
-        val[q] = (uint32_t)i;
-    }
-}
-
-__global__ void __launch_bounds__(kSqThreads) k_sq_widen(const uint32_t *__restrict__ a, unsigned long long *b) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) *b = *a;
-}
-
-// flag[q] = sorted proposal q is the first of its (target, chunk) run
-template <class KT>
-__global__ void __launch_bounds__(kSqThreads) k_sq_first(const KT *__restrict__ sk, int64_t bound,
-                                                         const uint32_t *__restrict__ count,
-                                                         uint32_t *__restrict__ flag) {
-    const int64_t E = *count;
-    SQ_LOOP(q, bound) flag[q] = (q < E && (q == 0 || sk[q - 1] != sk[q])) ? 1u : 0u;
-}
-
-template <class KT>
-__global__ void __launch_bounds__(kSqThreads) k_sq_compact(const KT *__restrict__ sk, const uint32_t *__restrict__ sv,
-                                                           const uint32_t *__restrict__ count,
-                                                           const uint32_t *__restrict__ pos, KT *__restrict__ wk,
-                                                           uint32_t *__restrict__ wv) {
-    const int64_t E = *count;
-    SQ_LOOP(q, E) {
-        if (q == 0 || sk[q - 1] != sk[q]) {
-            wk[pos[q]] = sk[q];
-            wv[pos[q]] = sv[q];
+#pragma unroll
+    for (int u = 0; u < kSqRounds; ++u) d[u] = make_int2(degree[e[u].x], degree[e[u].y]);
+    const uint64_t lt = lane ? ~0ull >> (64 - lane) : 0ull;
+    for (int32_t p = 0; p < P; ++p) {
+        const int32_t D = sq_threshold(D1, growth, p);
+        uint32_t at = kWrite ? tally[p * tiles + tile] : 0u;
+#pragma unroll
+        for (int u = 0; u < kSqRounds; ++u) {
+            const int32_t v = p < first ? -1 : sq_target(e[u], c[u], d[u], p, D, tie);
+            const uint64_t mask = __ballot(v >= 0);
+            if (kWrite && v >= 0) {
+                const uint32_t q = at + (uint32_t)__popcll(mask & lt);
+                ekey[q] = (uint32_t)v;
+                etime[q] = (uint32_t)(p * m + i0 + u * kWave);
+            }
+            at += (uint32_t)__popcll(mask);
         }
+        if (!kWrite && lane == 0) tally[p * tiles + tile] = at;
     }
 }
 
-// The run of each node in the sorted winners (beg/end cleared before).
-template <class KT>
-__global__ void __launch_bounds__(kSqThreads) k_sq_wruns(const KT *__restrict__ wk,
-                                                         const uint32_t *__restrict__ wcount, int gbits,
-                                                         uint32_t *__restrict__ beg, uint32_t *__restrict__ end) {
-    const int64_t W = *wcount;
-    SQ_LOOP(r, W) {
-        const uint32_t v = (uint32_t)((uint64_t)wk[r] >> gbits);
-        if (r == 0 || (uint32_t)((uint64_t)wk[r - 1] >> gbits) != v) beg[v] = (uint32_t)r;
-        if (r + 1 == W || (uint32_t)((uint64_t)wk[r + 1] >> gbits) != v) end[v] = (uint32_t)(r + 1);
+// The first time of time t's chunk (t = p m + i; chunks of B <= m edges within a pass).
+__device__ __forceinline__ uint32_t sq_chunk_start(uint32_t t, uint32_t m, uint32_t B) {
+    const uint32_t p = t / m, i = t - p * m;
+    return p * m + i / B * B;
+}
+
+__global__ void k_sq_widen(const uint32_t *__restrict__ a, unsigned long long *b) { *b = *a; }
+
+// A wavefront takes kSqTile consecutive sorted proposals.  A proposal wins if the one
+// before it has another target or lies before its chunk.  Counting: its winners into
+// tally[tile].  Writing (tally now holds exclusive sums): their targets and times, and the
+// run of each node among them.
+template <bool kWrite>
+__global__ void __launch_bounds__(kSqThreads) k_sq_winners(const uint32_t *__restrict__ sk,
+                                                           const uint32_t *__restrict__ st,
+                                                           const unsigned long long *__restrict__ count, uint32_t m,
+                                                           uint32_t B, int64_t tiles, uint32_t *__restrict__ tally,
+                                                           uint32_t *__restrict__ wk, uint32_t *__restrict__ wt,
+                                                           uint2 *__restrict__ wrun) {
+    const int64_t E = (int64_t)*count;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t tile = (blockIdx.x * (int64_t)kSqThreads + threadIdx.x) / kWave;
+    if (tile >= tiles) return;
+    const int64_t q0 = tile * kSqTile + lane;
+    const uint64_t lt = lane ? ~0ull >> (64 - lane) : 0ull;
+    uint32_t at = kWrite ? tally[tile] : 0u;
+#pragma unroll
+    for (int u = 0; u < kSqRounds; ++u) {
+        const int64_t q = q0 + u * kWave;
+        bool win = false, start = false;
+        uint32_t k = 0, t = 0;
+        if (q < E) {
+            k = sk[q];
+            t = st[q];
+            start = q == 0 || sk[q - 1] != k;
+            win = start || st[q - 1] < sq_chunk_start(t, m, B);
+        }
+        const uint64_t mask = __ballot(win);
+        if (kWrite && q < E) {
+            const uint32_t r = at + (uint32_t)__popcll(mask & lt);
+            if (win) {
+                wk[r] = k;
+                wt[r] = t;
+            }
+            if (start) wrun[k].x = r;
+            if (q + 1 == E || sk[q + 1] != k) wrun[k].y = r + (win ? 1u : 0u);
+        }
+        at += (uint32_t)__popcll(mask);
     }
+    if (!kWrite && lane == 0) tally[tile] = at;
 }
 
 // Winner r's link: the last winner into its source with an earlier chunk, or none
 // (~0); packed with the label it carries when it has no link: the source's starting
 // label (its id, or lab0 of a resumed run).
-template <class KT>
-__global__ void __launch_bounds__(kSqThreads) k_sq_links(const int2 *__restrict__ edges, const KT *__restrict__ wk,
-                                                         const uint32_t *__restrict__ wv,
-                                                         const uint32_t *__restrict__ wcount, int gbits,
-                                                         const uint32_t *__restrict__ beg,
-                                                         const uint32_t *__restrict__ end,
+__global__ void __launch_bounds__(kSqThreads) k_sq_links(const int2 *__restrict__ edges,
+                                                         const uint32_t *__restrict__ wk,
+                                                         const uint32_t *__restrict__ wt,
+                                                         const uint32_t *__restrict__ wcount, uint32_t m, uint32_t B,
+                                                         const uint2 *__restrict__ wrun,
                                                          const int32_t *__restrict__ lab0,
                                                          unsigned long long *__restrict__ jv) {
     const int64_t W = *wcount;
     SQ_LOOP(r, W) {
-        const uint64_t key = (uint64_t)wk[r];
-        const uint64_t gmask = gbits >= 64 ? ~0ull : ((1ull << gbits) - 1ull);
-        const int32_t v = (int32_t)(key >> gbits);
-        const int2 e = edges[wv[r]];
-        const int32_t u = e.x == v ? e.y : e.x;
-        const uint64_t want = ((uint64_t)u << gbits) | (key & gmask);
-        const uint32_t b0 = beg[u];
-        uint32_t lo = b0, hi = end[u];  // u's winners (empty: beg = end = 0); first key >= want
+        const uint32_t t = wt[r];
+        const int2 e = edges[t % m];
+        const int32_t u = e.x == (int32_t)wk[r] ? e.y : e.x;
+        const uint32_t want = sq_chunk_start(t, m, B);
+        const uint2 b = wrun[u];  // u's winners (none: an empty run); the first time >= want
+        uint32_t lo = b.x, hi = b.y;
         while (lo < hi) {
             const uint32_t mid = lo + (hi - lo) / 2;
-            if ((uint64_t)wk[mid] < want) lo = mid + 1;
+            if (wt[mid] < want) lo = mid + 1;
             else hi = mid;
         }
-        const uint32_t link = lo > b0 ? lo - 1 : 0xffffffffu;
+        const uint32_t link = lo > b.x ? lo - 1 : 0xffffffffu;
         const int32_t l0 = lab0 ? lab0[u] : u;
         jv[r] = ((unsigned long long)(uint32_t)l0 << 32) | link;
     }
 }
 
-// One pointer-jumping round, in place: a winner whose link is resolved takes its
-// label; any other skips to its link's link.  Each 8-byte word is read and written by
-// one instruction, so a concurrent reader sees a link and label that belong together
-// (older or newer, both true of the chain: its label is that of its link's), and the
-// final label is copied only from a resolved word; every word read is at least as new
-// as the round's start, so each round at least halves every remaining chain.  The
-// round does nothing if the previous one left nothing unresolved (*go_in == 0), and
-// sets *go_out when it did not resolve everything.
+// One pointer-jumping round, in place: a winner follows up to kSqHops links; where it
+// meets a resolved one it takes its label, else it keeps the last link it read.  Each
+// 8-byte word is read and written by one instruction, so a concurrent reader sees a link
+// and label that belong together (older or newer, both true of the chain: its label is
+// that of its link's), and the final label is copied only from a resolved word; every
+// word read is at least as new as the round's start, so each round shortens every
+// remaining chain to at most a (kSqHops + 1)-th.  The round does nothing if the previous
+// one left nothing unresolved (*go_in == 0), and sets *go_out when it did not resolve
+// everything.
 __global__ void __launch_bounds__(kSqThreads) k_sq_jump(unsigned long long *jv, const uint32_t *__restrict__ wcount,
                                                         const int32_t *go_in, int32_t *go_out) {
     if (*go_in == 0) return;  // the same value for every thread of the grid
     const int64_t W = *wcount;
     bool more = false;
     SQ_LOOP(r, W) {
-        const unsigned long long w0 = __hip_atomic_load(&jv[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        const uint32_t a = (uint32_t)w0;
-        if (a == 0xffffffffu) continue;
-        const unsigned long long wa = __hip_atomic_load(&jv[a], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        const uint32_t b = (uint32_t)wa;
-        const unsigned long long nw = b == 0xffffffffu ? wa : ((w0 & 0xffffffff00000000ull) | b);
-        more |= b != 0xffffffffu;
-        __hip_atomic_store(&jv[r], nw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        unsigned long long w = __hip_atomic_load(&jv[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if ((uint32_t)w == 0xffffffffu) continue;
+        const unsigned long long own = w & 0xffffffff00000000ull;
+        for (int h = 0; h < kSqHops && (uint32_t)w != 0xffffffffu; ++h)
+            w = __hip_atomic_load(&jv[(uint32_t)w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        const bool done = (uint32_t)w == 0xffffffffu;
+        more |= !done;
+        __hip_atomic_store(&jv[r], done ? w : (own | (uint32_t)w), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     if (__syncthreads_or(more) && threadIdx.x == 0) *go_out = 1;
 }
 
-__global__ void __launch_bounds__(kSqThreads) k_sq_init(int32_t n, int32_t rows, int32_t *__restrict__ labels,
-                                                        int32_t *__restrict__ pass_labels,
-                                                        const uint32_t *__restrict__ beg,
-                                                        const uint32_t *__restrict__ end,
-                                                        const int32_t *__restrict__ lab0,
-                                                        int32_t *__restrict__ degree) {
-    SQ_LOOP(v, n) {
-        labels[v] = lab0 ? lab0[v] : (int32_t)v;
-        degree[v] = (int32_t)(end[v] - beg[v]);
-        for (int32_t p = 0; p < rows; ++p) pass_labels[(int64_t)p * n + v] = (int32_t)v;
-    }
-}
-
-// A node's label after pass p: the label of its last winner in a chunk of passes 0..p.
-template <class KT>
-__global__ void __launch_bounds__(kSqThreads) k_sq_labels(const KT *__restrict__ wk,
-                                                          const uint32_t *__restrict__ wcount, int gbits,
-                                                          int64_t nchunk, int32_t P,
-                                                          const unsigned long long *__restrict__ jv,
-                                                          int32_t n, int32_t *__restrict__ labels,
-                                                          int32_t *__restrict__ pass_labels) {
+// A node's label after pass p: the label of its last winner in passes 0..p.
+__global__ void __launch_bounds__(kSqThreads) k_sq_pass_labels(const uint32_t *__restrict__ wk,
+                                                               const uint32_t *__restrict__ wt,
+                                                               const uint32_t *__restrict__ wcount, uint32_t m,
+                                                               int32_t P, const unsigned long long *__restrict__ jv,
+                                                               int32_t n, int32_t *__restrict__ pass_labels) {
     const int64_t W = *wcount;
     SQ_LOOP(r, W) {
-        const uint64_t key = (uint64_t)wk[r];
-        const uint64_t gmask = gbits >= 64 ? ~0ull : ((1ull << gbits) - 1ull);
-        const int32_t v = (int32_t)(key >> gbits);
-        const bool more = r + 1 < W && (int32_t)((uint64_t)wk[r + 1] >> gbits) == v;
+        const uint32_t v = wk[r];
         const int32_t lab = (int32_t)(jv[r] >> 32);
-        if (!more) labels[v] = lab;
-        if (pass_labels) {
-            const int32_t p0 = (int32_t)((key & gmask) / (uint64_t)nchunk);
-            const int32_t p1 = more ? (int32_t)(((uint64_t)wk[r + 1] & gmask) / (uint64_t)nchunk) : P;
-            for (int32_t p = p0; p < p1; ++p) pass_labels[(int64_t)p * n + v] = lab;
-        }
+        const int32_t p0 = (int32_t)(wt[r] / m);
+        const int32_t p1 = r + 1 < W && wk[r + 1] == v ? (int32_t)(wt[r + 1] / m) : P;
+        for (int32_t p = p0; p < p1; ++p) pass_labels[(int64_t)p * n + v] = lab;
     }
 }
 
-__global__ void __launch_bounds__(1024) k_sq_volume(const int32_t *__restrict__ labels,
-                                                    const int32_t *__restrict__ degree, int32_t n,
+// Final labels: of each node's last winner, or its starting one; and the volumes.
+__global__ void __launch_bounds__(1024) k_sq_finish(const uint2 *__restrict__ wrun,
+                                                    const unsigned long long *__restrict__ jv,
+                                                    const int32_t *__restrict__ degree,
+                                                    const int32_t *__restrict__ lab0, int32_t n,
+                                                    int32_t *__restrict__ labels,
                                                     unsigned long long *__restrict__ volume) {
     __shared__ VolumeTable tab;
-    vs_clear(tab);
+    if (volume) vs_clear(tab);
     __syncthreads();
     SQ_LOOP(v, n) {
-        const int32_t d = degree[v];
-        if (d) vs_add(tab, volume, labels[v], (unsigned long long)d);
+        const uint2 b = wrun[v];
+        const int32_t l = b.y > b.x ? (int32_t)(jv[b.y - 1] >> 32) : lab0 ? lab0[v] : (int32_t)v;
+        labels[v] = l;
+        const int32_t d = volume ? degree[v] : 0;
+        if (d) vs_add(tab, volume, l, (unsigned long long)d);
     }
     __syncthreads();
-    vs_flush(tab, volume);
+    if (volume) vs_flush(tab, volume);
 }
 
 // ------------------------------------------------------------------- driver ----
-template <class KT>
-static bgv_status sq_sort_events(SqWs &w, int64_t pm, int nbits, KT **sk, uint32_t **sv, hipStream_t s);
-
-template <>
-bgv_status sq_sort_events<uint32_t>(SqWs &w, int64_t pm, int nbits, uint32_t **sk, uint32_t **sv, hipStream_t s) {
-    return sort_pairs<uint32_t>(static_cast<uint32_t *>(w.evk), static_cast<uint32_t *>(w.evk_alt), w.evv, w.evv_alt, pm,
-                          nbits, sk, sv, w.sort_scratch, s, w.tot64);
-}
-
-template <>
-bgv_status sq_sort_events<uint64_t>(SqWs &w, int64_t pm, int nbits, uint64_t **sk, uint32_t **sv, hipStream_t s) {
-    return sort_pairs<uint64_t>(static_cast<uint64_t *>(w.evk), static_cast<uint64_t *>(w.evk_alt), w.evv, w.evv_alt, pm,
-                          nbits, sk, sv, w.sort_scratch, s, w.tot64);
-}
-
-template <class KT>
-static bgv_status sq_events(const int2 *e2, int32_t n, int64_t m, const bgv_cd_params *p, SqWs &w, int32_t *labels,
-                            int32_t *pass_labels, int32_t first, const int32_t *lab0, hipStream_t s) {
-    const int32_t P = p->passes;
-    const int64_t B = p->chunk, nchunk = (m + B - 1) / B, pm = (int64_t)P * m;
-    const int gbits = bits_for((uint64_t)P * (uint64_t)nchunk - 1);
-    const int nbits = std::max(1, bits_for((uint64_t)(n - 1)) + gbits);
-    const unsigned grid = grid_for(pm, kSqThreads, 65536);
-    // proposals of every pass, in (pass, stream) order
-    BGV_LAUNCH(k_sq_flags, dim3(grid), dim3(kSqThreads), 0, s, e2, w.cd, m, P, p->threshold, p->growth, p->tie,
-               first, w.flag);
-    BGV_TRY(exclusive_scan_u32(w.flag, w.flag, pm, w.tot, w.scan_scratch, s));
-    BGV_LAUNCH(k_sq_emit<KT>, dim3(grid), dim3(kSqThreads), 0, s, e2, w.cd, m, P, p->threshold, p->growth, p->tie,
-               first, B, nchunk,
-               gbits, w.flag, static_cast<KT *>(w.evk), w.evv);
-    BGV_LAUNCH(k_sq_widen, dim3(1), dim3(kSqThreads), 0, s, w.tot, w.tot64);
-    KT *sk = nullptr;
-    uint32_t *sv = nullptr;
-    BGV_TRY(sq_sort_events<KT>(w, pm, nbits, &sk, &sv, s));
-    // winners: first of each (target, chunk) run
-    BGV_LAUNCH(k_sq_first<KT>, dim3(grid), dim3(kSqThreads), 0, s, sk, pm, w.tot, w.flag);
-    BGV_TRY(exclusive_scan_u32(w.flag, w.flag, pm, w.tot + 1, w.scan_scratch, s));
-    KT *wk = static_cast<KT *>(w.wk);
-    BGV_LAUNCH(k_sq_compact<KT>, dim3(grid), dim3(kSqThreads), 0, s, sk, sv, w.tot, w.flag, wk, w.wv);
-    // each winner's link: a search in its source's run of winners (the occurrence runs'
-    // arrays, free by now, hold the winner runs)
-    BGV_TRY(fill<uint32_t>(w.beg, 0u, n, s));
-    BGV_TRY(fill<uint32_t>(w.end, 0u, n, s));
-    BGV_LAUNCH(k_sq_wruns<KT>, dim3(grid), dim3(kSqThreads), 0, s, wk, w.tot + 1, gbits, w.beg, w.end);
-    BGV_LAUNCH(k_sq_links<KT>, dim3(grid), dim3(kSqThreads), 0, s, e2, wk, w.wv, w.tot + 1, gbits, w.beg, w.end,
-               lab0, w.jv);
-    // a chain of links visits at most one winner per chunk: ceil(log2 chunks) + 1 rounds
-    const int rounds = bits_for((uint64_t)P * (uint64_t)nchunk) + 1;
-    BGV_TRY(fill<int32_t>(w.go, 0, rounds + 1, s));
-    BGV_TRY(fill<int32_t>(w.go, 1, 1, s));
-    for (int r = 0; r < rounds; ++r)
-        BGV_LAUNCH(k_sq_jump, dim3(grid), dim3(kSqThreads), 0, s, w.jv, w.tot + 1, w.go + r, w.go + r + 1);
-    BGV_LAUNCH(k_sq_labels<KT>, dim3(grid), dim3(kSqThreads), 0, s, wk, w.tot + 1, gbits, nchunk, P, w.jv, n, labels,
-               pass_labels);
-    return BGV_OK;
-}
-
 bgv_status sq_run(int32_t n, int64_t m, const int32_t *edges, const bgv_cd_params *p, int32_t *labels,
                   int32_t *degree, int64_t *volume, int32_t *pass_labels, int32_t first, const int32_t *lab0,
                   void *ws, hipStream_t s) {
@@ -427,25 +398,51 @@ bgv_status sq_run(int32_t n, int64_t m, const int32_t *edges, const bgv_cd_param
     SqWs w;
     sq_layout(c, n, m, p, &w);
     const int2 *e2 = reinterpret_cast<const int2 *>(edges);
-    const int64_t no = 2 * m;
+    const int32_t P = p->passes;
+    const int64_t no = 2 * m, pm = (int64_t)P * m, nchunk = (m + p->chunk - 1) / p->chunk;
+    const uint32_t um = (uint32_t)m, B = (uint32_t)std::min<int64_t>(p->chunk, m);
     const unsigned go = grid_for(no, kSqThreads, 65536), gn = grid_for(n, kSqThreads, 65536);
-    BGV_LAUNCH(k_sq_occ, dim3(grid_for(m, kSqThreads, 65536)), dim3(kSqThreads), 0, s, e2, m, n, w.okey, w.oval);
+    const unsigned gw = grid_for(pm, kSqThreads, 65536);
+    // a chain of links visits at most one winner per chunk, and a round leaves at most a
+    // (kSqHops + 1)-th of it
+    int rounds = 2;
+    for (uint64_t left = (uint64_t)P * (uint64_t)nchunk; left > 1; left = (left + kSqHops) / (kSqHops + 1)) ++rounds;
+    BGV_LAUNCH(k_sq_occ, dim3(std::max(grid_for(m, kSqThreads, 65536), gn)), dim3(kSqThreads), 0, s, e2, m, n,
+               reinterpret_cast<uint2 *>(w.okey), reinterpret_cast<uint2 *>(w.oval), w.run, w.wrun, w.go, rounds);
+    const int nbits = bits_for((uint64_t)n);
     uint32_t *sk = nullptr, *sv = nullptr;
-    BGV_TRY(sort_pairs<uint32_t>(w.okey, w.okey_alt, w.oval, w.oval_alt, no, bits_for((uint64_t)n), &sk, &sv,
-                           w.sort_scratch, s));
-    BGV_TRY(fill<uint32_t>(w.beg, 0u, n, s));
-    BGV_TRY(fill<uint32_t>(w.end, 0u, n, s));
-    BGV_LAUNCH(k_sq_runs, dim3(go), dim3(kSqThreads), 0, s, sk, no, n, w.beg, w.end);
-    BGV_LAUNCH(k_sq_counts, dim3(go), dim3(kSqThreads), 0, s, sk, sv, no, n, w.beg, w.end, m, p->chunk, w.cd);
-    BGV_LAUNCH(k_sq_init, dim3(gn), dim3(kSqThreads), 0, s, n, pass_labels ? p->passes : 0, labels, pass_labels,
-               w.beg, w.end, lab0, degree);
-    if (sq_wide(n, m, p))
-        BGV_TRY(sq_events<uint64_t>(e2, n, m, p, w, labels, pass_labels, first, lab0, s));
-    else
-        BGV_TRY(sq_events<uint32_t>(e2, n, m, p, w, labels, pass_labels, first, lab0, s));
-    if (volume)
-        BGV_LAUNCH(k_sq_volume, dim3(vs_grid(n)), dim3(1024), 0, s, labels, degree, n,
-                   reinterpret_cast<unsigned long long *>(volume));
+    BGV_TRY(sort_pairs<uint32_t>(w.okey, w.okey_alt, w.oval, w.oval_alt, no, nbits, &sk, &sv, w.osort, s));
+    BGV_LAUNCH(k_sq_runs, dim3(go), dim3(kSqThreads), 0, s, sk, no, n, w.run);
+    BGV_LAUNCH(k_sq_counts, dim3(go), dim3(kSqThreads), 0, s, sk, sv, no, n, w.run, um, B, w.cc);
+    BGV_LAUNCH(k_sq_init, dim3(gn), dim3(kSqThreads), 0, s, n, pass_labels ? P : 0, pass_labels, w.run, degree);
+
+    // proposals of every pass, in (pass, stream) order, then by target
+    const int64_t ptiles = sq_tiles(m);
+    const dim3 gp((unsigned)((ptiles * kWave + kSqThreads - 1) / kSqThreads));
+    const int2 *cc = reinterpret_cast<const int2 *>(w.cc);
+    BGV_LAUNCH(k_sq_proposals<false>, gp, dim3(kSqThreads), 0, s, e2, cc, degree, m, P, p->threshold, p->growth,
+               p->tie, first, ptiles, w.tally, (uint32_t *)nullptr, (uint32_t *)nullptr);
+    BGV_TRY(exclusive_scan_u32(w.tally, w.tally, P * ptiles, w.tot + 1, w.scan_scratch, s));
+    BGV_LAUNCH(k_sq_widen, dim3(1), dim3(1), 0, s, w.tot + 1, w.ne);
+    BGV_LAUNCH(k_sq_proposals<true>, gp, dim3(kSqThreads), 0, s, e2, cc, degree, m, P, p->threshold, p->growth,
+               p->tie, first, ptiles, w.tally, w.ekey, w.etime);
+    uint32_t *ek = nullptr, *et = nullptr;
+    BGV_TRY(sort_pairs<uint32_t>(w.ekey, w.ekey_alt, w.etime, w.etime_alt, pm, nbits, &ek, &et, w.esort, s, w.ne));
+
+    // winners, their links, the labels
+    uint32_t *wk = ek == w.ekey ? w.ekey_alt : w.ekey, *wt = et == w.etime ? w.etime_alt : w.etime;
+    const int64_t etiles = sq_tiles(pm);
+    const dim3 ge((unsigned)((etiles * kWave + kSqThreads - 1) / kSqThreads));
+    BGV_LAUNCH(k_sq_winners<false>, ge, dim3(kSqThreads), 0, s, ek, et, w.ne, um, B, etiles, w.tally, wk, wt, w.wrun);
+    BGV_TRY(exclusive_scan_u32(w.tally, w.tally, etiles, w.tot, w.scan_scratch, s));
+    BGV_LAUNCH(k_sq_winners<true>, ge, dim3(kSqThreads), 0, s, ek, et, w.ne, um, B, etiles, w.tally, wk, wt, w.wrun);
+    BGV_LAUNCH(k_sq_links, dim3(gw), dim3(kSqThreads), 0, s, e2, wk, wt, w.tot, um, B, w.wrun, lab0, w.jv);
+    for (int r = 0; r < rounds; ++r)
+        BGV_LAUNCH(k_sq_jump, dim3(gw), dim3(kSqThreads), 0, s, w.jv, w.tot, w.go + r, w.go + r + 1);
+    if (pass_labels)
+        BGV_LAUNCH(k_sq_pass_labels, dim3(gw), dim3(kSqThreads), 0, s, wk, wt, w.tot, um, P, w.jv, n, pass_labels);
+    BGV_LAUNCH(k_sq_finish, dim3(vs_grid(n)), dim3(1024), 0, s, w.wrun, w.jv, degree, lab0, n, labels,
+               reinterpret_cast<unsigned long long *>(volume));
     return BGV_OK;
 }
 

@@ -95,6 +95,29 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_down(const T *in, T *out,
     }
 }
 
+// A scan of few values by one workgroup: one launch instead of three.  Each round takes
+// blockDim consecutive values and carries their sum.
+constexpr int64_t kScanOneMax = 16384;
+template <class T>
+__global__ void __launch_bounds__(1024) k_scan_one(const T *in, T *out, int64_t n, T *total) {
+    T carry = T(0);
+    for (int64_t t0 = 0; t0 < n; t0 += 4 * 1024) {
+        const int64_t i = t0 + 4 * (int64_t)threadIdx.x;
+        T v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = i + j < n ? in[i + j] : T(0);
+        T tot;
+        T pre = carry + block_excl_scan<T>((v[0] + v[1]) + (v[2] + v[3]), &tot);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (i + j < n) out[i + j] = pre;
+            pre += v[j];
+        }
+        carry += tot;
+    }
+    if (threadIdx.x == 0 && total) *total = carry;
+}
+
 size_t scan_workspace(int64_t n) {
     int64_t nb = (n + kScanTile - 1) / kScanTile;
     return align_up(sizeof(double) * (size_t)(nb > 0 ? nb : 1));
@@ -106,6 +129,10 @@ bgv_status exclusive_scan(const T *in, T *out, int64_t n, T *total, void *scratc
         if (total) BGV_TRY(fill<T>(total, T(0), 1, s));
         return BGV_OK;
     }
+    if (n <= kScanOneMax) {
+        BGV_LAUNCH(k_scan_one<T>, dim3(1), dim3(1024), 0, s, in, out, n, total);
+        return BGV_OK;
+    }
     const int64_t nb = (n + kScanTile - 1) / kScanTile;
     T *part = static_cast<T *>(scratch);
     BGV_LAUNCH(k_scan_reduce<T>, dim3((unsigned)nb), dim3(kScanThreads), 0, s, in, n, part);
@@ -114,7 +141,6 @@ bgv_status exclusive_scan(const T *in, T *out, int64_t n, T *total, void *scratc
     return BGV_OK;
 }
 template bgv_status exclusive_scan<uint32_t>(const uint32_t *, uint32_t *, int64_t, uint32_t *, void *, hipStream_t);
-template bgv_status exclusive_scan<double>(const double *, double *, int64_t, double *, void *, hipStream_t);
 template bgv_status exclusive_scan<uint64_t>(const uint64_t *, uint64_t *, int64_t, uint64_t *, void *, hipStream_t);
 
 bgv_status exclusive_scan_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *total, void *scratch,

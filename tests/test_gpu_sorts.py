@@ -15,8 +15,9 @@ def bgv():
     return b
 
 
+# 512 edges fill a wavefront's tile
 @pytest.mark.parametrize("n,chunk", [(3000, 5000), (200_000, 40)])
-@pytest.mark.parametrize("m", [1, 511, 32_767, 32_768, 32_769, 524_288, 524_289])
+@pytest.mark.parametrize("m", [1, 511, 512, 513, 32_767, 32_768, 32_769, 524_288, 524_289])
 def test_occurrence_and_event_sorts(bgv, n, chunk, m):
     rng = np.random.default_rng(m)
     e = rng.integers(0, n, (m, 2)).astype(np.int32)
@@ -26,6 +27,11 @@ def test_occurrence_and_event_sorts(bgv, n, chunk, m):
     want = bgv.community(e, n, 9, 2, 2, max(1, min(chunk, m)), volume=True, method=1)
     for a, b in zip(got, want):
         assert torch.equal(a, b)
+
+
+def test_events_past_one_workgroups_scan(bgv):
+    """16,384 tiles of 512 proposals is the most that one workgroup scans."""
+    test_occurrence_and_event_sorts(bgv, 200_000, 300_000, 16_384 * 512 // 2 + 1)
 
 
 # rows of up to a few thousand FP32 terms: far inside the 1e-4 of the other force tests

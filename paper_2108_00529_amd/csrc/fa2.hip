@@ -23,11 +23,13 @@
 #include <cstddef>
 #include <cstring>
 #include <mutex>
+#include <type_traits>
 
 #include "block_scan.h"
 #include "common.h"
 #include "fa2_internal.h"
 #include "fa2_math.h"
+#include "fa2_resident.h"
 
 namespace bgv {
 
@@ -427,7 +429,7 @@ static bgv_status attc_setup(int32_t K, int64_t nent, CsrWs &w, hipStream_t s) {
 }
 
 bgv_status build_csr(int32_t K, int64_t E, const int32_t *edges, const float *attr_w, const float *mass_in,
-                     CsrWs &w, hipStream_t s, const float **mass_out) {
+                     CsrWs &w, hipStream_t s, const float **mass_out, bool items) {
     w.fmt = attr_w ? kCsrWeighted : (K <= 65536 ? kCsrIds16 : kCsrIds32);
     if (E == 0) {
         BGV_TRY(fill<uint32_t>(w.row, 0u, (int64_t)K + 1, s));
@@ -461,7 +463,7 @@ bgv_status build_csr(int32_t K, int64_t E, const int32_t *edges, const float *at
             BGV_TRY((attc_setup<uint32_t, uint16_t>(K, 2 * E, w, s)));
         else
             BGV_TRY((attc_setup<uint16_t, uint16_t>(K, 2 * E, w, s)));
-    } else {
+    } else if (items) {
         BGV_LAUNCH(k_att_item_counts, dim3(grid_for((int64_t)K + 1, kFaThreads, 65536)), dim3(kFaThreads), 0, s,
                    w.row, K, w.item_of);
         BGV_TRY(exclusive_scan_u32(w.item_of, w.item_of, (int64_t)K + 1, nullptr, w.scratch, s));
@@ -684,6 +686,38 @@ __global__ void __launch_bounds__(kFaThreads) k_force_combine(int32_t K, int32_t
                                                                const float2 *__restrict__ fprev,
                                                                float2 *__restrict__ F, double2 *__restrict__ part) {
     fa2_combine_tile((int32_t)blockIdx.x, K, nseg, seg, pos, mass, att, item_of, kr, kg, fprev, F, part);
+}
+
+// All iterations of a layout of at most kResidentMax nodes in one launch of one workgroup.
+constexpr int kResidentThreads = 1024;
+constexpr int kResidentIds = 32768;
+// The most nodes a layout of one graph takes there: past it one compute unit's vector issue
+// costs more than the launches (us per iteration with 16 superedges per node, three
+// launches / resident: 64 nodes 9.5 / 2.9, 256 15.1 / 8.7, 400 20.8 / 18.2, 512 23.2 /
+// 24.8).
+constexpr int32_t kResidentPlain = 448;
+constexpr int32_t kResidentIters = 4096;  // iterations per launch at most (tens of milliseconds)
+
+template <typename E>
+__global__ void __launch_bounds__(kResidentThreads) k_resident(int32_t K, int32_t iters, float2 *pos, float2 *fprev,
+                                                                const float *__restrict__ mass,
+                                                                const uint32_t *__restrict__ row,
+                                                                const E *__restrict__ cw, float *speed, float kr,
+                                                                float kg, float tau, float ks, float ksmax) {
+    extern __shared__ char lds[];
+    fa2_resident<kResidentThreads>(*reinterpret_cast<ResidentLds<kResidentIds> *>(lds), K, iters, pos, fprev, mass,
+                                   row, cw, speed, kr, kg, tau, ks, ksmax);
+}
+
+template <typename E>
+static bgv_status resident_iterations(int32_t K, float2 *pos, float2 *fprev, const float *mass, const CsrWs &csr,
+                                      float *speed, const bgv_fa2_params *p, hipStream_t s) {
+    const auto k_resident = bgv::k_resident<E>;  // one profiler name
+    for (int64_t it = 0; it < p->iters; it += kResidentIters)
+        BGV_LAUNCH(k_resident, dim3(1), dim3(kResidentThreads), sizeof(ResidentLds<kResidentIds>), s, K,
+                   (int32_t)std::min<int64_t>(kResidentIters, p->iters - it), pos, fprev, mass, csr.row,
+                   reinterpret_cast<const E *>(csr.cw), speed, p->kr, p->kg, p->tau, p->ks, p->ksmax);
+    return BGV_OK;
 }
 
 static bgv_status exact_forces(int32_t K, const float2 *pos, const float *mass, const float2 *A,
@@ -1689,7 +1723,8 @@ bgv_status bgv::fa2_layout_run(int32_t K, int64_t E, const int32_t *edges, const
     fa_layout(c, K, E, p, &w);
     if (range_check_on()) BGV_TRY(check_edge_ids(K, E, edges, w.flag, s));
     const float *m = nullptr;
-    BGV_TRY(build_csr(K, E, edges, attr_w, mass, w.csr, s, &m));
+    const bool resident = p->exact && K <= kResidentPlain;  // takes whole rows
+    BGV_TRY(build_csr(K, E, edges, attr_w, mass, w.csr, s, &m, !resident));
     if (!p->exact) {
         BGV_TRY(fill<uint32_t>(w.bh.icount, 0u, bh_force_blocks(K), s));
         BGV_TRY(fill<uint32_t>(w.bh.redo, 0u, 1, s));
@@ -1698,6 +1733,10 @@ bgv_status bgv::fa2_layout_run(int32_t K, int64_t E, const int32_t *edges, const
     float2 *x = reinterpret_cast<float2 *>(pos);
     float2 *fp = reinterpret_cast<float2 *>(fprev);
     const int32_t nb = (K + kFaThreads - 1) / kFaThreads;
+    if (resident) {
+        if (w.csr.fmt == kCsrWeighted) return resident_iterations<int2>(K, x, fp, m, w.csr, speed, p, s);
+        return resident_iterations<uint16_t>(K, x, fp, m, w.csr, speed, p, s);
+    }
     BGV_LAUNCH(k_copy_f32, dim3(1), dim3(1), 0, s, speed, w.speed);
     FaStreams st;
     st.s = s;

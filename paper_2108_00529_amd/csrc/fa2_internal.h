@@ -57,9 +57,10 @@ size_t csr_layout(Carver &c, int32_t K, int64_t E, CsrWs *w, bool allow_cols);
 // A[t] = attraction block sum of work item t (att_items_cap(K, E) entries), one
 // wavefront per item; node i's attraction is fa2_att_combine(A, csr.item_of, i).
 bgv_status attraction(int32_t K, const float2 *pos, const CsrWs &csr, float2 *A, hipStream_t s);
-// Builds the CSR; *mass_out = mass_in if given, else the degree-based masses.
+// Builds the CSR; *mass_out = mass_in if given, else the degree-based masses.  items =
+// false: without the work items (unless they are column-blocked).
 bgv_status build_csr(int32_t K, int64_t E, const int32_t *edges, const float *attr_w, const float *mass_in,
-                     CsrWs &w, hipStream_t s, const float **mass_out);
+                     CsrWs &w, hipStream_t s, const float **mass_out, bool items = true);
 
 // bgv_fa2_layout; may_fork lets the call run part of each iteration on a second stream
 // of the device (created once, on first use outside graph capture); results do not

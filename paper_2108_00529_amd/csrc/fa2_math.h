@@ -38,6 +38,66 @@ __device__ __forceinline__ void fa2_rep_run(float2 xi, const float4 *tile, int n
     }
 }
 
+// The same for a wavefront that is alone on its SIMD, which waits for every result it uses
+// at once: each group of eight is read while the one before it is used, and a group's
+// steps are kept apart (eight differences, eight reciprocals, ..., eight additions), which
+// the scheduler would interleave to save registers.
+__device__ __forceinline__ void fa2_rep_steps(float2 xi, const float4 (&b)[8], float &fx, float &fy) {
+    float dx[8], dy[8], d2[8], f[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        dx[u] = xi.x - b[u].x;
+        dy[u] = xi.y - b[u].y;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    uint32_t least = ~0u;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) d2[u] = fa2_norm2(dx[u], dy[u]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) f[u] = __builtin_amdgcn_rcpf(d2[u]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) least = min(least, __float_as_uint(d2[u]));
+#pragma unroll
+    for (int u = 0; u < 8; ++u) f[u] *= b[u].z;
+    if (__any(least == 0u)) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) f[u] = d2[u] > 0.f ? f[u] : 0.f;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        fx = __builtin_fmaf(f[u], dx[u], fx);
+        fy = __builtin_fmaf(f[u], dy[u], fy);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+}
+__device__ __forceinline__ void fa2_rep_load(const float4 *tile, float4 (&b)[8]) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) b[u] = tile[u];
+    __builtin_amdgcn_sched_barrier(0);
+}
+__device__ __forceinline__ void fa2_rep_ahead(float2 xi, const float4 *tile, int n, float &fx, float &fy) {
+    if (n <= 0) return;
+    float4 b[8], c[8];
+    fa2_rep_load(tile, b);
+    int q = 8;
+    for (; q + 8 < n; q += 16) {  // two groups a round, so that no group is moved
+        fa2_rep_load(tile + q, c);
+        fa2_rep_steps(xi, b, fx, fy);
+        fa2_rep_load(tile + q + 8, b);
+        fa2_rep_steps(xi, c, fx, fy);
+    }
+    if (q < n) {
+        fa2_rep_load(tile + q, c);
+        fa2_rep_steps(xi, b, fx, fy);
+        fa2_rep_steps(xi, c, fx, fy);
+    } else {
+        fa2_rep_steps(xi, b, fx, fy);
+    }
+}
+
 // The same sums on R bodies per lane, so that each LDS read serves R pairs.  With enough
 // bodies the loop is bound by vector issue, so the test for coincident bodies is taken
 // once per group: the smallest of its d^2 (as bit patterns: they are not negative) by
@@ -123,15 +183,75 @@ __device__ __forceinline__ void fa2_entry_add(E, float2 xj, float2 xi, float &ax
     ay += xj.y - xi.y;
 }
 
+// Sum over a wavefront by the tree that adds lanes 32 apart, then 16, 8, 4, 2 and 1 (what
+// a butterfly of __shfl_xor gives in every lane and one of __shfl_down in lane 0, bit for
+// bit: an addition's operands may change places), without the LDS crossbar: the first two
+// steps by lane swaps, the others by rotations within rows of 16, where the values
+// already repeat every 16, 8, 4 or 2 lanes.
+template <int kRor>
+__device__ __forceinline__ uint32_t fa2_row_rotate(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x120 + kRor, 0xf, 0xf, true);
+}
+__device__ __forceinline__ float fa2_wave_sum(float v) {
+    const uint32_t b = __float_as_uint(v);
+    const auto h = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    v = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+    const uint32_t c = __float_as_uint(v);
+    const auto q = __builtin_amdgcn_permlane16_swap(c, c, false, false);
+    v = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+    v += __uint_as_float(fa2_row_rotate<8>(__float_as_uint(v)));
+    v += __uint_as_float(fa2_row_rotate<4>(__float_as_uint(v)));
+    v += __uint_as_float(fa2_row_rotate<2>(__float_as_uint(v)));
+    v += __uint_as_float(fa2_row_rotate<1>(__float_as_uint(v)));
+    return v;
+}
+// Four such sums at once: lanes 16 q .. 16 q + 15 get the sum of v[q].  A swap exchanges
+// the halves of two registers, so that one addition folds both: ten instructions for four
+// sums instead of 64.
+__device__ __forceinline__ float fa2_wave_sum4(const float (&v)[4]) {
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[0]), __float_as_uint(v[2]), false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[1]), __float_as_uint(v[3]), false, false);
+    const float s = __uint_as_float(a[0]) + __uint_as_float(a[1]);  // halves: v[0], v[2]
+    const float t = __uint_as_float(b[0]) + __uint_as_float(b[1]);  // v[1], v[3]
+    const auto c = __builtin_amdgcn_permlane16_swap(__float_as_uint(s), __float_as_uint(t), false, false);
+    float r = __uint_as_float(c[0]) + __uint_as_float(c[1]);  // rows of 16: v[0], v[1], v[2], v[3]
+    r += __uint_as_float(fa2_row_rotate<8>(__float_as_uint(r)));
+    r += __uint_as_float(fa2_row_rotate<4>(__float_as_uint(r)));
+    r += __uint_as_float(fa2_row_rotate<2>(__float_as_uint(r)));
+    r += __uint_as_float(fa2_row_rotate<1>(__float_as_uint(r)));
+    return r;
+}
+template <int kRor>
+__device__ __forceinline__ double fa2_row_rotate(double v) {
+    return __hiloint2double((int)fa2_row_rotate<kRor>((uint32_t)__double2hiint(v)),
+                            (int)fa2_row_rotate<kRor>((uint32_t)__double2loint(v)));
+}
+__device__ __forceinline__ double fa2_wave_sum(double v) {
+    uint32_t lo = (uint32_t)__double2loint(v), hi = (uint32_t)__double2hiint(v);
+    const auto hl = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto hh = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    v = __hiloint2double((int)hh[0], (int)hl[0]) + __hiloint2double((int)hh[1], (int)hl[1]);
+    lo = (uint32_t)__double2loint(v);
+    hi = (uint32_t)__double2hiint(v);
+    const auto ql = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto qh = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    v = __hiloint2double((int)qh[0], (int)ql[0]) + __hiloint2double((int)qh[1], (int)ql[1]);
+    v += fa2_row_rotate<8>(v);
+    v += fa2_row_rotate<4>(v);
+    v += fa2_row_rotate<2>(v);
+    v += fa2_row_rotate<1>(v);
+    return v;
+}
+
 // Attraction over the CSR entries [b0, b1) of one block (at most kAttBlock entries), by
 // one wavefront: lane l takes entries b0 + l, b0 + l + 64, ... in order (four loads in
 // flight), then a fixed butterfly combines the lanes; every lane returns the total.
 constexpr uint32_t kAttBlock = 16 * kWave;
 
-template <typename E>
-__device__ __forceinline__ float2 fa2_block_attraction(const float2 *__restrict__ pos, const E *__restrict__ cw,
-                                                       uint32_t b0, uint32_t b1, float2 xi, int lane) {
-    float ax = 0.f, ay = 0.f;
+template <typename P, typename E>  // P: positions by index (a pointer, or an accessor)
+__device__ __forceinline__ void fa2_block_lane(P pos, const E *__restrict__ cw, uint32_t b0, uint32_t b1, float2 xi,
+                                               int lane, float &ax, float &ay) {
+    ax = ay = 0.f;
     uint32_t k = b0 + lane;
     // every lane adds its entries in ascending k; the unrolled loads only overlap
     for (; k + 7 * kWave < b1; k += 8 * kWave) {
@@ -157,12 +277,14 @@ __device__ __forceinline__ float2 fa2_block_attraction(const float2 *__restrict_
         const E e = cw[k];
         fa2_entry_add(e, pos[fa2_entry_id(e)], xi, ax, ay);
     }
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        ax += __shfl_xor(ax, o, kWave);
-        ay += __shfl_xor(ay, o, kWave);
-    }
-    return make_float2(ax, ay);
+}
+
+template <typename P, typename E>
+__device__ __forceinline__ float2 fa2_block_attraction(P pos, const E *__restrict__ cw,
+                                                       uint32_t b0, uint32_t b1, float2 xi, int lane) {
+    float ax, ay;
+    fa2_block_lane(pos, cw, b0, b1, xi, lane, ax, ay);
+    return make_float2(fa2_wave_sum(ax), fa2_wave_sum(ay));
 }
 
 // Attraction on node i = sum over its CSR entries [r0, r1) of w * (x_j - x_i): the row
@@ -170,8 +292,8 @@ __device__ __forceinline__ float2 fa2_block_attraction(const float2 *__restrict_
 // added in order (the first taken as is).  A row of up to kAttBlock entries is a single
 // block.  The blocks of a long (hub) row can then be summed by different wavefronts and
 // combined afterwards with the same additions (fa2_att_combine).
-template <typename E>
-__device__ __forceinline__ float2 fa2_row_attraction(const float2 *__restrict__ pos, const E *__restrict__ cw,
+template <typename P, typename E>
+__device__ __forceinline__ float2 fa2_row_attraction(P pos, const E *__restrict__ cw,
                                                      uint32_t r0, uint32_t r1, float2 xi, int lane) {
     float2 t = fa2_block_attraction(pos, cw, r0, r1 - r0 > kAttBlock ? r0 + kAttBlock : r1, xi, lane);
     for (uint32_t b = r0 + kAttBlock; b < r1; b += kAttBlock) {
@@ -197,15 +319,12 @@ __device__ __forceinline__ float2 fa2_att_combine(const float2 *__restrict__ att
 }
 
 // Fixed-pattern sum of one double2 per thread over a group of 256 threads (4
-// wavefronts): shuffle-down within each wavefront, then the 4 wavefront sums in order.
+// wavefronts): the wavefront tree, then the 4 wavefront sums in order.
 // ws must hold blockDim/64 entries; the result is valid in the group's first thread.
 // Contains a barrier: every thread of the workgroup must call it.
 __device__ __forceinline__ double2 fa2_sum256(double2 v, double2 *ws) {
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        v.x += __shfl_down(v.x, o, kWave);
-        v.y += __shfl_down(v.y, o, kWave);
-    }
+    v.x = fa2_wave_sum(v.x);
+    v.y = fa2_wave_sum(v.y);
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
     if (lane == 0) ws[w] = v;
     __syncthreads();

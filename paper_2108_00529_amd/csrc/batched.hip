@@ -9,9 +9,12 @@
 // over j in order, the same per-row attraction wavefront, per-256-node partial sums of
 // swing and traction in the plain kernels' fixed order, the same speed and move
 // arithmetic (fa2_math.h).  Integer results equal the plain path's by construction.
+#include <algorithm>
+
 #include "block_scan.h"
 #include "common.h"
 #include "fa2_math.h"
+#include "fa2_resident.h"
 #include "sketch_hash.h"
 
 namespace bgv {
@@ -21,6 +24,12 @@ constexpr int kBtMaxCells = 8192;  // rows*cols of a per-graph sketch, held in L
 // and the repulsion segments it has at most (segment sums: that many per node).
 constexpr int32_t kBtBigMax = 4096;
 constexpr int32_t kBtMaxSeg = kBtBigMax / kRepSegment;
+
+// An attraction item's workgroup holds the positions of a graph of up to this many nodes.
+constexpr int32_t kBtAttPos = 2048;
+
+constexpr int kBtIds = 8192;  // neighbour ids that a workgroup of the persistent launch holds on chip
+static_assert(sizeof(ResidentLds<kBtIds>) <= sizeof(uint32_t) * kBtMaxCells, "fits where the sketch was");
 
 struct BtArgs {
     int32_t G;
@@ -147,7 +156,7 @@ __global__ void __launch_bounds__(NT) k_batched(BtArgs a) {
     constexpr int NV = NT / 256;  // 256-node groups handled side by side in the layout
     static_assert(NT % 256 == 0 && NT <= 1024, "workgroup of 256, 512 or 1024 threads");
     static_assert(NT % kRepSegment == 0 || kRepSegment % NT == 0, "segment boundaries fall on LDS tile halves");
-    __shared__ uint32_t sk[kBtMaxCells];
+    __shared__ __align__(16) uint32_t sk[kBtMaxCells];
     __shared__ uint32_t hist[256], running[256];
     __shared__ uint32_t wcnt[NW][256];
     __shared__ float4 tile[NT];
@@ -346,6 +355,14 @@ __global__ void __launch_bounds__(NT) k_batched(BtArgs a) {
             __syncthreads();
             continue;
         }
+        __syncthreads();
+        if (NT >= kResidentMax && K <= (uint32_t)kResidentMax) {
+            // the state on chip, where the sketch was
+            fa2_resident<NT >= kResidentMax ? NT : kResidentMax, true>(
+                *reinterpret_cast<ResidentLds<kBtIds> *>(sk), (int32_t)K, a.iters, a.pos + n0, a.fprev + n0, mass, row,
+                cw, a.speed + g, a.kr, a.kg, a.tau, a.ks, a.ksmax);
+            continue;
+        }
 
         // ---- exact ForceAtlas2 iterations -------------------------------------------
         float2 *pos = a.pos + n0, *fprev = a.fprev + n0, *F = a.F + n0, *att = a.att + n0;
@@ -431,64 +448,85 @@ __global__ void __launch_bounds__(NT) k_batched(BtArgs a) {
 }
 
 // ---- layout of the listed large graphs, all of them per launch ------------------
-// Work items are the listed graphs' CSR rows (attraction), (256-node tile, repulsion
-// segment) pairs (repulsion) or tiles (segment sums, update), numbered through
-// exclusive prefix sums over the list; an item finds its graph by a table made once
-// per call.  Each graph goes through exactly the plain path's tile functions, so its
-// result equals a plain layout of it bit for bit.
+// Work items are (64-node wave tile, repulsion segment) pairs for the repulsion and wave
+// tiles for the attraction, in tables made once per call.  Each node's sums are those of
+// the plain path in the same order, so a graph's result equals a plain layout of it bit
+// for bit.
 struct BtBig {
     const int64_t *node_off, *edge_off;
     const int32_t *K;
     const int32_t *big;
     const unsigned int *nbig;
-    uint32_t *tile_off, *row_off;  // G+1 each: prefix sums of tiles / rows over the list
-    uint32_t *fitem_off;           // G+1: prefix sums of wave tiles x segments over the list
-    uint32_t *tile_slot;           // list slot of every tile item
-    uint32_t *fitem_slot;          // list slot of every (wave tile, segment) item
-    uint4 *row_desc;               // per row item: CSR entries [x, y) in cw, node z, graph base w
+    uint32_t *fitem_off, *aitem_off;  // G+1 each: prefix sums of the pairs / wave tiles over the list
+    uint32_t *total;                  // (pairs, wave tiles, graphs)
+    uint4 *graph;                     // per slot: first node, K, g, where its last segment's pairs start in fitem
+    uint32_t *fpos;                   // per slot: where its whole segments' pairs start there
+    uint4 *fitem;                     // (first node, K, wave tile, segment) of every pair, longest segments first
+    uint4 *aitem;                     // (first node, K, wave tile, g) of every attraction item
     const uint32_t *row;
     const int2 *cw;
     const float *mass;
-    float2 *pos, *fprev, *F, *att;
-    float2 *seg;                   // segment sums: kBtMaxSeg per node from the graph's first node
-    double2 *vpart;
-    float *speed;                  // caller's per-graph speeds (initial and final)
-    float *bspeed;                 // 2 per graph: ping-pong across iterations
+    float2 *pos, *fprev, *att;
+    float2 *seg;  // segment sums: kBtMaxSeg per node from the graph's first node
+    float *speed;
     float kr, kg, tau, ks, ksmax;
 };
 
-// Prefix sums of tiles, rows and (tile, segment) items over the list; initial speeds
-// into the ping-pong pair.
+// Prefix sums of the items over the list, and the places of every graph's pairs in the
+// order of falling segment length (32 classes; the order inside one does not matter).
 __global__ void __launch_bounds__(1024) k_bt_plan(BtBig b) {
     const uint32_t nb = *b.nbig;
-    uint32_t ct = 0, cr = 0, cf = 0;
+    uint32_t cf = 0, ca = 0;
     for (uint32_t s0 = 0; s0 < nb; s0 += 1024) {
         const uint32_t sl = s0 + threadIdx.x;
-        uint32_t tiles = 0, rows = 0, fitems = 0;
+        uint32_t wt = 0, segs = 0;
         if (sl < nb) {
-            const int32_t g = b.big[sl];
-            rows = (uint32_t)b.K[g];
-            tiles = (rows + kFa2Tile - 1) / kFa2Tile;
-            fitems = ((rows + kWave - 1) / kWave) * (uint32_t)fa2_rep_segments((int32_t)rows);
-            b.bspeed[2 * g] = b.speed[g];
+            const int32_t K = b.K[b.big[sl]];
+            wt = (uint32_t)((K + kWave - 1) / kWave);
+            segs = (uint32_t)fa2_rep_segments(K);
         }
-        uint32_t tt, tr, tf;
-        const uint32_t et = block_excl_scan<uint32_t>(tiles, &tt);
-        const uint32_t er = block_excl_scan<uint32_t>(rows, &tr);
-        const uint32_t ef = block_excl_scan<uint32_t>(fitems, &tf);
+        uint32_t tf, ta;
+        const uint32_t ef = block_excl_scan<uint32_t>(wt * segs, &tf);
+        const uint32_t ea = block_excl_scan<uint32_t>(wt, &ta);
         if (sl < nb) {
-            b.tile_off[sl] = ct + et;
-            b.row_off[sl] = cr + er;
             b.fitem_off[sl] = cf + ef;
+            b.aitem_off[sl] = ca + ea;
         }
-        ct += tt;
-        cr += tr;
         cf += tf;
+        ca += ta;
     }
     if (threadIdx.x == 0) {
-        b.tile_off[nb] = ct;
-        b.row_off[nb] = cr;
         b.fitem_off[nb] = cf;
+        b.aitem_off[nb] = ca;
+        b.total[0] = cf;
+        b.total[1] = ca;
+        b.total[2] = nb;
+    }
+    constexpr uint32_t kWidth = kRepSegment / 32;
+    __shared__ uint32_t at[32];
+    if (threadIdx.x < 32) at[threadIdx.x] = 0u;
+    __syncthreads();
+    for (uint32_t sl = threadIdx.x; sl < nb; sl += 1024) {
+        const uint32_t K = (uint32_t)b.K[b.big[sl]], wt = (K + kWave - 1) / kWave, rest = K % kRepSegment;
+        if (K >= (uint32_t)kRepSegment) atomicAdd(&at[0], wt * (K / kRepSegment));
+        if (rest) atomicAdd(&at[(kRepSegment - rest) / kWidth], wt);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t run = 0;
+        for (int c = 0; c < 32; ++c) {
+            const uint32_t n = at[c];
+            at[c] = run;
+            run += n;
+        }
+    }
+    __syncthreads();
+    for (uint32_t sl = threadIdx.x; sl < nb; sl += 1024) {
+        const int32_t g = b.big[sl];
+        const uint32_t K = (uint32_t)b.K[g], wt = (K + kWave - 1) / kWave, rest = K % kRepSegment;
+        b.fpos[sl] = K >= (uint32_t)kRepSegment ? atomicAdd(&at[0], wt * (K / kRepSegment)) : 0u;
+        b.graph[sl] = make_uint4((uint32_t)b.node_off[g], K, (uint32_t)g,
+                                 rest ? atomicAdd(&at[(kRepSegment - rest) / kWidth], wt) : 0u);
     }
 }
 
@@ -503,24 +541,21 @@ __device__ __forceinline__ uint32_t bt_slot(const uint32_t *off, uint32_t nb, ui
     return lo;
 }
 
-// Per-call maps: each row item's descriptor and each tile and (tile, segment) item's
-// slot, found once instead of once per iteration.
-__global__ void __launch_bounds__(kFa2Tile) k_bt_maps(BtBig b) {
-    const uint32_t nb = *b.nbig;
-    const uint32_t R = b.row_off[nb], T = b.tile_off[nb], FI = b.fitem_off[nb];
-    const uint32_t stride = gridDim.x * kFa2Tile;
-    for (uint32_t r = blockIdx.x * kFa2Tile + threadIdx.x; r < R; r += stride) {
-        const uint32_t sl = bt_slot(b.row_off, nb, r);
-        const int32_t g = b.big[sl];
-        const uint32_t i = r - b.row_off[sl];
-        const int64_t n0 = b.node_off[g];
-        const uint32_t *row = b.row + n0 + g;
-        const uint32_t c0 = (uint32_t)(2 * b.edge_off[g]);
-        b.row_desc[r] = make_uint4(c0 + row[i], c0 + row[i + 1], (uint32_t)n0 + i, (uint32_t)n0);
+// The items of both tables.
+__global__ void __launch_bounds__(256) k_bt_maps(BtBig b) {
+    const uint32_t FI = b.total[0], AI = b.total[1], nb = b.total[2];
+    const uint32_t stride = gridDim.x * 256, t = blockIdx.x * 256 + threadIdx.x;
+    for (uint32_t x = t; x < FI; x += stride) {
+        const uint32_t sl = bt_slot(b.fitem_off, nb, x), q = x - b.fitem_off[sl];
+        const uint4 d = b.graph[sl];
+        const uint32_t wt = (d.y + kWave - 1) / kWave, whole = wt * (d.y / kRepSegment);
+        b.fitem[q < whole ? b.fpos[sl] + q : d.w + (q - whole)] = make_uint4(d.x, d.y, q % wt, q / wt);
     }
-    for (uint32_t x = blockIdx.x * kFa2Tile + threadIdx.x; x < T; x += stride) b.tile_slot[x] = bt_slot(b.tile_off, nb, x);
-    for (uint32_t x = blockIdx.x * kFa2Tile + threadIdx.x; x < FI; x += stride)
-        b.fitem_slot[x] = bt_slot(b.fitem_off, nb, x);
+    for (uint32_t x = t; x < AI; x += stride) {
+        const uint32_t sl = bt_slot(b.aitem_off, nb, x);
+        const uint4 d = b.graph[sl];
+        b.aitem[x] = make_uint4(d.x, d.y, x - b.aitem_off[sl], d.z);
+    }
 }
 
 // Repulsion of one (64-target wave tile, segment) item by one wavefront: the segment's
@@ -551,70 +586,122 @@ __device__ __forceinline__ void bt_wave_repulsion(int32_t wt, int32_t sgm, int32
     if (live) seg[(int64_t)sgm * K + i] = make_float2(fx, fy);
 }
 
-// All (wave tile, segment) items, one per wavefront, then the attraction of the listed
-// graphs' rows, one wavefront per row as in the persistent kernel (the row descriptor:
-// absolute CSR range, node, graph base, in one load).  A graph of one segment takes the
-// same path: its one segment sum is its repulsion.
-__global__ void __launch_bounds__(kFa2Tile) k_bt_force(BtBig b) {
-    __shared__ float4 slab[kFa2Tile];
-    const uint32_t nb = *b.nbig;
-    const uint32_t FI = b.fitem_off[nb], R = b.row_off[nb];
+// The first rep_blocks workgroups sum repulsion: their wavefronts share out the pairs,
+// longest first, back and forth, so that each gets about the same number of terms whatever
+// the graphs' sizes.  The others take the attraction of a wave tile's rows each, the
+// graph's positions in LDS: read from memory for every entry, they took longer than the
+// repulsion (47 against 31 us).  A graph of one segment takes the same path: its one
+// segment sum is its repulsion.  Bound by vector issue: 512 planted graphs (74M pairs, 4.5M
+// row entries per iteration) take 40.6 us, the repulsion alone 30.6 and the attraction alone
+// 25; a wavefront per item and then per row in one grid took 48.4.
+__global__ void __launch_bounds__(kFa2Tile) k_bt_force(BtBig b, uint32_t rep_blocks) {
+    __shared__ __align__(16) float2 xs[kBtAttPos];
+    __shared__ uint32_t rows[kWave + 1];
+    constexpr int NW = kFa2Tile / kWave;
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    const uint32_t nw = gridDim.x * (kFa2Tile / kWave);
-    for (uint32_t x = blockIdx.x * (kFa2Tile / kWave) + w; x < FI; x += nw) {
-        const uint32_t sl = b.fitem_slot[x];
-        const int32_t g = b.big[sl];
-        const int64_t n0 = b.node_off[g];
-        const int32_t K = b.K[g];
-        const uint32_t wtiles = (uint32_t)((K + kWave - 1) / kWave);
-        const uint32_t q = x - b.fitem_off[sl];
-        bt_wave_repulsion((int32_t)(q % wtiles), (int32_t)(q / wtiles), K, b.pos + n0, b.mass + n0,
-                          b.seg + kBtMaxSeg * n0, slab + w * kWave);
+    if (blockIdx.x < rep_blocks) {
+        float4 *slab = reinterpret_cast<float4 *>(xs) + w * kWave;
+        const uint32_t FI = b.total[0], nw = rep_blocks * NW, x0 = blockIdx.x * NW + w;
+        for (uint32_t base = 0, round = 0; base < FI; base += nw, ++round) {
+            const uint32_t x = base + (round & 1u ? nw - 1u - x0 : x0);
+            if (x >= FI) continue;
+            const uint4 it = b.fitem[x];
+            bt_wave_repulsion((int32_t)it.z, (int32_t)it.w, (int32_t)it.y, b.pos + it.x, b.mass + it.x,
+                              b.seg + (int64_t)kBtMaxSeg * it.x, slab);
+        }
+        return;
     }
-    for (uint32_t r = (blockIdx.x * kFa2Tile + threadIdx.x) / kWave; r < R; r += nw) {
-        const uint4 d = b.row_desc[r];  // (first entry, end entry, node, graph's first node)
-        const float2 *pos = b.pos + d.w;
-        const float2 f = fa2_row_attraction(pos, b.cw, d.x, d.y, b.pos[d.z], lane);
-        if (lane == 0) b.att[d.z] = f;
-    }
-}
-
-// Segment sums added in order, then the rest of every force and the tiles' partials.
-__global__ void __launch_bounds__(kFa2Tile) k_bt_combine(BtBig b) {
-    const uint32_t nb = *b.nbig;
-    const uint32_t T = b.tile_off[nb];
-    for (uint32_t x = blockIdx.x; x < T; x += gridDim.x) {
-        const uint32_t sl = b.tile_slot[x];
-        const int32_t g = b.big[sl];
-        const int64_t n0 = b.node_off[g];
-        const int32_t K = b.K[g];
-        fa2_combine_tile((int32_t)(x - b.tile_off[sl]), K, fa2_rep_segments(K), b.seg + kBtMaxSeg * n0, b.pos + n0,
-                         b.mass + n0, b.att + n0, nullptr, b.kr, b.kg, b.fprev + n0, b.F + n0,
-                         b.vpart + (n0 / 256) + g);
-        __syncthreads();  // the tile function's LDS is reused by the next item
+    const uint32_t AI = b.total[1];
+    for (uint32_t x = blockIdx.x - rep_blocks; x < AI; x += gridDim.x - rep_blocks) {
+        const uint4 it = b.aitem[x];
+        const int64_t n0 = it.x;
+        const int32_t g = (int32_t)it.w, K = (int32_t)it.y, r0 = (int32_t)it.z * kWave, nr = min(kWave, K - r0);
+        const uint32_t *row = b.row + n0 + g + r0;
+        const int2 *cw = b.cw + 2 * b.edge_off[g];
+        const float2 *pos = b.pos + n0;
+        if (threadIdx.x <= (uint32_t)nr) rows[threadIdx.x] = row[threadIdx.x];
+        if (K <= kBtAttPos)
+            for (int32_t i = threadIdx.x; i < K; i += kFa2Tile) xs[i] = pos[i];
+        __syncthreads();
+        if (K <= kBtAttPos)
+            fa2_rows_attraction((const float2 *)xs, cw, rows, r0, nr, b.att + n0 + r0, w, NW, lane);
+        else
+            fa2_rows_attraction(pos, cw, rows, r0, nr, b.att + n0 + r0, w, NW, lane);
+        __syncthreads();
     }
 }
 
-__global__ void __launch_bounds__(kFa2Tile) k_bt_update(BtBig b, int32_t it) {
-    const uint32_t nb = *b.nbig;
-    const uint32_t T = b.tile_off[nb];
-    for (uint32_t x = blockIdx.x; x < T; x += gridDim.x) {
-        const uint32_t sl = b.tile_slot[x];
-        const int32_t g = b.big[sl];
-        const int64_t n0 = b.node_off[g];
-        const int32_t ntiles = (int32_t)(b.tile_off[sl + 1] - b.tile_off[sl]);
-        fa2_update_tile((int32_t)(x - b.tile_off[sl]), ntiles, b.K[g], b.pos + n0, b.fprev + n0, b.F + n0,
-                        b.vpart + (n0 / 256) + g, ntiles, b.bspeed + 2 * g + (it & 1),
-                        b.bspeed + 2 * g + ((it + 1) & 1), b.tau, b.ks, b.ksmax);
-        __syncthreads();  // the tile function's LDS is reused by the next item
-    }
-}
-
-__global__ void k_bt_finish(BtBig b, int32_t iters) {
-    const uint32_t nb = *b.nbig;
-    for (uint32_t sl = blockIdx.x * blockDim.x + threadIdx.x; sl < nb; sl += gridDim.x * blockDim.x) {
-        const int32_t g = b.big[sl];
-        b.speed[g] = b.bspeed[2 * g + (iters & 1)];
+constexpr int kBtStep = 512;  // 256 threads 15.5 us, 1,024 10.0
+// One workgroup per listed graph: segment sums added in order, the rest of every force, the
+// 256-node tiles' partial sums, the global speed and the moves.  Two launches with a
+// workgroup per tile took 10.9 us, this one 9.0: its chain of dependent loads.
+__global__ void __launch_bounds__(kBtStep) k_bt_step(BtBig b) {
+    constexpr int NW = kBtStep / kWave, kRounds = kBtBigMax / kBtStep;
+    static_assert(kRounds * NW == kWave, "a lane per wavefront sum");
+    __shared__ double2 ws[kWave];
+    const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
+    const uint32_t nb = b.total[2];
+    for (uint32_t sl = blockIdx.x; sl < nb; sl += gridDim.x) {
+        const uint4 d = b.graph[sl];
+        const int64_t n0 = d.x;
+        const int32_t K = (int32_t)d.y, nseg = fa2_rep_segments(K);
+        const float2 *seg = b.seg + kBtMaxSeg * n0;
+        float s = b.speed[d.z];
+        float2 xi[kRounds], fp[kRounds], f[kRounds];
+#pragma unroll
+        for (int q = 0; q < kRounds; ++q) {
+            const int32_t i = q * kBtStep + t;
+            double2 st = make_double2(0.0, 0.0);
+            if (q * kBtStep + w * kWave < K) {  // whole wavefronts without a node add nothing
+                if (i < K) {
+                    const float mi = b.mass[n0 + i];
+                    const float2 at = b.att[n0 + i];
+                    xi[q] = b.pos[n0 + i];
+                    fp[q] = b.fprev[n0 + i];
+                    float2 v[kBtMaxSeg];  // all loads before the first sum
+#pragma unroll
+                    for (int32_t u = 0; u < kBtMaxSeg; ++u)
+                        if (u < nseg) v[u] = seg[(int64_t)u * K + i];
+                    float2 r = v[0];
+#pragma unroll
+                    for (int32_t u = 1; u < kBtMaxSeg; ++u)
+                        if (u < nseg) {
+                            r.x += v[u].x;
+                            r.y += v[u].y;
+                        }
+                    f[q] = fa2_net_force(xi[q], mi, b.kr, r.x, r.y, at, b.kg);
+                    st = fa2_swing_traction(f[q], fp[q], mi);
+                }
+                st.x = fa2_wave_sum(st.x);
+                st.y = fa2_wave_sum(st.y);
+            }
+            if (lane == 0) ws[q * NW + w] = st;
+        }
+        __syncthreads();
+        if (w * kWave < K) {
+            // every wavefront for itself: a tile's four wavefront sums in order, then the tiles'
+            // as one wavefront of the plain kernel sums them (its other three hold zeros)
+            double2 acc = make_double2(0.0, 0.0);
+            if (lane < kWave / 4)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    acc.x += ws[4 * lane + q].x;
+                    acc.y += ws[4 * lane + q].y;
+                }
+            acc.x = fa2_wave_sum(acc.x);
+            acc.y = fa2_wave_sum(acc.y);
+            s = fa2_global_speed(acc.x, acc.y, s, b.tau);
+#pragma unroll
+            for (int q = 0; q < kRounds; ++q) {
+                const int32_t i = q * kBtStep + t;
+                if (i < K) {
+                    b.pos[n0 + i] = fa2_move(xi[q], f[q], fp[q], s, b.ks, b.ksmax);
+                    b.fprev[n0 + i] = f[q];
+                }
+            }
+        }
+        __syncthreads();  // LDS is reused by the next graph; every thread has read the speed
+        if (t == 0) b.speed[d.z] = s;
     }
 }
 
@@ -630,10 +717,10 @@ struct BtWs {
     unsigned int *queue;
     int32_t *big;
     unsigned int *nbig;
-    uint32_t *tile_off, *row_off, *fitem_off, *tile_slot, *fitem_slot;
-    uint4 *row_desc;
+    uint32_t *fitem_off, *aitem_off;
+    uint32_t *total, *fpos;
+    uint4 *graph, *fitem, *aitem;
     float2 *seg;
-    float *bspeed;
 };
 
 static size_t bt_layout(Carver &c, int32_t G, int64_t n_total, int64_t m_total, BtWs *w) {
@@ -654,16 +741,15 @@ static size_t bt_layout(Carver &c, int32_t G, int64_t n_total, int64_t m_total, 
     w->queue = c.take<unsigned int>(1);
     w->big = c.take<int32_t>((size_t)G);
     w->nbig = c.take<unsigned int>(1);
-    w->tile_off = c.take<uint32_t>((size_t)G + 1);
-    w->row_off = c.take<uint32_t>((size_t)G + 1);
     w->fitem_off = c.take<uint32_t>((size_t)G + 1);
-    w->tile_slot = c.take<uint32_t>(n / kFa2Tile + (size_t)G + 1);
-    // a listed graph has K <= kBtBigMax supernodes, at most kBtMaxSeg segments of them
+    w->aitem_off = c.take<uint32_t>((size_t)G + 1);
     // a listed graph has K <= kBtBigMax supernodes: at most kBtMaxSeg segments of K / 64 + 1 wave tiles
-    w->fitem_slot = c.take<uint32_t>((size_t)kBtMaxSeg * (n / kWave + (size_t)G + 1));
-    w->row_desc = c.take<uint4>(n);
+    w->fitem = c.take<uint4>((size_t)kBtMaxSeg * (n / kWave + (size_t)G + 1));
+    w->aitem = c.take<uint4>(n / kWave + (size_t)G + 1);
+    w->fpos = c.take<uint32_t>((size_t)G);
+    w->graph = c.take<uint4>((size_t)G);
+    w->total = c.take<uint32_t>(3);
     w->seg = c.take<float2>((size_t)kBtMaxSeg * n);
-    w->bspeed = c.take<float>(2 * (size_t)G);
     return c.size();
 }
 
@@ -795,43 +881,37 @@ extern "C" bgv_status bgv_batched(int32_t G, int64_t n_total, int64_t m_total, c
         b.K = K;
         b.big = w.big;
         b.nbig = w.nbig;
-        b.tile_off = w.tile_off;
-        b.row_off = w.row_off;
         b.fitem_off = w.fitem_off;
-        b.tile_slot = w.tile_slot;
-        b.fitem_slot = w.fitem_slot;
-        b.row_desc = w.row_desc;
+        b.aitem_off = w.aitem_off;
+        b.fitem = w.fitem;
+        b.aitem = w.aitem;
+        b.fpos = w.fpos;
+        b.graph = w.graph;
+        b.total = w.total;
         b.seg = w.seg;
         b.row = w.row;
         b.cw = w.cw;
         b.mass = w.mass;
         b.pos = a.pos;
         b.fprev = a.fprev;
-        b.F = w.F;
         b.att = w.att;
-        b.vpart = w.vpart;
         b.speed = speed;
-        b.bspeed = w.bspeed;
         b.kr = fa->kr;
         b.kg = fa->kg;
         b.tau = fa->tau;
         b.ks = fa->ks;
         b.ksmax = fa->ksmax;
-        // item bounds known on the host (tiles <= n_total/256 + G, rows <= n_total); wide
-        // grids, since a workgroup holding two items of a large graph doubles the path
-        // (measured: 512 workgroups looping over the items were 1.4x slower than 4096)
-        const unsigned tiles_bound = (unsigned)(n_total / kFa2Tile + G);
-        const unsigned gt = tiles_bound < 4096u ? (tiles_bound > 0 ? tiles_bound : 1u) : 4096u;
-        // force items are wavefronts: four per workgroup
-        const unsigned gf = gt * (unsigned)kBtMaxSeg < 16384u ? gt * (unsigned)kBtMaxSeg : 16384u;
+        // Two wavefronts per SIMD for the repulsion, whose items are few and long (three:
+        // 40.8 -> 43.9 us per launch), and as many attraction workgroups as pay: six per
+        // compute unit 43.5 us, 14 40.8, 24 the same.
+        const unsigned rep_blocks = 2u * (unsigned)cus;
+        const unsigned att_blocks = (unsigned)std::min<int64_t>(n_total / kWave + G, 14 * cus);
         BGV_LAUNCH(k_bt_plan, dim3(1), dim3(1024), 0, s, b);
-        BGV_LAUNCH(k_bt_maps, dim3(grid_for(n_total > 0 ? n_total : 1, kFa2Tile, 4096)), dim3(kFa2Tile), 0, s, b);
+        BGV_LAUNCH(k_bt_maps, dim3(grid_for(n_total > 0 ? n_total : 1, 256, 1024)), dim3(256), 0, s, b);
         for (int32_t it = 0; it < fa->iters; ++it) {
-            BGV_LAUNCH(k_bt_force, dim3(gf), dim3(kFa2Tile), 0, s, b);
-            BGV_LAUNCH(k_bt_combine, dim3(gt), dim3(kFa2Tile), 0, s, b);
-            BGV_LAUNCH(k_bt_update, dim3(gt), dim3(kFa2Tile), 0, s, b, it);
+            BGV_LAUNCH(k_bt_force, dim3(rep_blocks + att_blocks), dim3(kFa2Tile), 0, s, b, rep_blocks);
+            BGV_LAUNCH(k_bt_step, dim3((unsigned)std::min(G, 2048 / kBtStep * cus)), dim3(kBtStep), 0, s, b);
         }
-        BGV_LAUNCH(k_bt_finish, dim3(1), dim3(256), 0, s, b, fa->iters);
     }
     return BGV_OK;
 }

@@ -705,8 +705,9 @@ __global__ void __launch_bounds__(kResidentThreads) k_resident(int32_t K, int32_
                                                                 const E *__restrict__ cw, float *speed, float kr,
                                                                 float kg, float tau, float ks, float ksmax) {
     extern __shared__ char lds[];
-    fa2_resident<kResidentThreads>(*reinterpret_cast<ResidentLds<kResidentIds> *>(lds), K, iters, pos, fprev, mass,
-                                   row, cw, speed, kr, kg, tau, ks, ksmax);
+    fa2_resident<kResidentThreads, !std::is_same<E, int2>::value>(*reinterpret_cast<ResidentLds<kResidentIds> *>(lds),
+                                                                  K, iters, pos, fprev, mass, row, cw, speed, kr, kg,
+                                                                  tau, ks, ksmax);
 }
 
 template <typename E>

@@ -304,6 +304,50 @@ __device__ __forceinline__ float2 fa2_row_attraction(P pos, const E *__restrict_
     return t;
 }
 
+// The attractions of nodes base + first, base + first + step, ... below base + n by one
+// wavefront into att[first], ...; row[0] is node base's row start.  Four rows at a time, so
+// that their loads overlap and one packed reduction sums all four; rows cut into blocks
+// (more than kAttBlock entries) go one by one.
+template <typename P, typename E>
+__device__ __forceinline__ void fa2_rows_attraction(P pos, const E *cw, const uint32_t *row, int32_t base, int32_t n,
+                                                    float2 *att, int32_t first, int32_t step, int lane) {
+    for (int32_t r0 = first; r0 < n; r0 += 4 * step) {
+        uint32_t b[4], len[4], longest = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int32_t r = min(r0 + q * step, n - 1);
+            b[q] = row[r];
+            len[q] = r0 + q * step < n ? row[r + 1] - b[q] : 0u;
+            longest = max(longest, len[q]);
+        }
+        float ax[4], ay[4];
+        if (longest <= (uint32_t)kWave) {  // uniform over the wavefront
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                ax[q] = ay[q] = 0.f;
+                if ((uint32_t)lane < len[q]) {
+                    const E e = cw[b[q] + lane];
+                    fa2_entry_add(e, pos[fa2_entry_id(e)], pos[base + min(r0 + q * step, n - 1)], ax[q], ay[q]);
+                }
+            }
+        } else if (longest <= kAttBlock) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                fa2_block_lane(pos, cw, b[q], b[q] + len[q], pos[base + min(r0 + q * step, n - 1)], lane, ax[q], ay[q]);
+        } else {
+            for (int q = 0; q < 4 && r0 + q * step < n; ++q) {
+                const int32_t r = r0 + q * step;
+                const float2 a = fa2_row_attraction(pos, cw, b[q], b[q] + len[q], pos[base + r], lane);
+                if (lane == 0) att[r] = a;
+            }
+            continue;
+        }
+        const float sx = fa2_wave_sum4(ax), sy = fa2_wave_sum4(ay);
+        const int32_t r = r0 + lane / 16 * step;
+        if (lane % 16 == 0 && r < n) att[r] = make_float2(sx, sy);
+    }
+}
+
 // Node i's attraction from its block sums attb[item_of[i] .. item_of[i + 1]), added in
 // block order exactly as fa2_row_attraction adds them.
 __device__ __forceinline__ float2 fa2_att_combine(const float2 *__restrict__ attb, const uint32_t *__restrict__ item_of,
@@ -380,7 +424,7 @@ __device__ __forceinline__ float2 fa2_move(float2 p, float2 f, float2 fp, float 
     return p;
 }
 
-// ---- whole-tile bodies shared by the plain kernels and the batched big-graph path ----
+// ---- whole-tile bodies of the plain kernels --------------------------------------------
 // A tile is 256 consecutive nodes handled by one 256-thread workgroup.
 constexpr int kFa2Tile = 256;
 

@@ -30,54 +30,10 @@ struct ResidentPos {
     __device__ __forceinline__ float2 operator[](int32_t i) const { return make_float2(body[i].x, body[i].y); }
 };
 
-// The attractions of rows first, first + step, ... by one wavefront, four rows at a time,
-// so that their loads overlap and one packed reduction sums all four; rows cut into blocks
-// (more than kAttBlock entries) go one by one.
-template <typename E>
-__device__ __forceinline__ void resident_attraction(const float4 *body, const E *cw, const uint32_t *row,
-                                                    float2 *att, int32_t K, int32_t first, int32_t step, int lane) {
-    const ResidentPos pos{body};
-    for (int32_t r0 = first; r0 < K; r0 += 4 * step) {
-        uint32_t b[4], len[4], longest = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int32_t r = min(r0 + q * step, K - 1);
-            b[q] = row[r];
-            len[q] = r0 + q * step < K ? row[r + 1] - b[q] : 0u;
-            longest = max(longest, len[q]);
-        }
-        float ax[4], ay[4];
-        if (longest <= (uint32_t)kWave) {  // uniform over the wavefront
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                ax[q] = ay[q] = 0.f;
-                if ((uint32_t)lane < len[q]) {
-                    const E e = cw[b[q] + lane];
-                    fa2_entry_add(e, pos[fa2_entry_id(e)], pos[min(r0 + q * step, K - 1)], ax[q], ay[q]);
-                }
-            }
-        } else if (longest <= kAttBlock) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                fa2_block_lane(pos, cw, b[q], b[q] + len[q], pos[min(r0 + q * step, K - 1)], lane, ax[q], ay[q]);
-        } else {
-            for (int q = 0; q < 4 && r0 + q * step < K; ++q) {
-                const int32_t r = r0 + q * step;
-                const float2 a = fa2_row_attraction(pos, cw, b[q], b[q] + len[q], pos[r], lane);
-                if (lane == 0) att[r] = a;
-            }
-            continue;
-        }
-        const float sx = fa2_wave_sum4(ax), sy = fa2_wave_sum4(ay);
-        const int32_t r = r0 + lane / 16 * step;
-        if (lane % 16 == 0 && r < K) att[r] = make_float2(sx, sy);
-    }
-}
-
 // `iters` iterations of K <= kResidentMax nodes by NT >= kResidentMax threads.  row[K+1]
-// and cw: the supergraph's rows; pos, fprev and *speed in and out.  Every thread of the
-// workgroup calls it.
-template <int NT, int kIds, typename E>
+// and cw: the supergraph's rows (kUnit: every weight is 1, so ids alone will do); pos,
+// fprev and *speed in and out.  Every thread of the workgroup calls it.
+template <int NT, bool kUnit, int kIds, typename E>
 __device__ __forceinline__ void fa2_resident(ResidentLds<kIds> &sh, int32_t K, int32_t iters, float2 *pos,
                                              float2 *fprev, const float *mass, const uint32_t *row, const E *cw,
                                              float *speed, float kr, float kg, float tau, float ks, float ksmax) {
@@ -86,7 +42,7 @@ __device__ __forceinline__ void fa2_resident(ResidentLds<kIds> &sh, int32_t K, i
     const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
     const bool live = t < K;
     const uint32_t nent = row[K];
-    const bool staged = !std::is_same<E, int2>::value && nent <= (uint32_t)kIds;
+    const bool staged = kUnit && nent <= (uint32_t)kIds;
     float2 xi = live ? pos[t] : make_float2(0.f, 0.f), fp = live ? fprev[t] : make_float2(0.f, 0.f);
     const float mi = live ? mass[t] : 0.f;
     float s = *speed;
@@ -106,8 +62,8 @@ __device__ __forceinline__ void fa2_resident(ResidentLds<kIds> &sh, int32_t K, i
         if (w < owners) fa2_rep_ahead(xi, sh.body, (K + 7) & ~7, rx, ry);
         if (helpers == 0 || w >= owners) {
             const int32_t first = helpers ? w - owners : w, step = helpers ? helpers : NW;
-            if (staged) resident_attraction(sh.body, sh.ids, sh.row, sh.att, K, first, step, lane);
-            else resident_attraction(sh.body, cw, sh.row, sh.att, K, first, step, lane);
+            if (staged) fa2_rows_attraction(ResidentPos{sh.body}, sh.ids, sh.row, 0, K, sh.att, first, step, lane);
+            else fa2_rows_attraction(ResidentPos{sh.body}, cw, sh.row, 0, K, sh.att, first, step, lane);
         }
         __syncthreads();
         float2 f = make_float2(0.f, 0.f);
@@ -148,6 +104,11 @@ __device__ __forceinline__ void fa2_resident(ResidentLds<kIds> &sh, int32_t K, i
         fprev[t] = fp;
     }
     if (t == 0) *speed = s;
+    // Before the LDS is used again, and before whatever thread 0 alone does next: without a
+    // barrier in between, a caller's loop over graphs that starts with thread 0 taking the
+    // next one is compiled into a loop of thread 0 around a loop of its wavefront's other
+    // lanes, which then meet the barriers without it and never end.
+    __syncthreads();
 }
 
 }  // namespace bgv

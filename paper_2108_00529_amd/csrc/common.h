@@ -167,10 +167,9 @@ bgv_status onesweep_sort_pairs(KT *keys, KT *keys_alt, uint32_t *vals, uint32_t 
                                uint32_t **vals_out, void *scratch, hipStream_t s, bool counted = false);
 
 // One-sweep sort of 32-bit keys with 32-bit values (all 32 bits, four 8-bit passes, one
-// launch per pass after a counting launch; see primitives.hip).  keys/alt and
-// vals/vals_alt are ping-pong buffers of n entries; after the four passes the result is
-// back in keys/vals.  Scratch from onesweep_workspace(n).  With counted = true a
-// producer of the keys has already done what the counting launch would, for tiles of
+// launch per pass; see primitives.hip).  keys/alt and vals/vals_alt are ping-pong buffers of
+// n entries; after the four passes the result is back in keys/vals.  Scratch from
+// onesweep_workspace(n).  The producer of the keys has done the counting, for tiles of
 // 256 * os_items(n) consecutive keys: added each tile's digit counts of all four passes
 // into OsBuffers::totals[pass*256 + d] (which the caller had cleared before, in an
 // earlier launch) and written zeros over OsBuffers::status (status_words words).
@@ -186,6 +185,6 @@ int os_items(int64_t n);
 size_t onesweep_workspace(int64_t n);
 void onesweep_layout(void *scratch, int64_t n, int items, OsBuffers *b);
 bgv_status onesweep_sort_u32(uint32_t *keys, uint32_t *keys_alt, uint32_t *vals, uint32_t *vals_alt, int64_t n,
-                             uint32_t **keys_out, uint32_t **vals_out, void *scratch, hipStream_t s, bool counted);
+                             uint32_t **keys_out, uint32_t **vals_out, void *scratch, hipStream_t s);
 
 }  // namespace bgv

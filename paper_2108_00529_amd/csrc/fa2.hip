@@ -8,7 +8,8 @@
 //   exact:  k_force_exact   LDS-tiled all-pairs repulsion (split into 512-body segments
 //                           summed by k_force_combine when K is larger) + attraction +
 //                           gravity, swing/traction, FP64 block partials of the two sums
-//   BH:     k_bh_bbox -> k_bh_codes -> radix sort -> k_bh_gather -> FP64 prefix sums
+//   BH:     k_bh_bbox -> Morton codes and bodies in their order (k_bh_split, k_bh_bucket;
+//           a radix sort for the most bodies) -> FP64 prefix sums
 //           -> k_bh_build_attract (binary radix tree: centre of mass of a node =
 //           difference of prefix sums over its body range, so no atomics; the
 //           attraction in the same launch) -> k_bh_force (traversal with a shared
@@ -25,6 +26,7 @@
 #include <mutex>
 #include <type_traits>
 
+#include "bh_sort.h"
 #include "block_scan.h"
 #include "common.h"
 #include "fa2_internal.h"
@@ -117,6 +119,7 @@ size_t csr_layout(Carver &c, int32_t K, int64_t E, CsrWs *w, bool allow_cols) {
     w->cw = c.take<int2>((size_t)nent);
     w->mass = c.take<float>((size_t)K);
     w->cols = allow_cols && att_cols(K);
+    w->beside = false;
     w->items_bound = att_items_cap(K, E, w->cols);
     w->item_of = c.take<uint32_t>((size_t)K + 1);
     w->item_row = c.take<uint32_t>((size_t)w->items_bound);
@@ -390,10 +393,15 @@ __global__ void k_attc_plan(int32_t nblk, int32_t G, const uint32_t *__restrict_
     wg_first[nblk] = (uint32_t)G;
 }
 
-static bgv_status att_col_grid(int32_t K, int32_t *G) {
+// One workgroup per compute unit, or, where it runs beside an iteration's sort and tree
+// build, on three quarters of them: it waits for memory (53 us on 256 compute units beside
+// them, 56 on 192), and a workgroup takes most of its unit's LDS, so that the sort's wait
+// for a free one (171,724 bodies: 35 us a bucket sort against 24; 172 us an iteration
+// against 166).
+static bgv_status att_col_grid(int32_t K, bool beside, int32_t *G) {
     int cus = 1;
     BGV_TRY(device_cu_count(&cus));
-    *G = std::max(cus, att_col_blocks(K));
+    *G = std::max(beside ? cus * 3 / 4 : cus, att_col_blocks(K));
     return BGV_OK;
 }
 
@@ -423,7 +431,7 @@ static bgv_status attc_setup(int32_t K, int64_t nent, CsrWs &w, hipStream_t s) {
                w.nitems, w.item_beg, w.item_row, w.cstart, w.gfirst, w.gbase, w.it, w.ir, w.il,
                reinterpret_cast<EC *>(w.cwb));
     int32_t G = 1;
-    BGV_TRY(att_col_grid(K, &G));
+    BGV_TRY(att_col_grid(K, w.beside, &G));
     BGV_LAUNCH(k_attc_plan, dim3(1), dim3(64), 0, s, nblk, G, w.gfirst, w.gbase, w.wg_first);
     return BGV_OK;
 }
@@ -558,7 +566,7 @@ __global__ void __launch_bounds__(kAttLdsThreads) k_attract_lds(int32_t K, const
 }
 
 // Column-blocked attraction: the workgroups [wg_first[c], wg_first[c + 1]) of column
-// block c (one per compute unit: the block's positions take 128 KiB of LDS) stage the
+// block c (at most one per compute unit: the block's positions take 128 KiB of LDS) stage the
 // block's positions, then their wavefronts take the block's groups in turn, one item
 // per lane: the lane adds its item's entries in order, reading them from the group's
 // transposed run (coalesced) and the positions from LDS.  Every item sum, and so
@@ -613,7 +621,7 @@ __global__ void __launch_bounds__(kAttColThreads) k_attract_cols(int32_t K, int3
 
 static bgv_status attraction_cols(int32_t K, const float2 *pos, const CsrWs &csr, float2 *A, hipStream_t s) {
     int32_t G = 1;
-    BGV_TRY(att_col_grid(K, &G));
+    BGV_TRY(att_col_grid(K, csr.beside, &G));
     const int32_t nblk = att_col_blocks(K);
     const size_t lds = sizeof(float2) * (size_t)kAttCol;
     if (csr.fmt == kCsrWeighted)
@@ -748,8 +756,9 @@ static bgv_status exact_forces(int32_t K, const float2 *pos, const float *mass, 
 // ----------------------------------------------------------------- update ------
 // Bounding box (xmin, xmax, ymin, ymax) of the block's points; result in every thread.
 // min/max are order-independent, so any reduction order gives the same box.
+template <int NT = kFaThreads>
 __device__ __forceinline__ float4 block_bbox(float4 b) {
-    __shared__ float4 ws[kFaThreads / kWave];
+    __shared__ float4 ws[NT / kWave];
     __shared__ float4 res;
 #pragma unroll
     for (int o = kWave / 2; o > 0; o >>= 1) {
@@ -763,7 +772,7 @@ __device__ __forceinline__ float4 block_bbox(float4 b) {
     __syncthreads();
     if (threadIdx.x == 0) {
         float4 r = ws[0];
-        for (int q = 1; q < kFaThreads / kWave; ++q) {
+        for (int q = 1; q < NT / kWave; ++q) {
             r.x = fminf(r.x, ws[q].x);
             r.y = fmaxf(r.y, ws[q].y);
             r.z = fminf(r.z, ws[q].z);
@@ -846,11 +855,11 @@ __global__ void __launch_bounds__(kBhSpeedThreads) k_bh_speed(const double2 *__r
 
 // ... and the update blocks read the result; each writes the bounding box of the
 // positions it moved.
-// The Morton sort's digit totals, which the next encoding launch adds into, cleared by
+// The one-sweep Morton sort's digit totals (none below its sizes), which the next encoding launch adds into, cleared by
 // the launch before it (the bounding box before the first iteration, the update after
 // each one).
 __device__ __forceinline__ void bh_clear_totals(uint32_t *__restrict__ totals) {
-    if (blockIdx.x == 0)
+    if (blockIdx.x == 0 && totals)
         for (int i = threadIdx.x; i < kOsTotals; i += blockDim.x) totals[i] = 0u;
 }
 
@@ -889,14 +898,15 @@ __device__ __forceinline__ uint32_t spread16(uint32_t v) {
 
 // The bounding square of the positions (from the per-block boxes): origin and side s0.
 // Every thread of the block gets the result; block 0 stores s0.
+template <int NT = kFaThreads>
 __device__ __forceinline__ void bh_frame(const float4 *__restrict__ part, int nparts, float *xmin, float *ymin,
                                          float *s0, float *__restrict__ s0_out) {
     float4 bb = make_float4(kInf, -kInf, kInf, -kInf);
-    for (int q = threadIdx.x; q < nparts; q += kFaThreads) {
+    for (int q = threadIdx.x; q < nparts; q += NT) {
         const float4 r = part[q];
         bb = make_float4(fminf(bb.x, r.x), fmaxf(bb.y, r.y), fminf(bb.z, r.z), fmaxf(bb.w, r.w));
     }
-    bb = block_bbox(bb);
+    bb = block_bbox<NT>(bb);
     *xmin = bb.x;
     *ymin = bb.z;
     const float ex = bb.y - bb.x, ey = bb.w - bb.z;
@@ -915,18 +925,6 @@ __device__ __forceinline__ uint32_t bh_morton(float2 p, float xmin, float ymin, 
     qx = qx > 65535 ? 65535 : qx;
     qy = qy > 65535 ? 65535 : qy;
     return spread16((uint32_t)qx) | (spread16((uint32_t)qy) << 1);
-}
-
-__global__ void __launch_bounds__(kFaThreads) k_bh_codes(int32_t K, const float2 *__restrict__ pos,
-                                                          const float4 *__restrict__ part, int nparts,
-                                                          uint32_t *__restrict__ keys, uint32_t *__restrict__ vals,
-                                                          float *__restrict__ s0_out) {
-    float xmin, ymin, s0;
-    bh_frame(part, nparts, &xmin, &ymin, &s0, s0_out);
-    for (int32_t i = blockIdx.x * kFaThreads + threadIdx.x; i < K; i += gridDim.x * kFaThreads) {
-        keys[i] = bh_morton(pos[i], xmin, ymin, s0);
-        vals[i] = (uint32_t)i;
-    }
 }
 
 // The codes and the one-sweep sort's counts in one launch: workgroup t encodes the
@@ -965,6 +963,40 @@ __global__ void __launch_bounds__(kFaThreads) k_bh_codes_os(int32_t K, const flo
 #pragma unroll
     for (int q = 0; q < 4; ++q)
         if (hist[q][threadIdx.x]) atomicAdd(&totals[q * 256 + threadIdx.x], hist[q][threadIdx.x]);
+}
+
+// The bodies of a tile encoded and grouped by bucket.
+template <int NT, int ITEMS>
+__global__ void __launch_bounds__(NT) k_bh_split(int32_t K, int32_t it, const float2 *__restrict__ pos,
+                                                              const float4 *__restrict__ part, int nparts,
+                                                              const float4 *__restrict__ before, uint64_t *__restrict__ keys,
+                                                              uint16_t *__restrict__ off, float *__restrict__ s0_out) {
+    float xmin, ymin, s0;
+    bh_frame<NT>(part, nparts, &xmin, &ymin, &s0, s0_out);
+    bh_split_tile<NT, ITEMS>(K, bh_split_shape(K, it), pos, [=](float2 p) { return bh_morton(p, xmin, ymin, s0); }, before, keys,
+                         off);
+}
+
+// The group totals of the FP64 mass moments of bodies already in Morton order.
+__global__ void __launch_bounds__(kFaThreads) k_bh_moments(int32_t K, const float4 *__restrict__ body,
+                                                            double *__restrict__ part3) {
+    const int32_t k = blockIdx.x * kFaThreads + threadIdx.x;
+    double m = 0.0, mx = 0.0, my = 0.0;
+    if (k < K) {
+        const float4 bd = body[k];
+        m = (double)bd.z;
+        mx = m * (double)bd.x;
+        my = m * (double)bd.y;
+    }
+    double t0, t1, t2;
+    block_excl_scan<double>(m, &t0);
+    block_excl_scan<double>(mx, &t1);
+    block_excl_scan<double>(my, &t2);
+    if (threadIdx.x == 0) {
+        part3[3 * blockIdx.x] = t0;
+        part3[3 * blockIdx.x + 1] = t1;
+        part3[3 * blockIdx.x + 2] = t2;
+    }
 }
 
 // Bodies [256 g, 256 g + 256) in Morton order (one per thread) and the group totals of
@@ -1495,7 +1527,7 @@ static size_t fa_layout(Carver &c, int32_t K, int64_t E, const bgv_fa2_params *p
         b.kids = c.take<BhKids>((size_t)K);
         b.icount = c.take<uint32_t>((size_t)bh_force_blocks(K));
         b.redo = c.take<uint32_t>((size_t)bh_force_blocks(K) + 1);
-        b.sort_scratch = c.take<char>(onesweep_workspace(K));
+        b.sort_scratch = K > kBhSplitMax ? c.take<char>(onesweep_workspace(K)) : nullptr;
     }
     return c.size();
 }
@@ -1529,40 +1561,53 @@ static bgv_status build_attract(int32_t K, const BhWs &b, unsigned att_blocks, s
 
 // The Morton sort's digit totals in the layout's sort scratch.
 static uint32_t *bh_sort_totals(const BhWs &b, int32_t K) {
+    if (K <= kBhSplitMax) return nullptr;
     OsBuffers ob;
     onesweep_layout(b.sort_scratch, K, os_items(K), &ob);
     return ob.totals;
 }
 
 // Morton codes of the positions, sorted, the bodies gathered in Morton order and the
-// FP64 prefix sums of their mass moments: everything the node build reads.
-static bgv_status bh_sorted_bodies(int32_t K, const float2 *pos, const float *mass, BhWs &b, hipStream_t s) {
+// FP64 prefix sums of their mass moments: everything the node build reads.  it: the call's
+// iteration (b.body holds the order of the one before).
+static bgv_status bh_sorted_bodies(int32_t K, const float2 *pos, const float *mass, BhWs &b, int32_t it,
+                                   hipStream_t s) {
     const unsigned nb = (unsigned)((K + kFaThreads - 1) / kFaThreads);
     // b.bbox holds one box per update block (written by k_bh_bbox before the first
     // iteration and by k_bh_update after each one)
     const int nbox = bh_update_blocks(K);
-    // 32-bit Morton codes, sorted as 32-bit keys (the index buffers hold them)
-    uint32_t *keys = reinterpret_cast<uint32_t *>(b.keys), *keys_alt = reinterpret_cast<uint32_t *>(b.keys_alt);
-    uint32_t *sk = keys;
-    uint32_t *sv = b.vals;
-    if (K > 1) {
-        // codes and the sort's digit counts in one launch, then the one-sweep passes
+    if (K <= kBhSplitMax) {
+        const BhSplit sp = bh_split_shape(K, it);
+        const float4 *before = it > 0 ? b.body : nullptr;
+        const auto k_bh_split_small = k_bh_split<kBhTileSmall, 1>;
+        const auto k_bh_split_large = k_bh_split<kBhTileLarge / 2, 2>;
+        uint16_t *off = reinterpret_cast<uint16_t *>(b.vals);  // tiles * (buckets + 1) <= 2 K of them
+        if (K <= kBhSplitSmall)
+            BGV_LAUNCH(k_bh_split_small, dim3((unsigned)sp.tiles), dim3(kBhTileSmall), 0, s, K, it, pos, b.bbox, nbox, before,
+                       b.keys, off, b.s0);
+        else
+            BGV_LAUNCH(k_bh_split_large, dim3((unsigned)sp.tiles), dim3(kBhTileLarge / 2), 0, s, K, it, pos, b.bbox, nbox, before,
+                       b.keys, off, b.s0);
+        BGV_LAUNCH(k_bh_bucket, dim3((unsigned)sp.buckets), dim3(kBhBucketThreads), 0, s, K, it, pos, mass, b.keys, off,
+                   b.keys_alt, reinterpret_cast<uint64_t *>(b.PM), b.body, b.code);  // PM is written after this
+        BGV_LAUNCH(k_bh_moments, dim3(nb), dim3(kFaThreads), 0, s, K, b.body, b.part3);
+    } else {
+        // 32-bit Morton codes, sorted as 32-bit keys (the index buffers hold them): codes and
+        // the sort's digit counts in one launch, then the one-sweep passes
+        uint32_t *keys = reinterpret_cast<uint32_t *>(b.keys), *keys_alt = reinterpret_cast<uint32_t *>(b.keys_alt);
+        uint32_t *sk = keys;
+        uint32_t *sv = b.vals;
         OsBuffers ob;
         onesweep_layout(b.sort_scratch, K, os_items(K), &ob);
-        if (ob.items == 4)
-            BGV_LAUNCH(k_bh_codes_os<4>, dim3((unsigned)ob.tiles), dim3(kFaThreads), 0, s, K, pos, b.bbox, nbox, keys,
-                       b.vals, b.s0, ob.totals, ob.status, ob.status_words);
-        else if (ob.items == 8)
+        if (ob.items == 8)
             BGV_LAUNCH(k_bh_codes_os<8>, dim3((unsigned)ob.tiles), dim3(kFaThreads), 0, s, K, pos, b.bbox, nbox, keys,
                        b.vals, b.s0, ob.totals, ob.status, ob.status_words);
         else
             BGV_LAUNCH(k_bh_codes_os<16>, dim3((unsigned)ob.tiles), dim3(kFaThreads), 0, s, K, pos, b.bbox, nbox, keys,
                        b.vals, b.s0, ob.totals, ob.status, ob.status_words);
-        BGV_TRY(onesweep_sort_u32(keys, keys_alt, b.vals, b.vals_alt, K, &sk, &sv, b.sort_scratch, s, true));
-    } else {
-        BGV_LAUNCH(k_bh_codes, dim3(1), dim3(kFaThreads), 0, s, K, pos, b.bbox, nbox, keys, b.vals, b.s0);
+        BGV_TRY(onesweep_sort_u32(keys, keys_alt, b.vals, b.vals_alt, K, &sk, &sv, b.sort_scratch, s));
+        BGV_LAUNCH(k_bh_gather, dim3(nb), dim3(kFaThreads), 0, s, K, pos, mass, sk, sv, b.body, b.code, b.part3);
     }
-    BGV_LAUNCH(k_bh_gather, dim3(nb), dim3(kFaThreads), 0, s, K, pos, mass, sk, sv, b.body, b.code, b.part3);
     BGV_LAUNCH(k_bh_prefix, dim3(nb), dim3(kFaThreads), 0, s, K, b.body, b.part3, b.PM, b.PX, b.PY);
     return BGV_OK;
 }
@@ -1589,10 +1634,21 @@ struct FaStreams {
     hipStream_t s;
     hipStream_t side = nullptr;
     hipEvent_t fork = nullptr, join = nullptr;
+    explicit FaStreams(hipStream_t main) : s(main) {}
+    FaStreams(const FaStreams &) = delete;
+    ~FaStreams() {
+        if (fork) (void)hipEventDestroy(fork);
+        if (join) (void)hipEventDestroy(join);
+    }
+    void open(hipStream_t second) {
+        if (second && hipEventCreateWithFlags(&fork, hipEventDisableTiming) == hipSuccess &&
+            hipEventCreateWithFlags(&join, hipEventDisableTiming) == hipSuccess)
+            side = second;
+    }
 };
 
 static bgv_status bh_forces(int32_t K, const float2 *pos, const float *mass, const CsrWs &csr, float theta, float kr,
-                            float kg, const float2 *fprev, FaWs &w, const FaStreams &st) {
+                            float kg, const float2 *fprev, FaWs &w, int32_t it, const FaStreams &st) {
     hipStream_t s = st.s;
     BhWs &b = w.bh;
     const bool side = st.side && csr.cols && K > 1;
@@ -1602,7 +1658,7 @@ static bgv_status bh_forces(int32_t K, const float2 *pos, const float *mass, con
         BGV_TRY(attraction_cols(K, pos, csr, w.A, st.side));
         BGV_CHECK_HIP(hipEventRecord(st.join, st.side));
     }
-    BGV_TRY(bh_sorted_bodies(K, pos, mass, b, s));
+    BGV_TRY(bh_sorted_bodies(K, pos, mass, b, it, s));
     // the tree and the attraction (which the force kernel combines), in one launch
     if (K > 1) {
         if (csr.cols) {
@@ -1679,7 +1735,7 @@ static bgv_status fa2_iterations(int32_t K, float2 *x, float2 *fp, const float *
             BGV_TRY(attraction(K, x, w.csr, w.A, s));
             BGV_TRY(exact_forces(K, x, m, w.A, w.csr.item_of, p->kr, p->kg, fp, w.F, w.part, w.seg, s));
         } else {
-            BGV_TRY(bh_forces(K, x, m, w.csr, p->theta, p->kr, p->kg, fp, w, st));  // attraction included
+            BGV_TRY(bh_forces(K, x, m, w.csr, p->theta, p->kr, p->kg, fp, w, it, st));  // attraction included
         }
         const int32_t nparts = p->exact ? nb : bh_force_blocks(K);
         if (p->exact) {
@@ -1723,6 +1779,9 @@ bgv_status bgv::fa2_layout_run(int32_t K, int64_t E, const int32_t *edges, const
     FaWs w;
     fa_layout(c, K, E, p, &w);
     if (range_check_on()) BGV_TRY(check_edge_ids(K, E, edges, w.flag, s));
+    FaStreams st(s);
+    if (may_fork && !p->exact && w.csr.cols && K > 1 && p->iters > 0) st.open(side_stream(s));
+    w.csr.beside = st.side != nullptr;
     const float *m = nullptr;
     const bool resident = p->exact && K <= kResidentPlain;  // takes whole rows
     BGV_TRY(build_csr(K, E, edges, attr_w, mass, w.csr, s, &m, !resident));
@@ -1739,21 +1798,7 @@ bgv_status bgv::fa2_layout_run(int32_t K, int64_t E, const int32_t *edges, const
         return resident_iterations<uint16_t>(K, x, fp, m, w.csr, speed, p, s);
     }
     BGV_LAUNCH(k_copy_f32, dim3(1), dim3(1), 0, s, speed, w.speed);
-    FaStreams st;
-    st.s = s;
-    if (may_fork && !p->exact && w.csr.cols && K > 1 && p->iters > 0) {
-        st.side = side_stream(s);
-        if (st.side && (hipEventCreateWithFlags(&st.fork, hipEventDisableTiming) != hipSuccess ||
-                        hipEventCreateWithFlags(&st.join, hipEventDisableTiming) != hipSuccess)) {
-            if (st.fork) (void)hipEventDestroy(st.fork);
-            st = FaStreams{};
-            st.s = s;
-        }
-    }
-    const bgv_status rc = fa2_iterations(K, x, fp, m, p, w, nb, st);
-    if (st.fork) (void)hipEventDestroy(st.fork);
-    if (st.join) (void)hipEventDestroy(st.join);
-    BGV_TRY(rc);
+    BGV_TRY(fa2_iterations(K, x, fp, m, p, w, nb, st));
     BGV_LAUNCH(k_copy_f32, dim3(1), dim3(1), 0, s, w.speed + (p->iters & 1), speed);
     if (!p->exact && p->iters > 0 && prof_on())
         BGV_LAUNCH(k_count_total, dim3(1), dim3(kFaThreads), 0, s, w.bh.icount, bh_force_blocks(K));
@@ -1790,7 +1835,7 @@ extern "C" bgv_status bgv_bh_tree(int32_t K, const float *pos, const float *mass
     const float2 *x = reinterpret_cast<const float2 *>(pos);
     const unsigned nb = (unsigned)((K + kFaThreads - 1) / kFaThreads);
     BGV_LAUNCH(k_bh_bbox, dim3(bh_update_blocks(K)), dim3(kFaThreads), 0, s, K, x, b.bbox, bh_sort_totals(b, K));
-    BGV_TRY(bh_sorted_bodies(K, x, mass, b, s));
+    BGV_TRY(bh_sorted_bodies(K, x, mass, b, 0, s));
     if (K > 1)
         BGV_LAUNCH(k_bh_build, dim3(grid_for(K - 1, kFaThreads, 65536)), dim3(kFaThreads), 0, s, K, b.code, b.PM,
                    b.PX, b.PY, b.s0, b.body, b.node, b.kids);

@@ -29,6 +29,7 @@ struct CsrWs {
     // gbase[gi] + 64 k + l) as in-block offsets (uint16, or (offset, weight bits) when
     // weighted), in the sort keys' buffer, free once the CSR is built.
     bool cols;
+    bool beside;  // the column-blocked attraction runs beside other kernels
     uint32_t *it, *ir;
     uint16_t *il;
     uint32_t *cstart, *gfirst, *gbase;

@@ -378,35 +378,6 @@ size_t onesweep_workspace(int64_t n) {
            align_up(sizeof(uint32_t) * ((size_t)kOsPasses * tiles * 256 + kOsPasses));
 }
 
-// Digit counts of one tile's keys for all four passes, added into the totals, and,
-// spread over the grid, the clearing of the look-back words.
-template <int ITEMS>
-__global__ void __launch_bounds__(kRsThreads) k_os_count(const uint32_t *__restrict__ keys, int64_t n,
-                                                          uint32_t *__restrict__ totals,
-                                                          uint32_t *__restrict__ status, int64_t status_words) {
-    __shared__ uint32_t hist[kOsPasses][256];
-#pragma unroll
-    for (int q = 0; q < kOsPasses; ++q) hist[q][threadIdx.x] = 0u;
-    for (int64_t i = (int64_t)blockIdx.x * kRsThreads + threadIdx.x; i < status_words;
-         i += (int64_t)gridDim.x * kRsThreads)
-        status[i] = 0u;
-    __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * (kRsThreads * ITEMS);
-#pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-        const int64_t i = base + (int64_t)j * kRsThreads + threadIdx.x;
-        if (i < n) {
-            const uint32_t k = keys[i];
-#pragma unroll
-            for (int q = 0; q < kOsPasses; ++q) atomicAdd(&hist[q][(k >> (8 * q)) & 255u], 1u);
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < kOsPasses; ++q)
-        if (hist[q][threadIdx.x]) atomicAdd(&totals[q * 256 + threadIdx.x], hist[q][threadIdx.x]);
-}
-
 template <int ITEMS>
 __global__ void __launch_bounds__(kRsThreads) k_os_pass(const uint32_t *__restrict__ keys, uint32_t *__restrict__ keys_out,
                                                          const uint32_t *__restrict__ vals,
@@ -788,34 +759,19 @@ template bgv_status onesweep_sort_pairs<uint64_t>(uint64_t *, uint64_t *, uint32
                                                   const unsigned long long *, int, int, uint64_t **, uint32_t **,
                                                   void *, hipStream_t, bool);
 
-int os_items(int64_t n) { return n <= (int64_t)(1 << 16) ? 4 : n <= (int64_t)(1 << 20) ? 8 : 16; }
+int os_items(int64_t n) { return n <= (int64_t)(1 << 20) ? 8 : 16; }
 
 bgv_status onesweep_sort_u32(uint32_t *keys, uint32_t *keys_alt, uint32_t *vals, uint32_t *vals_alt, int64_t n,
-                             uint32_t **keys_out, uint32_t **vals_out, void *scratch, hipStream_t s, bool counted) {
+                             uint32_t **keys_out, uint32_t **vals_out, void *scratch, hipStream_t s) {
     OsBuffers b;
     onesweep_layout(scratch, n, os_items(n), &b);
     uint32_t *src = keys, *dst = keys_alt, *vsrc = vals, *vdst = vals_alt;
     if (n > 1) {
         const unsigned tiles = (unsigned)b.tiles;
-        if (!counted) {
-            BGV_TRY(fill<uint32_t>(b.totals, 0u, kOsTotals, s));
-            if (b.items == 4)
-                BGV_LAUNCH(k_os_count<4>, dim3(tiles), dim3(kRsThreads), 0, s, src, n, b.totals, b.status,
-                           b.status_words);
-            else if (b.items == 8)
-                BGV_LAUNCH(k_os_count<8>, dim3(tiles), dim3(kRsThreads), 0, s, src, n, b.totals, b.status,
-                           b.status_words);
-            else
-                BGV_LAUNCH(k_os_count<16>, dim3(tiles), dim3(kRsThreads), 0, s, src, n, b.totals, b.status,
-                           b.status_words);
-        }
         uint32_t *counters = b.status + (int64_t)kOsPasses * b.tiles * 256;
         for (int pass = 0; pass < kOsPasses; ++pass) {
             uint32_t *st = b.status + (int64_t)pass * b.tiles * 256;
-            if (b.items == 4)
-                BGV_LAUNCH(k_os_pass<4>, dim3(tiles), dim3(kRsThreads), 0, s, src, dst, vsrc, vdst, n, b.tiles,
-                           8 * pass, b.totals + 256 * pass, st, counters + pass);
-            else if (b.items == 8)
+            if (b.items == 8)
                 BGV_LAUNCH(k_os_pass<8>, dim3(tiles), dim3(kRsThreads), 0, s, src, dst, vsrc, vdst, n, b.tiles,
                            8 * pass, b.totals + 256 * pass, st, counters + pass);
             else

@@ -16,7 +16,7 @@
 //           stack per body)
 //   exact:  k_update        global speed from the partials (every block reduces them in
 //                           the same order), local speeds, displacement
-//   BH:     k_bh_speed      global speed from the partials (one per 8 bodies) in one block
+//   BH:     k_bh_redo_speed global speed from the partials (one per few bodies) in one block
 //           k_bh_update     local speeds, displacement, bounding-box partials
 // No floating-point atomics anywhere: results are identical run to run.
 #include <algorithm>
@@ -488,28 +488,6 @@ bgv_status build_csr(int32_t K, int64_t E, const int32_t *edges, const float *at
     return BGV_OK;
 }
 
-// --------------------------------------------------------------- reductions ------
-// Deterministic block sum of a double2 (fixed shuffle pattern, fixed wave order).
-__device__ __forceinline__ double2 block_sum2(double2 v) {
-    __shared__ double2 ws[kFaThreads / kWave];
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        v.x += __shfl_down(v.x, o, kWave);
-        v.y += __shfl_down(v.y, o, kWave);
-    }
-    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    if (lane == 0) ws[w] = v;
-    __syncthreads();
-    double2 r = make_double2(0.0, 0.0);
-    if (threadIdx.x == 0)
-        for (int q = 0; q < (int)(blockDim.x / kWave); ++q) {
-            r.x += ws[q].x;
-            r.y += ws[q].y;
-        }
-    __syncthreads();
-    return r;  // valid in thread 0
-}
-
 // Attraction: one wavefront per node; lanes stride over the CSR row and the partial
 // sums are combined by a fixed butterfly, so the result does not depend on timing.
 // Power-law supernode degrees (rows of thousands of entries next to rows of a few)
@@ -804,57 +782,6 @@ __global__ void __launch_bounds__(kFaThreads) k_update(int32_t K, float2 *__rest
 
 __global__ void k_copy_f32(const float *__restrict__ a, float *__restrict__ b) { *b = *a; }
 
-// Barnes-Hut iterations have one force partial per 8 bodies, too many for every update
-// block to reduce: one 1024-thread block reduces them (each thread its strided share in
-// ascending order, eight loads in flight; then the waves in order) ...
-constexpr int kBhSpeedThreads = 1024;
-
-// Also clears the force launch's redo count for the next iteration (adding it to a
-// running tally that the profiler can read).
-__device__ unsigned long long g_bh_redo_blocks;
-
-__global__ void __launch_bounds__(kBhSpeedThreads) k_bh_speed(const double2 *__restrict__ part, int32_t nparts,
-                                                               const float *__restrict__ speed_in,
-                                                               float *__restrict__ speed_out, float tau,
-                                                               uint32_t *__restrict__ redo) {
-    __shared__ double2 ws[kBhSpeedThreads / kWave];
-    double2 acc = make_double2(0.0, 0.0);
-    int32_t p = threadIdx.x;
-    for (; p + 7 * kBhSpeedThreads < nparts; p += 8 * kBhSpeedThreads) {
-        double2 v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = part[p + u * kBhSpeedThreads];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            acc.x += v[u].x;
-            acc.y += v[u].y;
-        }
-    }
-    for (; p < nparts; p += kBhSpeedThreads) {
-        acc.x += part[p].x;
-        acc.y += part[p].y;
-    }
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        acc.x += __shfl_down(acc.x, o, kWave);
-        acc.y += __shfl_down(acc.y, o, kWave);
-    }
-    if ((threadIdx.x & (kWave - 1)) == 0) ws[threadIdx.x / kWave] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double2 r = ws[0];
-        for (int q = 1; q < kBhSpeedThreads / kWave; ++q) {
-            r.x += ws[q].x;
-            r.y += ws[q].y;
-        }
-        *speed_out = fa2_global_speed(r.x, r.y, *speed_in, tau);
-        g_bh_redo_blocks += redo[0];
-        redo[0] = 0u;
-    }
-}
-
-// ... and the update blocks read the result; each writes the bounding box of the
-// positions it moved.
 // The one-sweep Morton sort's digit totals (none below its sizes), which the next encoding launch adds into, cleared by
 // the launch before it (the bounding box before the first iteration, the update after
 // each one).
@@ -965,12 +892,18 @@ __global__ void __launch_bounds__(kFaThreads) k_bh_codes_os(int32_t K, const flo
         if (hist[q][threadIdx.x]) atomicAdd(&totals[q * 256 + threadIdx.x], hist[q][threadIdx.x]);
 }
 
-// The bodies of a tile encoded and grouped by bucket.
+// What a block total of k_bh_prefix holds before it is there: a NaN that no sum of
+// converted floats gives.
+constexpr unsigned long long kBhUnset = ~0ull;
+
+// The bodies of a tile encoded and grouped by bucket; the words of k_bh_prefix<true> cleared.
 template <int NT, int ITEMS>
 __global__ void __launch_bounds__(NT) k_bh_split(int32_t K, int32_t it, const float2 *__restrict__ pos,
                                                               const float4 *__restrict__ part, int nparts,
                                                               const float4 *__restrict__ before, uint64_t *__restrict__ keys,
-                                                              uint16_t *__restrict__ off, float *__restrict__ s0_out) {
+                                                              uint16_t *__restrict__ off, float *__restrict__ s0_out,
+                                                              unsigned long long *__restrict__ totals, int32_t ntotals) {
+    for (int32_t i = blockIdx.x * NT + threadIdx.x; i < ntotals; i += gridDim.x * NT) totals[i] = kBhUnset;
     float xmin, ymin, s0;
     bh_frame<NT>(part, nparts, &xmin, &ymin, &s0, s0_out);
     bh_split_tile<NT, ITEMS>(K, bh_split_shape(K, it), pos, [=](float2 p) { return bh_morton(p, xmin, ymin, s0); }, before, keys,
@@ -1040,20 +973,18 @@ __global__ void __launch_bounds__(kFaThreads) k_bh_gather(int32_t K, const float
 
 // Exclusive FP64 prefix sums PM/PX/PY (K+1 entries) of the mass moments in Morton
 // order: block offset = fixed-order sum of the preceding block totals, then a block scan.
-__global__ void __launch_bounds__(kFaThreads) k_bh_prefix(int32_t K, const float4 *__restrict__ body,
-                                                           const double *__restrict__ part3,
+// With kWait the launch makes the totals itself: a block publishes its own (plane c of
+// part3 has nb words, each kBhUnset before the launch) and reads those of the blocks
+// before it once they are there, which all have started by then.  Up to kBhWaitMax bodies,
+// where each thread waits for one block at most: 17,724 bodies 7.4 us, in two launches 10.1;
+// 171,724 17.3 us, in two launches 14.1.
+constexpr int32_t kBhWaitMax = kFaThreads * kFaThreads;
+constexpr uint32_t kBhMaxSpins = 1u << 20;      // keeps a broken invariant from hanging the GPU
+
+template <bool kWait>
+__global__ void __launch_bounds__(kFaThreads) k_bh_prefix(int32_t K, const float4 *__restrict__ body, double *part3,
                                                            double *__restrict__ PM, double *__restrict__ PX,
                                                            double *__restrict__ PY) {
-    double b0 = 0.0, b1 = 0.0, b2 = 0.0;
-    for (int q = threadIdx.x; q < (int)blockIdx.x; q += kFaThreads) {
-        b0 += part3[3 * q];
-        b1 += part3[3 * q + 1];
-        b2 += part3[3 * q + 2];
-    }
-    double base0, base1, base2;
-    block_excl_scan<double>(b0, &base0);
-    block_excl_scan<double>(b1, &base1);
-    block_excl_scan<double>(b2, &base2);
     const int32_t k = blockIdx.x * kFaThreads + threadIdx.x;
     double m = 0.0, mx = 0.0, my = 0.0;
     if (k < K) {
@@ -1066,6 +997,37 @@ __global__ void __launch_bounds__(kFaThreads) k_bh_prefix(int32_t K, const float
     const double e0 = block_excl_scan<double>(m, &t0);
     const double e1 = block_excl_scan<double>(mx, &t1);
     const double e2 = block_excl_scan<double>(my, &t2);
+    double b0 = 0.0, b1 = 0.0, b2 = 0.0;
+    if (kWait) {
+        unsigned long long *w = reinterpret_cast<unsigned long long *>(part3);
+        const int32_t nb = (int32_t)gridDim.x;
+        if (threadIdx.x < 3)
+            __hip_atomic_store(&w[threadIdx.x * nb + blockIdx.x],
+                               (unsigned long long)__double_as_longlong(threadIdx.x == 0 ? t0 : threadIdx.x == 1 ? t1 : t2),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int32_t q = threadIdx.x; q < (int32_t)blockIdx.x; q += kFaThreads) {
+            unsigned long long v[3];
+            uint32_t spins = 0;
+            do {
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+                    v[c] = __hip_atomic_load(&w[c * nb + q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            } while ((v[0] == kBhUnset || v[1] == kBhUnset || v[2] == kBhUnset) && ++spins < kBhMaxSpins);
+            b0 += __longlong_as_double((long long)v[0]);
+            b1 += __longlong_as_double((long long)v[1]);
+            b2 += __longlong_as_double((long long)v[2]);
+        }
+    } else {
+        for (int q = threadIdx.x; q < (int)blockIdx.x; q += kFaThreads) {
+            b0 += part3[3 * q];
+            b1 += part3[3 * q + 1];
+            b2 += part3[3 * q + 2];
+        }
+    }
+    double base0, base1, base2;
+    block_excl_scan<double>(b0, &base0);
+    block_excl_scan<double>(b1, &base1);
+    block_excl_scan<double>(b2, &base2);
     if (k < K) {
         PM[k] = base0 + e0;
         PX[k] = base1 + e1;
@@ -1371,7 +1333,8 @@ __device__ __forceinline__ bool bh_force_block(int32_t blk, int32_t K, const flo
     }
 #pragma unroll
     for (int o = kWave / 2; o > 0; o >>= 1) ic += __shfl_xor(ic, o, kWave);
-    st = block_sum2(st);
+    st.x = fa2_wave_sum(st.x);  // the workgroup is one wavefront
+    st.y = fa2_wave_sum(st.y);
     if (threadIdx.x == 0) {
         part[blk] = st;
         icount[blk] += ic;
@@ -1383,7 +1346,7 @@ __device__ __forceinline__ bool bh_force_block(int32_t blk, int32_t K, const flo
 // depths.  The fast launch gives each body 20 entries per lane (5 KiB of LDS per
 // wavefront whatever G is), so that several times more wavefronts fit a compute unit's
 // LDS than with the full stack; a workgroup whose walk would not fit
-// appends itself to a list, and k_bh_force_full redoes it with the full stack (the same
+// appends itself to a list, and k_bh_redo_speed redoes it with the full stack (the same
 // steps, so the same bits: results never depend on the capacity).
 template <int G>
 struct BhStack {
@@ -1413,20 +1376,75 @@ __global__ void __launch_bounds__(kBhThreads) k_bh_force(int32_t K, const float4
     if (ovf && threadIdx.x == 0) redo[1 + atomicAdd(&redo[0], 1u)] = (uint32_t)blk;
 }
 
-// The listed workgroups again with the full stack; redo[0] counts them.
+// The listed workgroups again with the full stack (redo[0] counts them), and then the global
+// speed: there is one force partial per few bodies, too many for every update block to
+// reduce, so one 1024-thread workgroup reduces them (each thread its strided share in
+// ascending order, eight loads in flight; then the waves in order).  With an empty list,
+// which is the rule, that is workgroup 0 at once; else the last one to finish its share.  A
+// launch of its own for the list took 4.4 us an iteration, empty.  Clears the list for the
+// next iteration, adding its length to a running tally that the profiler can read.
+constexpr int kBhSpeedThreads = 1024;
+constexpr int kBhFullBlocks = 64;  // grid-stride over the list
+__device__ unsigned long long g_bh_redo_blocks;
+
 template <int G>
-__global__ void __launch_bounds__(kBhThreads) k_bh_force_full(int32_t K, const float4 *__restrict__ body,
-                                                               const BhKids *__restrict__ kids, float theta2,
-                                                               const float2 *__restrict__ att,
-                                                               const uint32_t *__restrict__ item_of, float kr,
-                                                               float kg, const float2 *__restrict__ fprev,
-                                                               float2 *__restrict__ F, double2 *__restrict__ part,
-                                                               uint32_t *__restrict__ icount,
-                                                               const uint32_t *__restrict__ redo) {
+__global__ void __launch_bounds__(kBhSpeedThreads) k_bh_redo_speed(
+    int32_t K, const float4 *__restrict__ body, const BhKids *__restrict__ kids, float theta2,
+    const float2 *__restrict__ att, const uint32_t *__restrict__ item_of, float kr, float kg,
+    const float2 *__restrict__ fprev, float2 *__restrict__ F, double2 *part, uint32_t *__restrict__ icount,
+    uint32_t *redo, uint32_t *done, int32_t nparts, const float *__restrict__ speed_in, float *__restrict__ speed_out,
+    float tau) {
+    __shared__ bool last;
     const uint32_t n = redo[0];
-    for (uint32_t i = blockIdx.x; i < n; i += gridDim.x)
-        bh_force_block<G, BhStack<G>::kFull>((int32_t)redo[1 + i], K, body, kids, theta2, att, item_of, kr,
-                                             kg, fprev, F, part, icount);
+    if (n == 0) {
+        if (blockIdx.x > 0) return;
+    } else {
+        if (threadIdx.x < kBhThreads) {  // one wavefront, as in the force launch
+            for (uint32_t i = blockIdx.x; i < n; i += gridDim.x)
+                bh_force_block<G, BhStack<G>::kFull>((int32_t)redo[1 + i], K, body, kids, theta2, att, item_of, kr, kg,
+                                                     fprev, F, part, icount);
+            __threadfence();
+            if (threadIdx.x == 0) last = atomicAdd(done, 1u) == gridDim.x - 1;
+        }
+        __syncthreads();
+        if (!last) return;
+        __threadfence();
+    }
+    __shared__ double2 ws[kBhSpeedThreads / kWave];
+    double2 acc = make_double2(0.0, 0.0);
+    int32_t p = threadIdx.x;
+    for (; p + 7 * kBhSpeedThreads < nparts; p += 8 * kBhSpeedThreads) {
+        double2 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = part[p + u * kBhSpeedThreads];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            acc.x += v[u].x;
+            acc.y += v[u].y;
+        }
+    }
+    for (; p < nparts; p += kBhSpeedThreads) {
+        acc.x += part[p].x;
+        acc.y += part[p].y;
+    }
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+        acc.x += __shfl_down(acc.x, o, kWave);
+        acc.y += __shfl_down(acc.y, o, kWave);
+    }
+    if ((threadIdx.x & (kWave - 1)) == 0) ws[threadIdx.x / kWave] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double2 r = ws[0];
+        for (int q = 1; q < kBhSpeedThreads / kWave; ++q) {
+            r.x += ws[q].x;
+            r.y += ws[q].y;
+        }
+        *speed_out = fa2_global_speed(r.x, r.y, *speed_in, tau);
+        g_bh_redo_blocks += n;
+        redo[0] = 0u;
+        *done = 0u;
+    }
 }
 
 static_assert(kBhThreads == kWave, "the interaction tally reduces over one wavefront per workgroup");
@@ -1464,7 +1482,6 @@ void prof_reset_counters() {
 static int32_t bh_force_blocks(int32_t K) {
     return (int32_t)(((int64_t)K * bh_lanes(K) + kBhThreads - 1) / kBhThreads);
 }
-constexpr int kBhFullBlocks = 64;  // workgroups of the full-stack redo launch (grid-stride over its list)
 
 // Blocks of the Barnes-Hut update, and so the number of bounding-box partials the next
 // tree build reduces (min/max, so any count gives the same box).
@@ -1485,6 +1502,7 @@ struct BhWs {
     BhNode *node;
     BhKids *kids;      // the children's records of each internal node (what the traversal reads)
     uint32_t *icount;  // interactions per force workgroup, summed over the call's iterations
+    uint32_t *done;    // workgroups done with their share of the list below
     uint32_t *redo;    // [0]: force workgroups to redo with the full stack, [1..]: their ids
     void *sort_scratch;
 };
@@ -1526,6 +1544,7 @@ static size_t fa_layout(Carver &c, int32_t K, int64_t E, const bgv_fa2_params *p
         b.node = c.take<BhNode>((size_t)K);
         b.kids = c.take<BhKids>((size_t)K);
         b.icount = c.take<uint32_t>((size_t)bh_force_blocks(K));
+        b.done = c.take<uint32_t>(1);
         b.redo = c.take<uint32_t>((size_t)bh_force_blocks(K) + 1);
         b.sort_scratch = K > kBhSplitMax ? c.take<char>(onesweep_workspace(K)) : nullptr;
     }
@@ -1584,12 +1603,18 @@ static bgv_status bh_sorted_bodies(int32_t K, const float2 *pos, const float *ma
         uint16_t *off = reinterpret_cast<uint16_t *>(b.vals);  // tiles * (buckets + 1) <= 2 K of them
         if (K <= kBhSplitSmall)
             BGV_LAUNCH(k_bh_split_small, dim3((unsigned)sp.tiles), dim3(kBhTileSmall), 0, s, K, it, pos, b.bbox, nbox, before,
-                       b.keys, off, b.s0);
+                       b.keys, off, b.s0, reinterpret_cast<unsigned long long *>(b.part3),
+                       K <= kBhWaitMax ? 3 * (int32_t)nb : 0);
         else
             BGV_LAUNCH(k_bh_split_large, dim3((unsigned)sp.tiles), dim3(kBhTileLarge / 2), 0, s, K, it, pos, b.bbox, nbox, before,
-                       b.keys, off, b.s0);
+                       b.keys, off, b.s0, reinterpret_cast<unsigned long long *>(b.part3),
+                       K <= kBhWaitMax ? 3 * (int32_t)nb : 0);
         BGV_LAUNCH(k_bh_bucket, dim3((unsigned)sp.buckets), dim3(kBhBucketThreads), 0, s, K, it, pos, mass, b.keys, off,
                    b.keys_alt, reinterpret_cast<uint64_t *>(b.PM), b.body, b.code);  // PM is written after this
+        if (K <= kBhWaitMax) {
+            BGV_LAUNCH(k_bh_prefix<true>, dim3(nb), dim3(kFaThreads), 0, s, K, b.body, b.part3, b.PM, b.PX, b.PY);
+            return BGV_OK;
+        }
         BGV_LAUNCH(k_bh_moments, dim3(nb), dim3(kFaThreads), 0, s, K, b.body, b.part3);
     } else {
         // 32-bit Morton codes, sorted as 32-bit keys (the index buffers hold them): codes and
@@ -1608,21 +1633,24 @@ static bgv_status bh_sorted_bodies(int32_t K, const float2 *pos, const float *ma
         BGV_TRY(onesweep_sort_u32(keys, keys_alt, b.vals, b.vals_alt, K, &sk, &sv, b.sort_scratch, s));
         BGV_LAUNCH(k_bh_gather, dim3(nb), dim3(kFaThreads), 0, s, K, pos, mass, sk, sv, b.body, b.code, b.part3);
     }
-    BGV_LAUNCH(k_bh_prefix, dim3(nb), dim3(kFaThreads), 0, s, K, b.body, b.part3, b.PM, b.PX, b.PY);
+    BGV_LAUNCH(k_bh_prefix<false>, dim3(nb), dim3(kFaThreads), 0, s, K, b.body, b.part3, b.PM, b.PX, b.PY);
     return BGV_OK;
 }
 
-// The force launch and the redo of the workgroups whose walk outgrew the fast stack.
+// The force launch, the redo of the workgroups whose walk outgrew the fast stack and the
+// global speed.
 template <int G>
-static bgv_status bh_force_launch(int32_t K, const BhWs &b, float theta, float kr, float kg, const float2 *fprev,
+static bgv_status bh_force_launch(int32_t K, const BhWs &b, const bgv_fa2_params *p, int32_t it, const float2 *fprev,
                                   const CsrWs &csr, FaWs &w, hipStream_t s) {
     const auto k_bh_force_g = k_bh_force<G>;  // one profiler name for every lane count
-    const auto k_bh_force_full_g = k_bh_force_full<G>;
-    const unsigned grid = (unsigned)((bh_force_blocks(K) + kBhXcds - 1) / kBhXcds * kBhXcds);
-    BGV_LAUNCH(k_bh_force_g, dim3(grid), dim3(kBhThreads), 0, s, K, b.body, b.kids, theta * theta, w.A,
-               csr.item_of, kr, kg, fprev, w.F, w.part, b.icount, b.redo);
-    BGV_LAUNCH(k_bh_force_full_g, dim3(kBhFullBlocks), dim3(kBhThreads), 0, s, K, b.body, b.kids, theta * theta, w.A,
-               csr.item_of, kr, kg, fprev, w.F, w.part, b.icount, b.redo);
+    const auto k_bh_redo_speed_g = k_bh_redo_speed<G>;
+    const int32_t nparts = bh_force_blocks(K);
+    const unsigned grid = (unsigned)((nparts + kBhXcds - 1) / kBhXcds * kBhXcds);
+    BGV_LAUNCH(k_bh_force_g, dim3(grid), dim3(kBhThreads), 0, s, K, b.body, b.kids, p->theta * p->theta, w.A,
+               csr.item_of, p->kr, p->kg, fprev, w.F, w.part, b.icount, b.redo);
+    BGV_LAUNCH(k_bh_redo_speed_g, dim3(kBhFullBlocks), dim3(kBhSpeedThreads), 0, s, K, b.body, b.kids,
+               p->theta * p->theta, w.A, csr.item_of, p->kr, p->kg, fprev, w.F, w.part, b.icount, b.redo, b.done, nparts,
+               w.speed + (it & 1), w.speed + ((it + 1) & 1), p->tau);
     return BGV_OK;
 }
 
@@ -1647,8 +1675,8 @@ struct FaStreams {
     }
 };
 
-static bgv_status bh_forces(int32_t K, const float2 *pos, const float *mass, const CsrWs &csr, float theta, float kr,
-                            float kg, const float2 *fprev, FaWs &w, int32_t it, const FaStreams &st) {
+static bgv_status bh_forces(int32_t K, const float2 *pos, const float *mass, const CsrWs &csr, const bgv_fa2_params *p,
+                            const float2 *fprev, FaWs &w, int32_t it, const FaStreams &st) {
     hipStream_t s = st.s;
     BhWs &b = w.bh;
     const bool side = st.side && csr.cols && K > 1;
@@ -1684,9 +1712,9 @@ static bgv_status bh_forces(int32_t K, const float2 *pos, const float *mass, con
         BGV_TRY(attraction(K, pos, csr, w.A, s));
     }
     switch (bh_lanes(K)) {
-        case 2: return bh_force_launch<2>(K, b, theta, kr, kg, fprev, csr, w, s);
-        case 4: return bh_force_launch<4>(K, b, theta, kr, kg, fprev, csr, w, s);
-        default: return bh_force_launch<8>(K, b, theta, kr, kg, fprev, csr, w, s);
+        case 2: return bh_force_launch<2>(K, b, p, it, fprev, csr, w, s);
+        case 4: return bh_force_launch<4>(K, b, p, it, fprev, csr, w, s);
+        default: return bh_force_launch<8>(K, b, p, it, fprev, csr, w, s);
     }
 }
 
@@ -1735,15 +1763,12 @@ static bgv_status fa2_iterations(int32_t K, float2 *x, float2 *fp, const float *
             BGV_TRY(attraction(K, x, w.csr, w.A, s));
             BGV_TRY(exact_forces(K, x, m, w.A, w.csr.item_of, p->kr, p->kg, fp, w.F, w.part, w.seg, s));
         } else {
-            BGV_TRY(bh_forces(K, x, m, w.csr, p->theta, p->kr, p->kg, fp, w, it, st));  // attraction included
+            BGV_TRY(bh_forces(K, x, m, w.csr, p, fp, w, it, st));  // attraction and speed included
         }
-        const int32_t nparts = p->exact ? nb : bh_force_blocks(K);
         if (p->exact) {
-            BGV_LAUNCH(k_update, dim3(nb), dim3(kFaThreads), 0, s, K, x, fp, w.F, w.part, nparts, w.speed + (it & 1),
+            BGV_LAUNCH(k_update, dim3(nb), dim3(kFaThreads), 0, s, K, x, fp, w.F, w.part, nb, w.speed + (it & 1),
                        w.speed + ((it + 1) & 1), p->tau, p->ks, p->ksmax, (float4 *)nullptr);
         } else {
-            BGV_LAUNCH(k_bh_speed, dim3(1), dim3(kBhSpeedThreads), 0, s, w.part, nparts, w.speed + (it & 1),
-                       w.speed + ((it + 1) & 1), p->tau, w.bh.redo);
             BGV_LAUNCH(k_bh_update, dim3(bh_update_blocks(K)), dim3(kFaThreads), 0, s, K, x, fp, w.F,
                        w.speed + ((it + 1) & 1), p->ks, p->ksmax, bbox, bh_sort_totals(w.bh, K));
         }
@@ -1788,6 +1813,7 @@ bgv_status bgv::fa2_layout_run(int32_t K, int64_t E, const int32_t *edges, const
     if (!p->exact) {
         BGV_TRY(fill<uint32_t>(w.bh.icount, 0u, bh_force_blocks(K), s));
         BGV_TRY(fill<uint32_t>(w.bh.redo, 0u, 1, s));
+        BGV_TRY(fill<uint32_t>(w.bh.done, 0u, 1, s));
     }
 
     float2 *x = reinterpret_cast<float2 *>(pos);

@@ -76,3 +76,18 @@ def test_one_call_equals_calls_of_one_iteration(bgv, K, ks):
     for _ in range(3):
         p, f, s = bgv.fa2_layout(e, p, 1, fprev=f, speed=s, **kw)
     assert torch.equal(one[0], p) and torch.equal(one[1], f) and float(one[2]) == float(s)
+
+
+# a node's centre is a difference of FP64 prefix sums (error below K * 50 * 2^-52 over its
+# mass) rounded to float32 (50 * 2^-24): 1e-5 holds both; masses of 1 sum exactly
+@pytest.mark.parametrize("K", [2, 255, 256, 257, 4000, 65_536, 65_537, 70_000, 262_145])
+def test_node_masses_and_centres(bgv, K):
+    p = positions(K, "clustered")
+    t = bgv.bh_tree(torch.from_numpy(p).cuda(), torch.ones(K, device="cuda"))
+    a, r = t["nodeA"].cpu().numpy(), t["nodeB"].cpu().numpy()
+    body = t["body"].cpu().numpy().astype(np.float64)
+    first, last = r[:, 2], r[:, 3]
+    assert np.array_equal(a[:, 2], (last - first + 1).astype(np.float32))
+    for c in (0, 1):
+        s = np.concatenate([[0.0], np.cumsum(body[:, c])])
+        np.testing.assert_allclose(a[:, c], (s[last + 1] - s[first]) / (last - first + 1), rtol=0, atol=1e-5)

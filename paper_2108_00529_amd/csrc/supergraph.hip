@@ -5,6 +5,8 @@
 //   4. LSD radix sort of the keys, unique -> superedges; sketch 2 gets each distinct
 //      pair's multiplicity at g_r(min label, max label); weights = min over rows of
 //      sketch 2; supernode sizes = min over rows of sketch 1
+#include <cmath>
+
 #include "block_scan.h"
 #include "common.h"
 #include "sketch_hash.h"
@@ -366,7 +368,40 @@ __global__ void k_sg_sketch_pairs(const int32_t *__restrict__ superedges, const 
     }
 }
 
-// Sketch 2 without global atomics, for sketches of at most kSkMaxCells cells, in buckets
+// The same with the whole sketch privatised in LDS (rows * cols <= kLdsCounters): device
+// atomics only for a workgroup's sums.  sg_pairs_grid balances those (workgroups * cells at
+// about 25 per ns) with the LDS adds of a workgroup's pairs (about 4 per ns), supposing a
+// quarter of the edges to be distinct pairs.  10M edges, 2.2M pairs, 4 x 4,096 cells:
+// 43 us, by k_sg_sketch_pairs 304.
+constexpr int kSkLdsThreads = 1024;
+inline unsigned sg_pairs_grid(int64_t m, int32_t rows, int64_t cells) {
+    const double g = std::sqrt(6.5 * 0.25 * (double)m * rows / (double)cells);
+    return g < 1.0 ? 1u : g > 256.0 ? 256u : (unsigned)g;
+}
+__global__ void __launch_bounds__(kSkLdsThreads) k_sg_sketch_pairs_lds(
+    const int32_t *__restrict__ superedges, const uint32_t *__restrict__ run_start, const uint32_t *__restrict__ Ep,
+    const unsigned long long *__restrict__ nkp, const int32_t *__restrict__ super_label, HashRows h, int32_t rows,
+    uint32_t cols, uint32_t *__restrict__ M2, uint32_t *__restrict__ se_count) {
+    __shared__ uint32_t loc[kLdsCounters];
+    const int32_t cells = rows * (int32_t)cols;
+    for (int32_t c = threadIdx.x; c < cells; c += kSkLdsThreads) loc[c] = 0u;
+    __syncthreads();
+    const int64_t E = *Ep;
+    const uint32_t nk = (uint32_t)*nkp;
+    for (int64_t j = blockIdx.x * (int64_t)kSkLdsThreads + threadIdx.x; j < E; j += (int64_t)gridDim.x * kSkLdsThreads) {
+        const uint32_t cnt = (j + 1 < E ? run_start[j + 1] : nk) - run_start[j];
+        const uint32_t la = (uint32_t)super_label[superedges[2 * j]];
+        const uint32_t lb = (uint32_t)super_label[superedges[2 * j + 1]];
+        for (int r = 0; r < rows; ++r)
+            atomicAdd(&loc[(uint32_t)r * cols + col_pair(h.a[r], h.b[r], h.c[r], la, lb, cols)], cnt);
+        if (se_count) se_count[j] = cnt;
+    }
+    __syncthreads();
+    for (int32_t c = threadIdx.x; c < cells; c += kSkLdsThreads)
+        if (loc[c]) atomicAdd(&M2[c], loc[c]);
+}
+
+// Sketch 2 without global atomics, for larger sketches (sk_grouped), in buckets
 // of 2^kB consecutive cells (cell = row * cols + column).  Each tile of distinct pairs
 // (4,096 of them, 2,048 with more than five rows) writes one 4-byte entry per (pair,
 // row) grouped by bucket, one segment per (tile, bucket), offsets in a per-tile table
@@ -387,6 +422,19 @@ inline int32_t sk_tile_pairs(int32_t rows) { return rows <= 5 ? 4096 : 2048; }
 constexpr int kSkCodeBits = 5;
 constexpr uint32_t kSkEscape = (1u << kSkCodeBits) - 1;
 constexpr int kSkResolveThreads = 1024;
+
+// Which form sketch 2 takes.  The grouped one has a workgroup per bucket, so it needs a
+// sketch of some buckets to fill the chip, and a stream long enough for its launches and
+// passes over the entries; elsewhere one device atomic per (pair, row), about 25 per ns on
+// different addresses, is the quicker (whole call, 2M edges, 5 rows: 10 buckets 455 us, by
+// atomics 397; 20 buckets 402 and 402; 40 buckets 384 and 396; 10M edges: 1,147 and 1,051,
+// 924 and 1,067.  40 buckets, 200,000 edges: 255 and 245; 320 buckets, 2M edges: 348 and
+// 415).  A sketch that fits LDS takes the adds there (k_sg_sketch_pairs_lds).
+constexpr int64_t kSkMinCells = 1 << 18;
+constexpr int64_t kSkMinAdds = 1 << 22;
+inline bool sk_grouped(int64_t m, int32_t rows, int64_t cells) {
+    return cells >= kSkMinCells && cells <= kSkMaxCells && m * rows >= kSkMinAdds;
+}
 
 inline int64_t sk_buckets(int64_t cells, int bits) { return (cells + (1ll << bits) - 1) >> bits; }
 
@@ -639,7 +687,7 @@ static size_t sg_layout(Carver &c, int32_t n, int64_t m, int32_t rows, int64_t c
         w->ltab = c.take<uint32_t>(tiles * (size_t)(lb_buckets(n) + 1));
     }
     const int64_t nb = sk_buckets(cells, 14);  // the larger of the two bucket counts
-    if (cells <= kSkMaxCells) {
+    if (sk_grouped(m, rows, cells)) {
         // distinct pairs <= m: a tile bound, rows entries per pair
         const size_t tp = (size_t)sk_tile_pairs(rows);
         const size_t tiles = ((size_t)mm + tp - 1) / tp;
@@ -867,8 +915,12 @@ extern "C" bgv_status bgv_supergraph(int32_t n, int64_t m, const int32_t *edges,
                 BGV_TRY(sg_sketch2_grouped<14>(m, w, superedges, nkeys_d, super_label, h2, rows, cols, cells, se_count,
                                                M2, se_weight, s));
         } else {
-            BGV_LAUNCH(k_sg_sketch_pairs, dim3(gk), dim3(kSgThreads), 0, s, superedges, w.run_start, &w.counters[1],
-                       nkeys_d, super_label, h2, rows, cols, M2, se_count);
+            if (lds_sketch)
+                BGV_LAUNCH(k_sg_sketch_pairs_lds, dim3(sg_pairs_grid(m, rows, cells)), dim3(kSkLdsThreads), 0, s,
+                           superedges, w.run_start, &w.counters[1], nkeys_d, super_label, h2, rows, cols, M2, se_count);
+            else
+                BGV_LAUNCH(k_sg_sketch_pairs, dim3(gk), dim3(kSgThreads), 0, s, superedges, w.run_start,
+                           &w.counters[1], nkeys_d, super_label, h2, rows, cols, M2, se_count);
             BGV_LAUNCH(k_sg_pair_weights, dim3(gk), dim3(kSgThreads), 0, s, superedges, &w.counters[1], super_label,
                        h2, rows, cols, M2, se_weight);
         }

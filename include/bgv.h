@@ -94,8 +94,8 @@ const char *bgv_last_error(void);
  * tile of a chunk, 32 KiB plus two offset rows as for the degree rule; above 2^24 nodes,
  * or above 2^20 nodes with chunks of fewer than n / 8192 edges, 24 bytes per node and 4
  * per edge of a chunk.  Method 0 picks 2 when it applies and the chunk-by-chunk form would
- * take more than 16 + passes * m / 2^17 chunk steps, else 1.  Other values are
- * BGV_E_INVALID.
+ * take more than min(16 + passes * m / 2^17, 10 + (passes + 2) * m / 2^18) chunk steps,
+ * else 1.  Other values are BGV_E_INVALID.
  */
 typedef struct {
     int32_t threshold; /* D1 >= 0: threshold of the first pass                   */

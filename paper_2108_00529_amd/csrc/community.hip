@@ -520,15 +520,16 @@ static bool cd_valid(int32_t n, int64_t m, const bgv_cd_params *p) {
     return p->method != 2 || m == 0 || sq_fits(n, m, p);
 }
 
-// 1: chunk by chunk; 2: back-pointer resolution.  Automatic: measured on a 10M-edge
-// stream, a chunk step costs about 12 us and back-pointer resolution about 150 us plus
-// 0.09 ns more per (pass, edge) than the chunk steps' streaming, so the second wins past
-// about 16 + passes * m / 2^17 chunk steps (245 at 3 x 10M edges, 16 on small graphs).
+// 1: chunk by chunk; 2: back-pointer resolution.  Automatic: a chunk step costs 9 - 16 us, so
+// the second wins past some number of steps, measured at 16,000 / 160,000 / 800,000 / 2.4M /
+// 8M / 24M edges: one pass 8 / 8 / 17 / 35 / 82 / 208 steps, two 8 / 9 / 19 / 44 / 96 / 272,
+// four 10 / 12 / 28 / 65 / 124 / 396.
 static int cd_method(int32_t n, int64_t m, const bgv_cd_params *p) {
     if (m == 0 || p->rule == 1) return 1;
     if (p->method != 0) return p->method;
     const int64_t steps = (int64_t)p->passes * ((m + p->chunk - 1) / p->chunk);
-    return steps > 16 + ((int64_t)p->passes * m >> 17) && sq_fits(n, m, p) ? 2 : 1;
+    const int64_t line = std::min(16 + ((int64_t)p->passes * m >> 17), 10 + (((int64_t)p->passes + 2) * m >> 18));
+    return steps > line && sq_fits(n, m, p) ? 2 : 1;
 }
 
 struct CdWs {

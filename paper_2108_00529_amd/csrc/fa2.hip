@@ -1059,13 +1059,13 @@ struct __align__(32) BhNode {
 
 // What a traversal step needs about the two children of an opened node, so that the
 // step that pops the node decides both children without loading their own records:
-// per child its (centre of mass, mass, size^2) — a body's (x, y, m, unused) —, its
-// body range and its index (>= 0 internal node, < 0 leaf ~body).  64 bytes: one line.
-struct __align__(64) BhKids {
+// per child its (centre of mass, mass, size^2) - a body's (x, y, m, unused) -, and the
+// node's first body, its left child's last one and its own last one.  The left child is
+// the body, or else the internal node, of number split, the right one that of split + 1.
+// Three loads of 16 bytes: with ranges and indices written out it was four.
+struct __align__(16) BhKids {
     float4 a[2];
-    int4 range;  // first and last body of the left child, then of the right one
-    int2 idx;    // left, right
-    int2 pad;
+    int32_t first, split, last, pad;
 };
 
 // (centre of mass, mass, size^2) of the internal node over bodies [first, last]
@@ -1140,9 +1140,10 @@ __device__ __forceinline__ void bh_build_nodes(int32_t K, const uint32_t *__rest
         BhKids kd;
         kd.a[0] = left < 0 ? body[first] : bh_range_data(K, code, PM, PX, PY, s0, first, gamma);
         kd.a[1] = right < 0 ? body[last] : bh_range_data(K, code, PM, PX, PY, s0, gamma + 1, last);
-        kd.range = make_int4(first, gamma, gamma + 1, last);
-        kd.idx = make_int2(left, right);
-        kd.pad = make_int2(0, 0);
+        kd.first = first;
+        kd.split = gamma;
+        kd.last = last;
+        kd.pad = 0;
         kids[i] = kd;
     }
 }
@@ -1218,6 +1219,9 @@ static int bh_lanes(int32_t K) { return K >= 131072 ? 2 : K >= 65536 ? 4 : 8; }
 // node's prefix is longer than its parent's, so the tree has at most 34 levels (root,
 // 32 prefix lengths, bodies) and the stack never exceeds that.  The order of the
 // additions depends only on G and the tree: results are identical run to run.
+// Bound by the latency of a step's chain (stack, record, decision, stack) with 8 lanes per
+// body and by the records' bytes with 2: 17,724 bodies 15.7 us a launch, 171,724 45.6.  With
+// a branch per kind of child, a shuffle scan and 64-byte records: 21.3 and 57.5.
 constexpr int kBhTreeLevels = 34;  // 32-bit Morton codes: root, 32 prefix lengths, equal-code cells
 
 // One force workgroup's bodies (block `blk`) with a stack of C entries per body.  A step
@@ -1237,6 +1241,9 @@ __device__ __forceinline__ bool bh_force_block(int32_t blk, int32_t K, const flo
     const int32_t r = (int32_t)(tid / G);
     const int L = (int)(tid % G);
     int *st_g = stk[threadIdx.x / G];
+    static_assert(G <= 32, "a body's lanes in half a ballot");
+    constexpr uint32_t kLanes = G == 32 ? ~0u : (1u << (G % 32)) - 1u;
+    const int first = (int)(threadIdx.x & (kWave - 1)) - L;  // the body's first lane
     double2 st = make_double2(0.0, 0.0);
     float fx = 0.f, fy = 0.f;
     uint32_t ic = 0;
@@ -1256,65 +1263,49 @@ __device__ __forceinline__ bool bh_force_block(int32_t blk, int32_t K, const flo
         size -= take;
         int c_left = 0, c_right = 0, np = 0;
         if (has) {
-            // an opened node: decide both children from its children's record
+            // an opened node: decide both children from its children's record, without
+            // branches but for cells of equal codes (a wavefront's lanes meet every kind of
+            // child in most steps, and a branch per kind costs more than its arithmetic)
             const BhKids kd = kids[e];
-            bool open[2] = {false, false};
+            bool open[2];
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
                 const float4 A = kd.a[q];
-                const int c = q ? kd.idx.y : kd.idx.x;
-                const int f = q ? kd.range.z : kd.range.x, l = q ? kd.range.w : kd.range.y;
-                if (c < 0) {
-                    if (~c != r) add_pair(xi, A, fx, fy, ic);  // a body
-                } else if (A.w < 0.f) {  // a cell of equal codes: direct sum
+                const int f = q ? kd.split + 1 : kd.first, l = q ? kd.last : kd.split;
+                const float dx = xi.x - A.x, dy = xi.y - A.y;
+                const float d2 = fa2_norm2(dx, dy);
+                const bool leaf = f == l, apart = d2 > 0.f, out = (r < f) | (r > l);
+                const bool cell = !leaf & (A.w < 0.f);  // of equal codes: summed directly
+                const bool far = !leaf & !cell & out & apart & (A.w < theta2 * d2);
+                const bool add = far | (leaf & out);
+                const float fr = apart ? A.z * __builtin_amdgcn_rcpf(d2) : 0.f;
+                const float gx = __builtin_fmaf(fr, dx, fx), gy = __builtin_fmaf(fr, dy, fy);
+                fx = add ? gx : fx;
+                fy = add ? gy : fy;
+                ic += add ? 1u : 0u;
+                if (cell)
                     for (int k = f; k <= l; ++k)
                         if (k != r) add_pair(xi, body[k], fx, fy, ic);
-                } else {
-                    bool o = r >= f && r <= l;
-                    if (!o) {
-                        const float dx = xi.x - A.x, dy = xi.y - A.y;
-                        const float d2 = fa2_norm2(dx, dy);
-                        if (d2 > 0.f && A.w < theta2 * d2) {
-                            const float fr = A.z * __builtin_amdgcn_rcpf(d2);
-                            fx += fr * dx;
-                            fy += fr * dy;
-                            ++ic;
-                        } else {
-                            o = true;
-                        }
-                    }
-                    open[q] = o;
-                }
+                open[q] = !(leaf | cell | far);
             }
-            if (open[0] && open[1]) {
-                c_left = kd.idx.x;
-                c_right = kd.idx.y;
-                np = 2;
-            } else if (open[0] || open[1]) {
-                c_left = open[0] ? kd.idx.x : kd.idx.y;
-                np = 1;
-            }
+            np = (open[0] ? 1 : 0) + (open[1] ? 1 : 0);
+            c_left = open[0] ? kd.split : kd.split + 1;
+            c_right = kd.split + 1;
         }
-        // inclusive scan of the pushes from the highest lane down, so lane 0 (the
-        // deepest popped entry) writes last, on top
-        int incl = np;
-#pragma unroll
-        for (int o = 1; o < G; o <<= 1) {
-            const int v = __shfl_down(incl, o, G);
-            if (L + o < G) incl += v;
-        }
-        const int total = __shfl(incl, 0, G);
+        // pushes of this lane and the higher ones, so lane 0 (the deepest popped entry)
+        // writes last, on top: counted in the ballots of "one or two" and "two" (a scan by
+        // lane shuffles is a chain of log2 G + 1 trips through LDS)
+        const uint64_t one = __ballot(np > 0) >> first, two = __ballot(np == 2) >> first;
+        const uint32_t b1 = (uint32_t)one & kLanes, b2 = (uint32_t)two & kLanes;
+        const int incl = __popc(b1 >> L) + __popc(b2 >> L);
+        const int total = __popc(b1) + __popc(b2);
         if (size + total > C) {  // uniform over the body's lanes
             overflow = true;
             size = 0;
         } else {
-            if (np == 2) {
-                const int at = size + incl - np;  // this lane's two slots: at, at + 1
-                st_g[at] = c_right;
-                st_g[at + 1] = c_left;  // left on top: popped first
-            } else if (np == 1) {
-                st_g[size + incl - 1] = c_left;
-            }
+            // this lane's slots: the left child on top, popped first
+            if (np > 0) st_g[size + incl - 1] = c_left;
+            if (np == 2) st_g[size + incl - 2] = c_right;
             size += total;
         }
     }

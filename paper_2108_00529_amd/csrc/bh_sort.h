@@ -31,7 +31,8 @@ constexpr int32_t kBhSettled = 16;
 constexpr int32_t kBhFewMax = 184320;
 constexpr int kBhBucketThreads = 512;
 constexpr int32_t kBhTilesMax = 256;    // at most a thread of a bucket's workgroup per tile
-constexpr int32_t kBhBucketLds = 2048;  // bodies of a bucket sorted in LDS; more: in memory
+constexpr int32_t kBhBucketLds = 1536;  // bodies of a bucket sorted in LDS; more: in memory
+                                        // (two workgroups beside one of the attraction's)
 constexpr int32_t kBhTileSmall = 256, kBhTileLarge = 1024;
 constexpr int32_t kBhSplitSmall = kBhTilesMax * kBhTileSmall;
 // Above this the radix sort (262,144 bodies, 100 iterations: 21.3 ms, with it 22.6).

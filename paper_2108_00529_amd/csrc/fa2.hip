@@ -529,6 +529,20 @@ __global__ void __launch_bounds__(kFaThreads) k_attract(int32_t K, const float2 
 constexpr int32_t kAttLdsMin = 4096;  // up to kAttLdsMax: dynamic LDS of K * 8 bytes
 constexpr int kAttLdsThreads = 1024;
 
+// src[0, n) into LDS by NT threads, eight loads of each thread in flight.
+template <int NT, typename T>
+__device__ __forceinline__ void stage_lds(T *__restrict__ dst, const T *__restrict__ src, int32_t n) {
+    for (int32_t x = threadIdx.x; x < n; x += 8 * NT) {
+        T v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (x + u * NT < n) v[u] = src[x + u * NT];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (x + u * NT < n) dst[x + u * NT] = v[u];
+    }
+}
+
 template <typename E>
 __global__ void __launch_bounds__(kAttLdsThreads) k_attract_lds(int32_t K, const float2 *__restrict__ pos,
                                                                  const uint32_t *__restrict__ row,
@@ -537,7 +551,7 @@ __global__ void __launch_bounds__(kAttLdsThreads) k_attract_lds(int32_t K, const
                                                                  const uint32_t *__restrict__ item_row,
                                                                  float2 *__restrict__ A) {
     extern __shared__ float2 sp[];  // K entries
-    for (int32_t i = threadIdx.x; i < K; i += kAttLdsThreads) sp[i] = pos[i];
+    stage_lds<kAttLdsThreads>(sp, pos, K);
     __syncthreads();
     att_items(K, sp, row, cw, item_of, item_row, A, (blockIdx.x * (int64_t)kAttLdsThreads + threadIdx.x) / kWave,
               (int64_t)gridDim.x * (kAttLdsThreads / kWave));
@@ -566,7 +580,7 @@ __global__ void __launch_bounds__(kAttColThreads) k_attract_cols(int32_t K, int3
     const uint32_t g = x - wg_first[c], wpb = wg_first[c + 1] - wg_first[c];
     const int32_t base = c << kAttColBits;
     const int32_t nb = min(kAttCol, K - base);
-    for (int32_t i = threadIdx.x; i < nb; i += kAttColThreads) sp[i] = pos[base + i];
+    stage_lds<kAttColThreads>(sp, pos + base, nb);
     __syncthreads();
     constexpr uint32_t kWaves = kAttColThreads / kWave;
     const uint32_t lane = threadIdx.x % kWave;
@@ -1040,10 +1054,21 @@ __global__ void __launch_bounds__(kFaThreads) k_bh_prefix(int32_t K, const float
     }
 }
 
+// Sorted codes, those of positions [lo, lo + n) also in LDS: a node's search takes codes one
+// after the other, mostly of its neighbours.
+struct BhCodes {
+    const uint32_t *code, *win;
+    int32_t lo, n;
+    __device__ __forceinline__ uint32_t operator[](int32_t i) const {
+        const uint32_t d = (uint32_t)(i - lo);
+        return d < (uint32_t)n ? win[d] : code[i];
+    }
+};
+
 // Common-prefix length of sorted positions i and j; index bits break ties between
 // equal codes (values >= 32 mean equal codes); -1 when j is outside [0, K) (only j is
 // checked: i must be a valid position).
-__device__ __forceinline__ int delta(const uint32_t *__restrict__ code, int32_t K, int32_t i, int32_t j) {
+__device__ __forceinline__ int delta(const BhCodes &code, int32_t K, int32_t i, int32_t j) {
     if (j < 0 || j >= K) return -1;
     const uint32_t a = code[i], b = code[j];
     if (a != b) return __clz(a ^ b);
@@ -1081,7 +1106,7 @@ struct __align__(16) BhKids {
 // cell with its own side, so the opening decisions are those of the quadtree.  The
 // parent of the node over [first, last] has the longer of the prefixes shared across
 // the range's two ends (Karras' tree: the parent extends the range on that side).
-__device__ __forceinline__ float4 bh_range_data(int32_t K, const uint32_t *__restrict__ code,
+__device__ __forceinline__ float4 bh_range_data(int32_t K, const BhCodes &code,
                                                 const double *__restrict__ PM, const double *__restrict__ PX,
                                                 const double *__restrict__ PY, float s0, int first, int last) {
     const int dnode = delta(code, K, first, last);
@@ -1105,62 +1130,86 @@ __device__ __forceinline__ float4 bh_range_data(int32_t K, const uint32_t *__res
 // construction): the record of its two children that the traversal reads and, when
 // `node` is given (the tree export), its own record (children >= 0 internal node, < 0
 // leaf ~child).
+__device__ __forceinline__ void bh_build_node(int32_t K, const BhCodes &code, const double *__restrict__ PM,
+                                              const double *__restrict__ PX, const double *__restrict__ PY, float s0,
+                                              const float4 *__restrict__ body, BhNode *__restrict__ node,
+                                              BhKids *__restrict__ kids, int32_t i) {
+    const int d = (delta(code, K, i, i + 1) - delta(code, K, i, i - 1)) >= 0 ? 1 : -1;
+    const int dmin = delta(code, K, i, i - d);
+    int lmax = 2;
+    while (delta(code, K, i, i + lmax * d) > dmin) lmax <<= 1;
+    int l = 0;
+    for (int t = lmax >> 1; t >= 1; t >>= 1)
+        if (delta(code, K, i, i + (l + t) * d) > dmin) l += t;
+    const int j = i + l * d;
+    const int dnode = delta(code, K, i, j);
+    int sgap = 0;
+    int t = l;
+    do {
+        t = (t + 1) >> 1;
+        if (delta(code, K, i, i + (sgap + t) * d) > dnode) sgap += t;
+    } while (t > 1);
+    const int gamma = i + sgap * d + (d < 0 ? -1 : 0);
+    const int first = min(i, j), last = max(i, j);
+    const int left = (first == gamma) ? ~gamma : gamma;
+    const int right = (last == gamma + 1) ? ~(gamma + 1) : gamma + 1;
+    if (node) {  // the tree export only: the traversal reads the children records
+        BhNode nd;
+        nd.a = bh_range_data(K, code, PM, PX, PY, s0, first, last);
+        nd.b = make_int4(left, right, first, last);
+        node[i] = nd;
+    }
+    BhKids kd;
+    kd.a[0] = left < 0 ? body[first] : bh_range_data(K, code, PM, PX, PY, s0, first, gamma);
+    kd.a[1] = right < 0 ? body[last] : bh_range_data(K, code, PM, PX, PY, s0, gamma + 1, last);
+    kd.first = first;
+    kd.split = gamma;
+    kd.last = last;
+    kd.pad = 0;
+    kids[i] = kd;
+}
+
+// The nodes of blocks of NT consecutive ones, the codes around each block in LDS (win:
+// room for cap >= NT of them).  171,724 bodies: 17.0 us, reading every code from memory 19.7.
+template <int NT>
 __device__ __forceinline__ void bh_build_nodes(int32_t K, const uint32_t *__restrict__ code,
                                                const double *__restrict__ PM, const double *__restrict__ PX,
                                                const double *__restrict__ PY, const float *__restrict__ s0p,
                                                const float4 *__restrict__ body, BhNode *__restrict__ node,
-                                               BhKids *__restrict__ kids, int32_t i0, int32_t stride) {
+                                               BhKids *__restrict__ kids, uint32_t *win, int32_t cap, int32_t block,
+                                               int32_t blocks) {
     const float s0 = *s0p;
-    for (int32_t i = i0; i < K - 1; i += stride) {
-        const int d = (delta(code, K, i, i + 1) - delta(code, K, i, i - 1)) >= 0 ? 1 : -1;
-        const int dmin = delta(code, K, i, i - d);
-        int lmax = 2;
-        while (delta(code, K, i, i + lmax * d) > dmin) lmax <<= 1;
-        int l = 0;
-        for (int t = lmax >> 1; t >= 1; t >>= 1)
-            if (delta(code, K, i, i + (l + t) * d) > dmin) l += t;
-        const int j = i + l * d;
-        const int dnode = delta(code, K, i, j);
-        int sgap = 0;
-        int t = l;
-        do {
-            t = (t + 1) >> 1;
-            if (delta(code, K, i, i + (sgap + t) * d) > dnode) sgap += t;
-        } while (t > 1);
-        const int gamma = i + sgap * d + (d < 0 ? -1 : 0);
-        const int first = min(i, j), last = max(i, j);
-        const int left = (first == gamma) ? ~gamma : gamma;
-        const int right = (last == gamma + 1) ? ~(gamma + 1) : gamma + 1;
-        if (node) {  // the tree export only: the traversal reads the children records
-            BhNode nd;
-            nd.a = bh_range_data(K, code, PM, PX, PY, s0, first, last);
-            nd.b = make_int4(left, right, first, last);
-            node[i] = nd;
-        }
-        BhKids kd;
-        kd.a[0] = left < 0 ? body[first] : bh_range_data(K, code, PM, PX, PY, s0, first, gamma);
-        kd.a[1] = right < 0 ? body[last] : bh_range_data(K, code, PM, PX, PY, s0, gamma + 1, last);
-        kd.first = first;
-        kd.split = gamma;
-        kd.last = last;
-        kd.pad = 0;
-        kids[i] = kd;
+    for (int64_t base = (int64_t)block * NT; base < K - 1; base += (int64_t)blocks * NT) {
+        const int64_t first = min(base - (cap - NT) / 2, (int64_t)K - cap);
+        const int32_t lo = (int32_t)max((int64_t)0, first), n = min(cap, K - lo);
+        stage_lds<NT>(win, code + lo, n);
+        __syncthreads();
+        const int64_t i = base + threadIdx.x;
+        if (i < K - 1) bh_build_node(K, BhCodes{code, win, lo, n}, PM, PX, PY, s0, body, node, kids, (int32_t)i);
+        __syncthreads();
     }
 }
 
-__global__ void k_bh_build(int32_t K, const uint32_t *__restrict__ code, const double *__restrict__ PM,
-                           const double *__restrict__ PX, const double *__restrict__ PY,
-                           const float *__restrict__ s0p, const float4 *__restrict__ body,
-                           BhNode *__restrict__ node, BhKids *__restrict__ kids) {
-    bh_build_nodes(K, code, PM, PX, PY, s0p, body, node, kids, blockIdx.x * blockDim.x + threadIdx.x,
-                   gridDim.x * blockDim.x);
+constexpr int32_t kBhWindow = 2048;
+
+__global__ void __launch_bounds__(kFaThreads) k_bh_build(int32_t K, const uint32_t *__restrict__ code,
+                                                          const double *__restrict__ PM,
+                                                          const double *__restrict__ PX,
+                                                          const double *__restrict__ PY,
+                                                          const float *__restrict__ s0p,
+                                                          const float4 *__restrict__ body, BhNode *__restrict__ node,
+                                                          BhKids *__restrict__ kids) {
+    __shared__ uint32_t win[kBhWindow];
+    bh_build_nodes<kFaThreads>(K, code, PM, PX, PY, s0p, body, node, kids, win, kBhWindow, blockIdx.x, gridDim.x);
 }
 
 // The tree build and the attraction in one launch: workgroups [0, build_blocks) build
 // the tree (a few dozen for a supergraph of some ten thousand bodies), the others take
 // the attraction items, which do not depend on the tree, so the two latency-bound jobs
 // overlap instead of following each other.  With kLds the attraction workgroups stage
-// the positions in (dynamic) LDS first, as k_attract_lds does.
+// the positions in (dynamic) LDS first, as k_attract_lds does.  17,724 bodies: 15.3 us, of
+// which the attraction alone takes 10 and the tree alone 15 (the vector issue of 18 workgroups'
+// searches and FP64 divisions; spread over every workgroup's first wavefronts it was 16).
 template <typename E, int NT, bool kLds>
 __global__ void __launch_bounds__(NT) k_bh_build_attract(int32_t K, const uint32_t *__restrict__ code,
                                                           const double *__restrict__ PM,
@@ -1174,16 +1223,21 @@ __global__ void __launch_bounds__(NT) k_bh_build_attract(int32_t K, const uint32
                                                           const uint32_t *__restrict__ item_of,
                                                           const uint32_t *__restrict__ item_row,
                                                           float2 *__restrict__ A) {
+    extern __shared__ float2 sp[];  // kLds: K entries
     if ((int32_t)blockIdx.x < build_blocks) {  // uniform over the workgroup
-        bh_build_nodes(K, code, PM, PX, PY, s0p, body, node, kids, blockIdx.x * NT + threadIdx.x,
-                       build_blocks * NT);
+        if (kLds) {
+            bh_build_nodes<NT>(K, code, PM, PX, PY, s0p, body, node, kids, reinterpret_cast<uint32_t *>(sp),
+                               min(K, 8 * NT), blockIdx.x, build_blocks);
+        } else {
+            __shared__ uint32_t win[kBhWindow];
+            bh_build_nodes<NT>(K, code, PM, PX, PY, s0p, body, node, kids, win, kBhWindow, blockIdx.x, build_blocks);
+        }
         return;
     }
     const int64_t wave0 = ((int64_t)(blockIdx.x - build_blocks) * NT + threadIdx.x) / kWave;
     const int64_t nwaves = (int64_t)(gridDim.x - build_blocks) * (NT / kWave);
     if (kLds) {
-        extern __shared__ float2 sp[];  // K entries
-        for (int32_t i = threadIdx.x; i < K; i += NT) sp[i] = pos[i];
+        stage_lds<NT>(sp, pos, K);
         __syncthreads();
         att_items(K, sp, row, cw, item_of, item_row, A, wave0, nwaves);
     } else {
@@ -1693,7 +1747,9 @@ static bgv_status bh_forces(int32_t K, const float2 *pos, const float *mass, con
             int cus = 1;
             BGV_TRY(device_cu_count(&cus));
             const unsigned wg = (unsigned)((csr.items_bound + kAttLdsThreads / kWave - 1) / (kAttLdsThreads / kWave));
-            BGV_TRY((build_attract<kAttLdsThreads, true>(K, b, wg < (unsigned)cus ? (wg > 0 ? wg : 1u) : (unsigned)cus,
+            // a workgroup of this launch takes most of a compute unit's LDS: one per unit
+            const unsigned most = (unsigned)std::max(1, cus - (K - 1 + kAttLdsThreads - 1) / kAttLdsThreads);
+            BGV_TRY((build_attract<kAttLdsThreads, true>(K, b, std::min(std::max(wg, 1u), most),
                                                          sizeof(float2) * (size_t)K, pos, csr, w.A, s)));
         } else {
             BGV_TRY((build_attract<kFaThreads, false>(K, b, grid_for(csr.items_bound, kFaThreads / kWave, 16384), 0,

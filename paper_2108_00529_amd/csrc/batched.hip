@@ -55,7 +55,7 @@ struct BtArgs {
     unsigned long long *win;
     uint32_t *sid, *row;
     uint64_t *keyA, *keyB;  // 2 * m_total each
-    int2 *cw;               // 2 * m_total
+    uint32_t *cw;           // 2 * m_total neighbour ids (unit weights)
     float *mass;
     float2 *F, *att;
     double2 *vpart;         // floor(n_total/256) + G + 1
@@ -332,12 +332,12 @@ __global__ void __launch_bounds__(NT) k_batched(BtArgs a) {
         __syncthreads();
         const uint64_t *dk = wg_radix_sort<NT>(keyA, keyB, 2 * (int64_t)E, 2 * kb, hist, running, wcnt);
         uint32_t *row = a.row + n0 + g;
-        int2 *cw = a.cw + 2 * e0;
+        uint32_t *cw = a.cw + 2 * e0;
         const int64_t nent = 2 * (int64_t)E;
         for (int64_t k = t; k < nent; k += NT) {
             const uint64_t key = dk[k];
             const int64_t src = (int64_t)(key >> kb);
-            cw[k] = make_int2((int32_t)(key & lowmask), __float_as_int(1.0f));
+            cw[k] = (uint32_t)(key & lowmask);
             const int64_t prev = k ? (int64_t)(dk[k - 1] >> kb) : -1;
             for (int64_t r = prev + 1; r <= src; ++r) row[r] = (uint32_t)k;
             if (k == nent - 1)
@@ -464,7 +464,7 @@ struct BtBig {
     uint4 *fitem;                     // (first node, K, wave tile, segment) of every pair, longest segments first
     uint4 *aitem;                     // (first node, K, wave tile, g) of every attraction item
     const uint32_t *row;
-    const int2 *cw;
+    const uint32_t *cw;
     const float *mass;
     float2 *pos, *fprev, *att;
     float2 *seg;  // segment sums: kBtMaxSeg per node from the graph's first node
@@ -591,9 +591,10 @@ __device__ __forceinline__ void bt_wave_repulsion(int32_t wt, int32_t sgm, int32
 // the graphs' sizes.  The others take the attraction of a wave tile's rows each, the
 // graph's positions in LDS: read from memory for every entry, they took longer than the
 // repulsion (47 against 31 us).  A graph of one segment takes the same path: its one
-// segment sum is its repulsion.  Bound by vector issue: 512 planted graphs (74M pairs, 4.5M
-// row entries per iteration) take 40.6 us, the repulsion alone 30.6 and the attraction alone
-// 25; a wavefront per item and then per row in one grid took 48.4.
+// segment sum is its repulsion.  Bound by the repulsion's vector issue: 512 planted graphs
+// (74M pairs, 4.5M row entries per iteration) take 33.1 us, the repulsion alone 30.6; with
+// entries of 8 bytes (id and weight) instead of 4, 40.6; a wavefront per item and then per
+// row in one grid took 48.4.
 __global__ void __launch_bounds__(kFa2Tile) k_bt_force(BtBig b, uint32_t rep_blocks) {
     __shared__ __align__(16) float2 xs[kBtAttPos];
     __shared__ uint32_t rows[kWave + 1];
@@ -617,7 +618,7 @@ __global__ void __launch_bounds__(kFa2Tile) k_bt_force(BtBig b, uint32_t rep_blo
         const int64_t n0 = it.x;
         const int32_t g = (int32_t)it.w, K = (int32_t)it.y, r0 = (int32_t)it.z * kWave, nr = min(kWave, K - r0);
         const uint32_t *row = b.row + n0 + g + r0;
-        const int2 *cw = b.cw + 2 * b.edge_off[g];
+        const uint32_t *cw = b.cw + 2 * b.edge_off[g];
         const float2 *pos = b.pos + n0;
         if (threadIdx.x <= (uint32_t)nr) rows[threadIdx.x] = row[threadIdx.x];
         if (K <= kBtAttPos)
@@ -710,7 +711,7 @@ struct BtWs {
     unsigned long long *win;
     uint32_t *sid, *row;
     uint64_t *keyA, *keyB;
-    int2 *cw;
+    uint32_t *cw;
     float *mass;
     float2 *F, *att;
     double2 *vpart;
@@ -732,7 +733,7 @@ static size_t bt_layout(Carver &c, int32_t G, int64_t n_total, int64_t m_total, 
     w->prop = c.take<int32_t>(m);
     w->keyA = c.take<uint64_t>(2 * m);
     w->keyB = c.take<uint64_t>(2 * m);
-    w->cw = c.take<int2>(2 * m);
+    w->cw = c.take<uint32_t>(2 * m);
     w->row = c.take<uint32_t>(n + (size_t)G);
     w->mass = c.take<float>(n);
     w->F = c.take<float2>(n);
@@ -902,8 +903,8 @@ extern "C" bgv_status bgv_batched(int32_t G, int64_t n_total, int64_t m_total, c
         b.ks = fa->ks;
         b.ksmax = fa->ksmax;
         // Two wavefronts per SIMD for the repulsion, whose items are few and long (three:
-        // 40.8 -> 43.9 us per launch), and as many attraction workgroups as pay: six per
-        // compute unit 43.5 us, 14 40.8, 24 the same.
+        // 15.5 -> 16.6 ms for 300 iterations); as many attraction workgroups as it has items
+        // or up to 14 per compute unit (eight are no slower).
         const unsigned rep_blocks = 2u * (unsigned)cus;
         const unsigned att_blocks = (unsigned)std::min<int64_t>(n_total / kWave + G, 14 * cus);
         BGV_LAUNCH(k_bt_plan, dim3(1), dim3(1024), 0, s, b);

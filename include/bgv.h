@@ -90,12 +90,12 @@ const char *bgv_last_error(void);
  * the threshold and whose endpoints' chunk-start labels differ proposes: the endpoint
  * whose community has the smaller or equal V joins the other's; endpoints that share a
  * label propose nothing.  Decisions then depend on labels, so rule 1 runs chunk by chunk
- * (method 0 or 1; tie must be 0).  Its workspace is 16 bytes per node and, per 2048-edge
- * tile of a chunk, 32 KiB plus two offset rows as for the degree rule; above 2^24 nodes,
- * or above 2^20 nodes with chunks of fewer than n / 8192 edges, 24 bytes per node and 4
- * per edge of a chunk.  Method 0 picks 2 when it applies and the chunk-by-chunk form would
- * take more than min(16 + passes * m / 2^17, 10 + (passes + 2) * m / 2^18) chunk steps,
- * else 1.  Other values are BGV_E_INVALID.
+ * (method 0 or 1; tie must be 0).  Its workspace is 24 bytes per node and 4 per edge of a
+ * chunk or, where that is more (up to 2^20 nodes, and up to 2^24 with chunks of at least
+ * n / 8192 edges), 16 bytes per node and, per 2048-edge tile of a chunk, 32 KiB plus two
+ * offset rows as for the degree rule.  Method 0 picks 2 when it applies and the
+ * chunk-by-chunk form would take more than 16 + m / 2^17 chunk steps with one pass, or
+ * 15 + (passes + 1) * m / 2^18 with more, else 1.  Other values are BGV_E_INVALID.
  */
 typedef struct {
     int32_t threshold; /* D1 >= 0: threshold of the first pass                   */

@@ -523,12 +523,13 @@ static bool cd_valid(int32_t n, int64_t m, const bgv_cd_params *p) {
 // 1: chunk by chunk; 2: back-pointer resolution.  Automatic: a chunk step costs 9 - 16 us, so
 // the second wins past some number of steps, measured at 16,000 / 160,000 / 800,000 / 2.4M /
 // 8M / 24M edges: one pass 8 / 8 / 17 / 35 / 82 / 208 steps, two 8 / 9 / 19 / 44 / 96 / 272,
-// four 10 / 12 / 28 / 65 / 124 / 396.
+// four 10 / 12 / 28 / 65 / 124 / 396.  (Short streams stay chunk by chunk up to 15 steps, where
+// the difference is tens of us and the second needs more workspace.)
 static int cd_method(int32_t n, int64_t m, const bgv_cd_params *p) {
     if (m == 0 || p->rule == 1) return 1;
     if (p->method != 0) return p->method;
     const int64_t steps = (int64_t)p->passes * ((m + p->chunk - 1) / p->chunk);
-    const int64_t line = std::min(16 + ((int64_t)p->passes * m >> 17), 10 + (((int64_t)p->passes + 2) * m >> 18));
+    const int64_t line = p->passes > 1 ? 15 + (((int64_t)p->passes + 1) * m >> 18) : 16 + (m >> 17);
     return steps > line && sq_fits(n, m, p) ? 2 : 1;
 }
 
@@ -842,7 +843,12 @@ static size_t vr_layout(Carver &c, int32_t n, int64_t m, const bgv_cd_params *p,
         t.prop = c.take<int32_t>(bb);
     }
     if (w) *w = t;
-    return c.size();
+    // never less than the atomic form takes, so that one size serves both
+    Carver a(nullptr);
+    a.take<unsigned long long>((size_t)n);
+    a.take<NodeState>((size_t)n);
+    a.take<int32_t>(bb);
+    return std::max(c.size(), a.size());
 }
 
 static bgv_status vr_run(int32_t n, int64_t m, const int32_t *edges, const bgv_cd_params *p, int32_t *labels,

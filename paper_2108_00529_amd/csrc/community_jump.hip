@@ -116,7 +116,9 @@ size_t sq_layout(Carver &c, int32_t n, int64_t m, const bgv_cd_params *p, void *
     w.esort = c.take<char>(sort_workspace((int64_t)pm, nbits));
     w.scan_scratch = c.take<char>(scan_workspace(tally));
     if (out) *static_cast<SqWs *>(out) = w;
-    return c.size();
+    // a caller may size its buffer by 48 bytes per edge and 40 per (pass, edge): the query
+    // never asks for less
+    return std::max(c.size(), 48 * (size_t)m + 40 * pm);
 }
 
 // ------------------------------------------------------------------ kernels ----

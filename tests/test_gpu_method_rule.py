@@ -1,6 +1,6 @@
-"""The automatic choice of the community method on both sides of its line (10 + (passes + 2)
-m / 2^18 or, for one pass of a long stream, 16 + passes m / 2^17 chunk steps): the labels,
-degrees and volumes are the oracle's whichever method it takes."""
+"""The automatic choice of the community method on both sides of its line (16 + m / 2^17 chunk
+steps with one pass, 15 + (passes + 1) m / 2^18 with more): the labels, degrees and volumes
+are the oracle's whichever method it takes."""
 import numpy as np
 import pytest
 import torch
@@ -16,8 +16,8 @@ def bgv():
     return b
 
 
-@pytest.mark.parametrize("m,passes,line", [(5_000, 1, 10), (5_000, 3, 10), (200_000, 4, 14), (2_000_000, 1, 31),
-                                           (2_000_000, 2, 40)])
+@pytest.mark.parametrize("m,passes,line", [(5_000, 1, 16), (5_000, 3, 15), (200_000, 4, 18), (2_000_000, 1, 31),
+                                           (2_000_000, 2, 37)])
 @pytest.mark.parametrize("past", [0, 1])
 def test_both_sides_of_the_line(bgv, m, passes, line, past):
     n, chunks = m // 8, (line + past * passes) // passes  # the most chunks at the line, or one more

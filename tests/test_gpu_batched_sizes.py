@@ -55,3 +55,29 @@ def test_every_size_equals_the_plain_layout(bgv, batch, wg_threads, big_k):
         assert int(out["K"][g]) == n
         assert torch.equal(out["pos"][a:b], p), n
         assert torch.equal(out["fprev"][a:b], f) and float(out["speed"][g]) == float(s), n
+
+
+@pytest.mark.parametrize("chunk", [1, 2, 255, 256, 257, 512, 1024, 1025, 100_000])
+@pytest.mark.parametrize("wg_threads,passes,tie", [(256, 3, 0), (1024, 2, 1)])
+def test_chunks_of_one_edge_per_thread_and_of_more(bgv, chunk, wg_threads, passes, tie):
+    """Chunks that leave each thread one edge at most and larger ones: labels and degrees are
+    the oracle's (graphs of no, fewer than, just as many and more edges than a chunk, loops,
+    repeated edges)."""
+    wl = dict(graphgen.WORKLOADS["batched_512"], passes=passes, chunk=chunk, tie=tie, fa2_iters=0)
+    c1 = graphgen.hash_coeffs(wl["rows"], 3)
+    rng = np.random.default_rng(chunk)
+    graphs = [(5, np.zeros((0, 2), np.int32))]
+    for n, m in ((3, 1), (40, 255), (40, 256), (40, 257), (300, 1024), (300, 1025), (900, 6000)):
+        e = rng.integers(0, n, (m, 2))
+        e[m // 2: m // 2 + m // 8] = e[0]
+        graphs.append((n, e.astype(np.int32)))
+    dev = torch.device("cuda")
+    edges, noff, eoff, noff_h, _ = bgv.pack_graphs(graphs, dev)
+    pos = torch.zeros((int(noff_h[-1]), 2), device=dev)
+    out = bgv.batched(edges, noff, eoff, int(noff_h[-1]), wl, c1, c1, pos, wg_threads=wg_threads)
+    for g, (n, e) in enumerate(graphs):
+        lab, cnt = oracle.bs_community(n, e, wl["threshold"], passes, wl["growth"], chunk, tie)
+        deg, _ = oracle.degree_volume(lab, cnt, passes)
+        a, b = int(noff_h[g]), int(noff_h[g + 1])
+        np.testing.assert_array_equal(out["labels"][a:b].cpu().numpy(), lab)
+        np.testing.assert_array_equal(out["degree"][a:b].cpu().numpy(), deg)

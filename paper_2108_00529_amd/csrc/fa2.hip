@@ -733,7 +733,7 @@ static bgv_status exact_forces(int32_t K, const float2 *pos, const float *mass, 
         BGV_LAUNCH(k_force_exact1, dim3(nb), dim3(kFaThreads), 0, s, K, pos, mass, A, item_of, kr, kg, fprev,
                    F, part, seg);
     } else {
-        if (K >= kRepTwoMin)
+        if (K >= kForceTwoMin)
             BGV_LAUNCH(k_force_exact_seg2, dim3((nb + 1) / 2, (unsigned)nseg), dim3(kFaThreads), 0, s, K, pos, mass, A,
                        item_of, kr, kg, fprev, F, part, seg);
         else

@@ -156,10 +156,13 @@ __device__ __forceinline__ void fa2_rep_run(const float2 (&xi)[1], const float4 
 // supergraph of a few thousand nodes spreads over many workgroups.
 constexpr int32_t kRepSegment = 512;
 
-// Bodies from which the all-pairs force kernels give each thread two bodies (us per layout
-// iteration with one / two: 16,384 bodies 87 / 87, 24,000 174 / 168, 50,000 616 / 555);
-// with fewer, halving the wavefronts costs what the shared reads give.
+// Bodies from which the gradient's repulsion gives each thread two bodies; with fewer, halving
+// the wavefronts costs what the shared reads give.
 constexpr int32_t kRepTwoMin = 16384;
+// The same for the layout's exact forces, whose one body per thread reads ahead (us per
+// iteration with one / two: 16,384 bodies 77 / 86, 30,000 218 / 224, 40,000 374 / 383, 50,000
+// 570 / 563, 100,000 2,160 / 2,124).
+constexpr int32_t kForceTwoMin = 45056;
 
 __host__ __device__ __forceinline__ int32_t fa2_rep_segments(int32_t K) {
     return (K + kRepSegment - 1) / kRepSegment;
@@ -436,7 +439,9 @@ __device__ __forceinline__ float2 fa2_att_value(const float2 *__restrict__ att, 
 
 // Exact repulsion of the nodes of tile bx (256 R nodes, R per thread) over the bodies of
 // j segment by (all of [0, K) when kSegmented is false), bodies staged through LDS 256 at
-// a time.  With one segment the tile's forces are finished (attraction, gravity, swing,
+// a time or, with one node per thread, the whole segment at once and each group read ahead
+// (few wavefronts share a SIMD then: 27.2 -> 25.0 us an iteration at 4,001 bodies, 60.9 ->
+// 57.6 at 12,000, 86.2 -> 82.1 at 16,000).  With one segment the tile's forces are finished (attraction, gravity, swing,
 // traction and the tile's FP64 partial sums into part[bx]); with several, the segment
 // sums go to seg.
 template <bool kSegmented, int R = 1>
@@ -446,7 +451,8 @@ __device__ __forceinline__ void fa2_exact_force_tile(int32_t bx, int32_t by, int
                                                      const float2 *__restrict__ fprev, float2 *__restrict__ F,
                                                      double2 *__restrict__ part, float2 *__restrict__ seg) {
     static_assert(kSegmented || R == 1, "finished tiles hold one node per thread");
-    __shared__ float4 tile[kFa2Tile];
+    constexpr int kStage = R == 1 ? kRepSegment : kFa2Tile;
+    __shared__ float4 tile[kStage];
     __shared__ double2 ws[kFa2Tile / kWave];
     const int32_t i = bx * (kFa2Tile * R) + threadIdx.x;
     float2 xi[R];
@@ -458,11 +464,16 @@ __device__ __forceinline__ void fa2_exact_force_tile(int32_t bx, int32_t by, int
     }
     const int32_t jb = kSegmented ? by * kRepSegment : 0;
     const int32_t je = kSegmented ? min(K, jb + kRepSegment) : K;
-    for (int32_t t0 = jb; t0 < je; t0 += kFa2Tile) {
-        const int32_t j = t0 + threadIdx.x;
-        tile[threadIdx.x] = j < je ? fa2_body(pos[j], mass[j]) : fa2_no_body();
+    for (int32_t t0 = jb; t0 < je; t0 += kStage) {
+#pragma unroll
+        for (int q = 0; q < kStage / kFa2Tile; ++q) {
+            const int32_t j = t0 + q * kFa2Tile + threadIdx.x;
+            tile[q * kFa2Tile + threadIdx.x] = j < je ? fa2_body(pos[j], mass[j]) : fa2_no_body();
+        }
         __syncthreads();
-        fa2_rep_run(xi, tile, min(kFa2Tile, (je - t0 + 7) & ~7), fx, fy);
+        const int n = min(kStage, (je - t0 + 7) & ~7);
+        if constexpr (R == 1) fa2_rep_ahead(xi[0], tile, n, fx[0], fy[0]);
+        else fa2_rep_run(xi, tile, n, fx, fy);
         __syncthreads();
     }
     if (kSegmented) {

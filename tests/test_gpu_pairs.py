@@ -49,3 +49,17 @@ def test_pairs(bgv, K):
     e_ref = oracle.fa2_energy(pos.astype(np.float64), SE, mass.astype(np.float64))
     e = float(bgv.fa2_energy(se, x, mass=m))
     assert abs(e - e_ref) <= 1e-5 * max(1.0, abs(e_ref))
+
+
+@pytest.mark.parametrize("K", [45_055, 45_056, 45_313])
+def test_forces_around_two_bodies_per_thread(bgv, K):
+    """The layout's forces where it goes over to two bodies per thread against the gradient
+    kernel's, which has gone over long before; the tolerance is that of test_pairs."""
+    pos, mass = bodies(K)
+    x, m, se = (torch.from_numpy(a).cuda() for a in (pos, mass, SE))
+    keep = np.ones(K, bool)
+    keep[[5, 7]] = False
+    grad = bgv.fa2_grad(se, x, mass=m).cpu().numpy()
+    _, force, _ = bgv.fa2_layout(se, x.clone(), 1, exact=True, mass=m)
+    scale = np.linalg.norm(grad[keep], axis=1).max()
+    assert np.linalg.norm(force.cpu().numpy()[keep] + grad[keep], axis=1).max() <= 1e-4 * scale

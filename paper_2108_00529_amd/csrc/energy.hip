@@ -119,7 +119,7 @@ __global__ void __launch_bounds__(kEnThreads) k_energy_pairs(int32_t K, int T, i
                 }
             }
         } else {
-            for (int q = 0; q < cnt; q += 8) {  // the tile's end is padded with bodies that add nothing
+            for (int q = 0; q < cnt; q += 8) {  // the last group's bodies past the end are left out
                 float4 b[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) b[u] = tile[q + u];
@@ -128,7 +128,7 @@ __global__ void __launch_bounds__(kEnThreads) k_energy_pairs(int32_t K, int T, i
 #pragma unroll
                     for (int u = 0; u < 8; ++u) {
                         const float v = en_log_term(fa2_norm2(xi[r].x - b[u].x, xi[r].y - b[u].y), b[u].z);
-                        s[r] += j0 + q + u > i0 + r * kEnThreads ? v : 0.f;
+                        s[r] += q + u < cnt && j0 + q + u > i0 + r * kEnThreads ? v : 0.f;
                     }
             }
         }

@@ -22,9 +22,12 @@ __device__ __forceinline__ void fa2_rep_term(float2 xi, float4 p, float &fx, flo
     fy = __builtin_fmaf(f, dy, fy);
 }
 
-// A body as the loops over all pairs stage it in LDS, and one that adds nothing.
+// A body as the loops over all pairs stage it in LDS, and one that adds nothing to any force:
+// without mass, and so far away that |x_i - x_j|^2 is large or zero for every x_i, since
+// near a body the reciprocal is infinite and 0 times it NaN (a pad at the origin was near a
+// body at (1e-20, 0)).  Its logarithm may be infinite: energies leave it out by its index.
 __device__ __forceinline__ float4 fa2_body(float2 x, float m) { return make_float4(x.x, x.y, m, 0.f); }
-__device__ __forceinline__ float4 fa2_no_body() { return make_float4(0.f, 0.f, 0.f, 0.f); }
+__device__ __forceinline__ float4 fa2_no_body() { return make_float4(1e18f, 1e18f, 0.f, 0.f); }
 
 // fa2_rep_term over n consecutive LDS bodies in ascending order, n a multiple of 8: each
 // group of eight is read before any of it is used, so the reads overlap.

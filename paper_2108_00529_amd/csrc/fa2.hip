@@ -916,8 +916,10 @@ __global__ void __launch_bounds__(NT) k_bh_split(int32_t K, int32_t it, const fl
                                                               const float4 *__restrict__ part, int nparts,
                                                               const float4 *__restrict__ before, uint64_t *__restrict__ keys,
                                                               uint16_t *__restrict__ off, float *__restrict__ s0_out,
-                                                              unsigned long long *__restrict__ totals, int32_t ntotals) {
+                                                              unsigned long long *__restrict__ totals, int32_t ntotals,
+                                                              uint32_t *__restrict__ started) {
     for (int32_t i = blockIdx.x * NT + threadIdx.x; i < ntotals; i += gridDim.x * NT) totals[i] = kBhUnset;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *started = 0u;
     float xmin, ymin, s0;
     bh_frame<NT>(part, nparts, &xmin, &ymin, &s0, s0_out);
     bh_split_tile<NT, ITEMS>(K, bh_split_shape(K, it), pos, [=](float2 p) { return bh_morton(p, xmin, ymin, s0); }, before, keys,
@@ -987,19 +989,29 @@ __global__ void __launch_bounds__(kFaThreads) k_bh_gather(int32_t K, const float
 
 // Exclusive FP64 prefix sums PM/PX/PY (K+1 entries) of the mass moments in Morton
 // order: block offset = fixed-order sum of the preceding block totals, then a block scan.
-// With kWait the launch makes the totals itself: a block publishes its own (plane c of
-// part3 has nb words, each kBhUnset before the launch) and reads those of the blocks
-// before it once they are there, which all have started by then.  Up to kBhWaitMax bodies,
-// where each thread waits for one block at most: 17,724 bodies 7.4 us, in two launches 10.1;
-// 171,724 17.3 us, in two launches 14.1.
+// With kWait the launch makes the totals itself: a workgroup publishes those of its block
+// (plane c of part3 has nb words, each kBhUnset before the launch) and reads those of the
+// blocks before it once they are there.  Workgroups take their blocks from the counter
+// *started, so whoever has the blocks before has started and publishes before it waits
+// itself; by workgroup number that does not hold, since each XCD starts its workgroups on
+// its own, and one behind another stream's kernel may be late by any time.  Up to kBhWaitMax
+// bodies, where each thread waits for one block at most: 17,724 bodies 7.4 us, in two launches
+// 10.1; 171,724 17.3 us, in two launches 14.1.
 constexpr int32_t kBhWaitMax = kFaThreads * kFaThreads;
 constexpr uint32_t kBhMaxSpins = 1u << 20;      // keeps a broken invariant from hanging the GPU
 
 template <bool kWait>
 __global__ void __launch_bounds__(kFaThreads) k_bh_prefix(int32_t K, const float4 *__restrict__ body, double *part3,
                                                            double *__restrict__ PM, double *__restrict__ PX,
-                                                           double *__restrict__ PY) {
-    const int32_t k = blockIdx.x * kFaThreads + threadIdx.x;
+                                                           double *__restrict__ PY, uint32_t *started) {
+    int32_t block = (int32_t)blockIdx.x;
+    if (kWait) {
+        __shared__ int32_t mine;
+        if (threadIdx.x == 0) mine = (int32_t)atomicAdd(started, 1u);
+        __syncthreads();
+        block = mine;
+    }
+    const int32_t k = block * kFaThreads + threadIdx.x;
     double m = 0.0, mx = 0.0, my = 0.0;
     if (k < K) {
         const float4 bd = body[k];
@@ -1016,10 +1028,10 @@ __global__ void __launch_bounds__(kFaThreads) k_bh_prefix(int32_t K, const float
         unsigned long long *w = reinterpret_cast<unsigned long long *>(part3);
         const int32_t nb = (int32_t)gridDim.x;
         if (threadIdx.x < 3)
-            __hip_atomic_store(&w[threadIdx.x * nb + blockIdx.x],
+            __hip_atomic_store(&w[threadIdx.x * nb + block],
                                (unsigned long long)__double_as_longlong(threadIdx.x == 0 ? t0 : threadIdx.x == 1 ? t1 : t2),
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        for (int32_t q = threadIdx.x; q < (int32_t)blockIdx.x; q += kFaThreads) {
+        for (int32_t q = threadIdx.x; q < block; q += kFaThreads) {
             unsigned long long v[3];
             uint32_t spins = 0;
             do {
@@ -1032,7 +1044,7 @@ __global__ void __launch_bounds__(kFaThreads) k_bh_prefix(int32_t K, const float
             b2 += __longlong_as_double((long long)v[2]);
         }
     } else {
-        for (int q = threadIdx.x; q < (int)blockIdx.x; q += kFaThreads) {
+        for (int32_t q = threadIdx.x; q < block; q += kFaThreads) {
             b0 += part3[3 * q];
             b1 += part3[3 * q + 1];
             b2 += part3[3 * q + 2];
@@ -1047,7 +1059,7 @@ __global__ void __launch_bounds__(kFaThreads) k_bh_prefix(int32_t K, const float
         PX[k] = base1 + e1;
         PY[k] = base2 + e2;
     }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+    if (block == (int32_t)gridDim.x - 1 && threadIdx.x == 0) {
         PM[K] = base0 + t0;
         PX[K] = base1 + t1;
         PY[K] = base2 + t2;
@@ -1548,6 +1560,7 @@ struct BhWs {
     BhKids *kids;      // the children's records of each internal node (what the traversal reads)
     uint32_t *icount;  // interactions per force workgroup, summed over the call's iterations
     uint32_t *done;    // workgroups done with their share of the list below
+    uint32_t *started; // workgroups of the prefix launch that have started
     uint32_t *redo;    // [0]: force workgroups to redo with the full stack, [1..]: their ids
     void *sort_scratch;
 };
@@ -1589,7 +1602,8 @@ static size_t fa_layout(Carver &c, int32_t K, int64_t E, const bgv_fa2_params *p
         b.node = c.take<BhNode>((size_t)K);
         b.kids = c.take<BhKids>((size_t)K);
         b.icount = c.take<uint32_t>((size_t)bh_force_blocks(K));
-        b.done = c.take<uint32_t>(1);
+        b.done = c.take<uint32_t>(2);
+        b.started = b.done ? b.done + 1 : nullptr;
         b.redo = c.take<uint32_t>((size_t)bh_force_blocks(K) + 1);
         b.sort_scratch = K > kBhSplitMax ? c.take<char>(onesweep_workspace(K)) : nullptr;
     }
@@ -1649,15 +1663,16 @@ static bgv_status bh_sorted_bodies(int32_t K, const float2 *pos, const float *ma
         if (K <= kBhSplitSmall)
             BGV_LAUNCH(k_bh_split_small, dim3((unsigned)sp.tiles), dim3(kBhTileSmall), 0, s, K, it, pos, b.bbox, nbox, before,
                        b.keys, off, b.s0, reinterpret_cast<unsigned long long *>(b.part3),
-                       K <= kBhWaitMax ? 3 * (int32_t)nb : 0);
+                       K <= kBhWaitMax ? 3 * (int32_t)nb : 0, b.started);
         else
             BGV_LAUNCH(k_bh_split_large, dim3((unsigned)sp.tiles), dim3(kBhTileLarge / 2), 0, s, K, it, pos, b.bbox, nbox, before,
                        b.keys, off, b.s0, reinterpret_cast<unsigned long long *>(b.part3),
-                       K <= kBhWaitMax ? 3 * (int32_t)nb : 0);
+                       K <= kBhWaitMax ? 3 * (int32_t)nb : 0, b.started);
         BGV_LAUNCH(k_bh_bucket, dim3((unsigned)sp.buckets), dim3(kBhBucketThreads), 0, s, K, it, pos, mass, b.keys, off,
                    b.keys_alt, reinterpret_cast<uint64_t *>(b.PM), b.body, b.code);  // PM is written after this
         if (K <= kBhWaitMax) {
-            BGV_LAUNCH(k_bh_prefix<true>, dim3(nb), dim3(kFaThreads), 0, s, K, b.body, b.part3, b.PM, b.PX, b.PY);
+            BGV_LAUNCH(k_bh_prefix<true>, dim3(nb), dim3(kFaThreads), 0, s, K, b.body, b.part3, b.PM, b.PX, b.PY,
+                       b.started);
             return BGV_OK;
         }
         BGV_LAUNCH(k_bh_moments, dim3(nb), dim3(kFaThreads), 0, s, K, b.body, b.part3);
@@ -1678,7 +1693,7 @@ static bgv_status bh_sorted_bodies(int32_t K, const float2 *pos, const float *ma
         BGV_TRY(onesweep_sort_u32(keys, keys_alt, b.vals, b.vals_alt, K, &sk, &sv, b.sort_scratch, s));
         BGV_LAUNCH(k_bh_gather, dim3(nb), dim3(kFaThreads), 0, s, K, pos, mass, sk, sv, b.body, b.code, b.part3);
     }
-    BGV_LAUNCH(k_bh_prefix<false>, dim3(nb), dim3(kFaThreads), 0, s, K, b.body, b.part3, b.PM, b.PX, b.PY);
+    BGV_LAUNCH(k_bh_prefix<false>, dim3(nb), dim3(kFaThreads), 0, s, K, b.body, b.part3, b.PM, b.PX, b.PY, nullptr);
     return BGV_OK;
 }
 

@@ -214,8 +214,9 @@ __global__ void __launch_bounds__(kEnThreads) k_grad_rep(int32_t K, int jtiles_p
         if (i + r * kEnThreads < K) prep[(int64_t)blockIdx.y * K + i + r * kEnThreads] = make_float2(fx[r], fy[r]);
 }
 
-// grad_i = -g * (kr m_i sum_splits rep + attraction + gravity)
-__global__ void __launch_bounds__(kEnThreads) k_grad_final(int32_t K, int nsplit, const float2 *__restrict__ prep,
+// grad_i = -g * (kr m_i sum_splits rep + attraction + gravity); split: bodies per split
+__global__ void __launch_bounds__(kEnThreads) k_grad_final(int32_t K, int nsplit, int32_t split,
+                                                            const float2 *__restrict__ prep,
                                                             const float2 *__restrict__ pos,
                                                             const float *__restrict__ mass,
                                                             const float2 *__restrict__ att,
@@ -231,6 +232,11 @@ __global__ void __launch_bounds__(kEnThreads) k_grad_final(int32_t K, int nsplit
         }
         const float2 xi = pos[i];
         const float mi = mass[i];
+        if (fa2_nan(rx, ry)) {
+            const float2 v = fa2_rep_again(xi, K, pos, mass, split);
+            rx = v.x;
+            ry = v.y;
+        }
         float fx = kr * mi * rx, fy = kr * mi * ry;
         const float2 a = fa2_att_combine(att, item_of, i);
         fx += a.x;
@@ -392,7 +398,8 @@ extern "C" bgv_status bgv_fa2_grad(int32_t K, int64_t E, const int32_t *edges, c
     else
         BGV_LAUNCH(k_grad_rep1, dim3(T, ns), dim3(kEnThreads), 0, s, K, per, x, m, w.gsplit);
     BGV_TRY(attraction(K, x, w.csr, w.att, s));
-    BGV_LAUNCH(k_grad_final, dim3(grid_for(K, kEnThreads, 65536)), dim3(kEnThreads), 0, s, K, ns, w.gsplit, x, m,
-               w.att, w.csr.item_of, kr, kg, grad_out, reinterpret_cast<float2 *>(grad));
+    const int32_t split = std::min(per * kEnThreads, K);  // bodies per split (at most 2^24)
+    BGV_LAUNCH(k_grad_final, dim3(grid_for(K, kEnThreads, 65536)), dim3(kEnThreads), 0, s, K, ns, split, w.gsplit, x,
+               m, w.att, w.csr.item_of, kr, kg, grad_out, reinterpret_cast<float2 *>(grad));
     return BGV_OK;
 }

@@ -41,7 +41,30 @@ __device__ __forceinline__ void fa2_rep_run(float2 xi, const float4 *tile, int n
     }
 }
 
-// The same for a wavefront that is alone on its SIMD, which waits for every result it uses
+// Whether a sum is not a number.  The loops below test groups of bodies for coincident ones,
+// not each pair, so a pair whose |x_i - x_j|^2 is NaN (a body with one coordinate NaN or
+// infinite), which the test of each pair drops along the other axis, reaches the sums there;
+// such sums are made once more, pair by pair: at once by fa2_rep_ahead, by fa2_rep_again
+// where the sums of the segments are added otherwise.
+__device__ __forceinline__ bool fa2_nan(float fx, float fy) { return !(fx == fx && fy == fy); }
+
+// The repulsion on a body at xi from all K, in segments of len: each summed from zero, then
+// the segments in order.
+__device__ __forceinline__ float2 fa2_rep_again(float2 xi, int32_t K, const float2 *__restrict__ pos,
+                                                const float *__restrict__ mass, int32_t len) {
+    float2 r = make_float2(0.f, 0.f);
+    for (int32_t b = 0; b < K; b += len) {
+        float sx = 0.f, sy = 0.f;
+        const int32_t e = K - b < len ? K : b + len;
+        for (int32_t j = b; j < e; ++j) fa2_rep_term(xi, fa2_body(pos[j], mass[j]), sx, sy);
+        r.x = b ? r.x + sx : sx;
+        r.y = b ? r.y + sy : sy;
+        if (e == K) break;
+    }
+    return r;
+}
+
+// The same as fa2_rep_run for a wavefront that is alone on its SIMD, which waits for every result it uses
 // at once: each group of eight is read while the one before it is used, and a group's
 // steps are kept apart (eight differences, eight reciprocals, ..., eight additions), which
 // the scheduler would interleave to save registers.
@@ -83,6 +106,7 @@ __device__ __forceinline__ void fa2_rep_load(const float4 *tile, float4 (&b)[8])
 }
 __device__ __forceinline__ void fa2_rep_ahead(float2 xi, const float4 *tile, int n, float &fx, float &fy) {
     if (n <= 0) return;
+    const float fx0 = fx, fy0 = fy;
     float4 b[8], c[8];
     fa2_rep_load(tile, b);
     int q = 8;
@@ -98,6 +122,11 @@ __device__ __forceinline__ void fa2_rep_ahead(float2 xi, const float4 *tile, int
         fa2_rep_steps(xi, c, fx, fy);
     } else {
         fa2_rep_steps(xi, b, fx, fy);
+    }
+    if (__any(fa2_nan(fx, fy))) {
+        fx = fx0;
+        fy = fy0;
+        fa2_rep_run(xi, tile, n, fx, fy);
     }
 }
 
@@ -512,6 +541,7 @@ __device__ __forceinline__ void fa2_combine_tile(int32_t bx, int32_t K, int32_t 
             r.x += v.x;
             r.y += v.y;
         }
+        if (fa2_nan(r.x, r.y)) r = fa2_rep_again(pos[i], K, pos, mass, kRepSegment);
         const float f_mi = mass[i];
         const float2 f = fa2_net_force(pos[i], f_mi, kr, r.x, r.y, fa2_att_value(att, item_of, i), kg);
         F[i] = f;

@@ -287,7 +287,8 @@ static int en_tiles(int32_t K) { return (K + kEnThreads - 1) / kEnThreads; }
 // Rows per thread of the pair kernel: two, so that each LDS read serves two pairs, from the
 // size on where that shortens the call (one row / two: 16,000 bodies 47 / 56 us, 20,480
 // 66 / 65, 24,000 86 / 81, 50,000 311 / 244).
-static int en_rows(int32_t K) { return K >= 20480 ? 2 : 1; }
+constexpr int32_t kEnTwoMin = 20480;
+static int en_rows(int32_t K) { return K >= kEnTwoMin ? 2 : 1; }
 static int64_t en_tri_pairs(int32_t K) {
     const int64_t T = en_tiles(K), R = en_rows(K), rows = (T + R - 1) / R;
     return rows * T - R * (rows * (rows - 1) / 2);
@@ -296,6 +297,10 @@ static int64_t en_tri_pairs(int32_t K) {
 // under the 2^32 work-items a launch may have)
 constexpr int64_t kEnPairBlocks = (int64_t)1 << 22;
 static int64_t en_tri_blocks(int32_t K) { return std::min(en_tri_pairs(K), kEnPairBlocks); }
+// the most of any call of at most K supernodes, so that a workspace sized for more serves fewer
+static int64_t en_most_tri_blocks(int32_t K) {
+    return std::max(en_tri_blocks(K), en_tri_blocks(std::min(K, kEnTwoMin - 1)));
+}
 static int en_edge_blocks(int64_t E) { return (int)grid_for(E, kEnThreads * 8, 2048); }
 static int en_grav_blocks(int32_t K) { return (int)grid_for(K, kEnThreads * 8, 2048); }
 static int en_splits(int32_t K) {  // about 2,048 workgroups of k_grad_rep
@@ -308,7 +313,7 @@ static int en_splits(int32_t K) {  // about 2,048 workgroups of k_grad_rep
 
 static size_t en_layout(Carver &c, int32_t K, int64_t E, EnWs *w) {
     csr_layout(c, K, E, &w->csr, false);  // one evaluation per call: no column-blocked setup
-    w->prep = c.take<double>((size_t)en_tri_blocks(K));
+    w->prep = c.take<double>((size_t)en_most_tri_blocks(K));
     w->patt = c.take<double>((size_t)en_edge_blocks(E));
     w->pgrav = c.take<double>((size_t)en_grav_blocks(K));
     w->gsplit = c.take<float2>((size_t)en_splits(K) * (size_t)K);

@@ -1539,6 +1539,11 @@ void prof_reset_counters() {
 static int32_t bh_force_blocks(int32_t K) {
     return (int32_t)(((int64_t)K * bh_lanes(K) + kBhThreads - 1) / kBhThreads);
 }
+// The most of any layout of at most K bodies (eight lanes each below 65,536 of them), so that
+// a workspace sized for more bodies serves fewer.
+static int32_t bh_most_force_blocks(int32_t K) {
+    return std::max(bh_force_blocks(K), bh_force_blocks(std::min(K, 65535)));
+}
 
 // Blocks of the Barnes-Hut update, and so the number of bounding-box partials the next
 // tree build reduces (min/max, so any count gives the same box).
@@ -1580,7 +1585,7 @@ static size_t fa_layout(Carver &c, int32_t K, int64_t E, const bgv_fa2_params *p
     const int64_t nb = (K + kFaThreads - 1) / kFaThreads;
     w->F = c.take<float2>((size_t)K);
     w->A = c.take<float2>((size_t)w->csr.items_bound);
-    w->part = c.take<double2>((size_t)(nb > bh_force_blocks(K) ? nb : bh_force_blocks(K)));
+    w->part = c.take<double2>((size_t)std::max<int64_t>(nb, bh_most_force_blocks(K)));
     w->speed = c.take<float>(2);
     w->flag = c.take<int32_t>(1);
     w->seg = nullptr;
@@ -1601,10 +1606,10 @@ static size_t fa_layout(Carver &c, int32_t K, int64_t E, const bgv_fa2_params *p
         b.PY = c.take<double>((size_t)K + 1);
         b.node = c.take<BhNode>((size_t)K);
         b.kids = c.take<BhKids>((size_t)K);
-        b.icount = c.take<uint32_t>((size_t)bh_force_blocks(K));
+        b.icount = c.take<uint32_t>((size_t)bh_most_force_blocks(K));
         b.done = c.take<uint32_t>(2);
         b.started = b.done ? b.done + 1 : nullptr;
-        b.redo = c.take<uint32_t>((size_t)bh_force_blocks(K) + 1);
+        b.redo = c.take<uint32_t>((size_t)bh_most_force_blocks(K) + 1);
         b.sort_scratch = K > kBhSplitMax ? c.take<char>(onesweep_workspace(K)) : nullptr;
     }
     return c.size();

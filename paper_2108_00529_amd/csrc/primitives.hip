@@ -3,6 +3,7 @@
 #include <stdarg.h>
 #include <stdio.h>
 
+#include <algorithm>
 #include <utility>
 
 #include "common.h"
@@ -373,7 +374,9 @@ void onesweep_layout(void *scratch, int64_t n, int items, OsBuffers *b) {
 }
 
 size_t onesweep_workspace(int64_t n) {
-    const int64_t tiles = os_tiles(n > 0 ? n : 1, os_items(n));
+    // not fewer than fewer keys take, whose tiles are smaller
+    const int64_t few = std::min<int64_t>(n > 0 ? n : 1, (int64_t)1 << 20);
+    const int64_t tiles = std::max(os_tiles(n > 0 ? n : 1, os_items(n)), os_tiles(few, os_items(few)));
     return align_up(sizeof(uint32_t) * kOsTotals) +
            align_up(sizeof(uint32_t) * ((size_t)kOsPasses * tiles * 256 + kOsPasses));
 }
@@ -504,8 +507,15 @@ static int64_t os_key_tiles(int64_t n) {
     return (n + tile - 1) / tile;
 }
 
+// The most tiles of any sort of at most n keys: past 2^16 and 2^20 keys the tiles double, and
+// a scratch sized for more keys has to serve fewer.
+static int64_t os_most_tiles(int64_t n) {
+    const int64_t small = std::max(os_key_tiles(std::min(n, (int64_t)1 << 16)), os_key_tiles(std::min(n, (int64_t)1 << 20)));
+    return std::max(os_key_tiles(n), small);
+}
+
 size_t onesweep_keys_workspace(int64_t n, int nbits) {
-    const int64_t tiles = os_key_tiles(n > 0 ? n : 1);
+    const int64_t tiles = os_most_tiles(n > 0 ? n : 1);
     const int passes = os_key_passes(nbits);
     return align_up(sizeof(uint32_t) * kOsMaxPasses * 256) +
            align_up(sizeof(uint32_t) * ((size_t)passes * tiles * 256 + passes));

@@ -93,7 +93,8 @@ const char *bgv_last_error(void);
  * (method 0 or 1; tie must be 0).  Its workspace is 24 bytes per node and 4 per edge of a
  * chunk or, where that is more (up to 2^20 nodes, and up to 2^24 with chunks of at least
  * n / 8192 edges), 16 bytes per node and, per 2048-edge tile of a chunk, 32 KiB plus two
- * offset rows as for the degree rule.  Method 0 picks 2 when it applies and the
+ * offset rows as for the degree rule; a call with less than the latter but the former is
+ * taken, by a slower form with the same results.  Method 0 picks 2 when it applies and the
  * chunk-by-chunk form would take more than 16 + m / 2^17 chunk steps with one pass, or
  * 15 + (passes + 1) * m / 2^18 with more, else 1.  Other values are BGV_E_INVALID.
  */

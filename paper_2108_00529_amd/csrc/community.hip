@@ -825,12 +825,12 @@ struct VrWs {
     uint32_t *ptab, *etab;
 };
 
-static size_t vr_layout(Carver &c, int32_t n, int64_t m, const bgv_cd_params *p, VrWs *w) {
+static size_t vr_layout(Carver &c, int32_t n, int64_t m, const bgv_cd_params *p, bool grouped, VrWs *w) {
     const int64_t b = p->chunk < m ? p->chunk : m;
     const size_t bb = (size_t)(b > 0 ? b : 1);
     VrWs t{};
     t.vol = c.take<unsigned long long>((size_t)n);
-    if (vr_grouped(n, m, p)) {
+    if (grouped) {
         const size_t tiles = (bb + kCdTile - 1) / kCdTile;
         const size_t nb = (size_t)cd_buckets(n, cd_bucket_bits(n));
         t.rec = c.take<int2>((size_t)n);
@@ -843,17 +843,24 @@ static size_t vr_layout(Carver &c, int32_t n, int64_t m, const bgv_cd_params *p,
         t.prop = c.take<int32_t>(bb);
     }
     if (w) *w = t;
-    // never less than the atomic form takes, so that one size serves both
-    Carver a(nullptr);
-    a.take<unsigned long long>((size_t)n);
-    a.take<NodeState>((size_t)n);
-    a.take<int32_t>(bb);
-    return std::max(c.size(), a.size());
+    return c.size();
+}
+
+// What the atomic form takes, the least that a call accepts, and what the query asks for,
+// which serves either form.  A workspace in between runs the atomic form: a chunk of a whole
+// stream takes four times as much grouped (16 bytes per edge).
+static size_t vr_least(int32_t n, int64_t m, const bgv_cd_params *p) {
+    Carver c(nullptr);
+    return vr_layout(c, n, m, p, false, nullptr);
+}
+static size_t vr_asked(int32_t n, int64_t m, const bgv_cd_params *p) {
+    Carver c(nullptr);
+    return std::max(vr_least(n, m, p), vr_grouped(n, m, p) ? vr_layout(c, n, m, p, true, nullptr) : 0);
 }
 
 static bgv_status vr_run(int32_t n, int64_t m, const int32_t *edges, const bgv_cd_params *p, int32_t *labels,
                          int32_t *degree, int64_t *volume, int32_t *pass_labels, int32_t first,
-                         const int32_t *lab0, void *ws, hipStream_t s);
+                         const int32_t *lab0, void *ws, size_t ws_bytes, hipStream_t s);
 
 }  // namespace bgv
 
@@ -863,7 +870,7 @@ extern "C" size_t bgv_community_workspace(int32_t n, int64_t m, const bgv_cd_par
     if (!cd_valid(n, m, p)) return 0;
     Carver c(nullptr);
     if (cd_method(n, m, p) == 2) return sq_layout(c, n, m, p, nullptr);
-    if (p->rule == 1) return vr_layout(c, n, m, p, nullptr);
+    if (p->rule == 1) return vr_asked(n, m, p);
     CdWs w;
     return cd_layout(c, n, m, p, &w);
 }
@@ -1014,7 +1021,7 @@ static bgv_status cd_run(int32_t n, int64_t m, const int32_t *edges, const bgv_c
         set_error("%s: null pointer", who);
         return BGV_E_INVALID;
     }
-    BGV_TRY(check_ws(ws, ws_bytes, bgv_community_workspace(n, m, p)));
+    BGV_TRY(check_ws(ws, ws_bytes, p->rule == 1 ? vr_least(n, m, p) : bgv_community_workspace(n, m, p)));
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     if (range_check_on()) {
         BGV_TRY(check_edge_ids(n, m, edges, labels, s));  // labels[0]: overwritten below
@@ -1023,7 +1030,8 @@ static bgv_status cd_run(int32_t n, int64_t m, const int32_t *edges, const bgv_c
     if (volume) BGV_TRY(fill<int64_t>(volume, 0, n, s));
     if (cd_method(n, m, p) == 2)
         return sq_run(n, m, edges, p, labels, degree, volume, pass_labels, first, lab0, ws, s);
-    if (p->rule == 1) return vr_run(n, m, edges, p, labels, degree, volume, pass_labels, first, lab0, ws, s);
+    if (p->rule == 1)
+        return vr_run(n, m, edges, p, labels, degree, volume, pass_labels, first, lab0, ws, ws_bytes, s);
     Carver c(ws);
     CdWs w;
     cd_layout(c, n, m, p, &w);
@@ -1168,12 +1176,13 @@ static bgv_status vr_run_grouped(int32_t n, int64_t m, const int2 *e2, const bgv
 
 static bgv_status vr_run(int32_t n, int64_t m, const int32_t *edges, const bgv_cd_params *p, int32_t *labels,
                          int32_t *degree, int64_t *volume, int32_t *pass_labels, int32_t first,
-                         const int32_t *lab0, void *ws, hipStream_t s) {
+                         const int32_t *lab0, void *ws, size_t ws_bytes, hipStream_t s) {
     Carver c(ws);
     VrWs w;
-    vr_layout(c, n, m, p, &w);
+    const bool grouped = vr_grouped(n, m, p) && ws_bytes >= vr_asked(n, m, p);
+    vr_layout(c, n, m, p, grouped, &w);
     const int2 *e2 = reinterpret_cast<const int2 *>(edges);
-    if (vr_grouped(n, m, p))
+    if (grouped)
         return cd_bucket_bits(n) == 13
                    ? vr_run_grouped<13>(n, m, e2, p, w, labels, degree, volume, pass_labels, first, lab0, s)
                    : vr_run_grouped<12>(n, m, e2, p, w, labels, degree, volume, pass_labels, first, lab0, s);

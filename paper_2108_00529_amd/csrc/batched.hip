@@ -440,9 +440,14 @@ __global__ void __launch_bounds__(NT) k_batched(BtArgs a) {
         __syncthreads();
         if (NT >= kResidentMax && K <= (uint32_t)kResidentMax) {
             // the state on chip, where the sketch was
-            fa2_resident<NT >= kResidentMax ? NT : kResidentMax, true>(
-                *reinterpret_cast<ResidentLds<kBtIds> *>(sk), (int32_t)K, a.iters, a.pos + n0, a.fprev + n0, mass, row,
-                cw, a.speed + g, a.kr, a.kg, a.tau, a.ks, a.ksmax);
+            constexpr int kThreads = NT >= kResidentMax ? NT : kResidentMax;
+            ResidentLds<kBtIds> &lds = *reinterpret_cast<ResidentLds<kBtIds> *>(sk);
+            if (resident_share<kThreads>((int32_t)K))
+                fa2_resident<kThreads, true, true>(lds, (int32_t)K, a.iters, a.pos + n0, a.fprev + n0, mass, row, cw,
+                                                   a.speed + g, a.kr, a.kg, a.tau, a.ks, a.ksmax);
+            else
+                fa2_resident<kThreads, true, false>(lds, (int32_t)K, a.iters, a.pos + n0, a.fprev + n0, mass, row, cw,
+                                                    a.speed + g, a.kr, a.kg, a.tau, a.ks, a.ksmax);
             continue;
         }
 

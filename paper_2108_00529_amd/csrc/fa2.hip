@@ -698,22 +698,23 @@ constexpr int kResidentIds = 32768;
 constexpr int32_t kResidentPlain = 448;
 constexpr int32_t kResidentIters = 4096;  // iterations per launch at most (tens of milliseconds)
 
-template <typename E>
+template <typename E, bool kShare>
 __global__ void __launch_bounds__(kResidentThreads) k_resident(int32_t K, int32_t iters, float2 *pos, float2 *fprev,
                                                                 const float *__restrict__ mass,
                                                                 const uint32_t *__restrict__ row,
                                                                 const E *__restrict__ cw, float *speed, float kr,
                                                                 float kg, float tau, float ks, float ksmax) {
     extern __shared__ char lds[];
-    fa2_resident<kResidentThreads, !std::is_same<E, int2>::value>(*reinterpret_cast<ResidentLds<kResidentIds> *>(lds),
-                                                                  K, iters, pos, fprev, mass, row, cw, speed, kr, kg,
-                                                                  tau, ks, ksmax);
+    fa2_resident<kResidentThreads, !std::is_same<E, int2>::value, kShare>(
+        *reinterpret_cast<ResidentLds<kResidentIds> *>(lds), K, iters, pos, fprev, mass, row, cw, speed, kr, kg, tau,
+        ks, ksmax);
 }
 
 template <typename E>
 static bgv_status resident_iterations(int32_t K, float2 *pos, float2 *fprev, const float *mass, const CsrWs &csr,
                                       float *speed, const bgv_fa2_params *p, hipStream_t s) {
-    const auto k_resident = bgv::k_resident<E>;  // one profiler name
+    // one profiler name
+    const auto k_resident = resident_share<kResidentThreads>(K) ? bgv::k_resident<E, true> : bgv::k_resident<E, false>;
     for (int64_t it = 0; it < p->iters; it += kResidentIters)
         BGV_LAUNCH(k_resident, dim3(1), dim3(kResidentThreads), sizeof(ResidentLds<kResidentIds>), s, K,
                    (int32_t)std::min<int64_t>(kResidentIters, p->iters - it), pos, fprev, mass, csr.row,

@@ -693,9 +693,20 @@ constexpr int kResidentThreads = 1024;
 constexpr int kResidentIds = 32768;
 // The most nodes a layout of one graph takes there: past it one compute unit's vector issue
 // costs more than the launches (us per iteration with 16 superedges per node, three
-// launches / resident: 64 nodes 9.5 / 2.9, 256 15.1 / 8.7, 400 20.8 / 18.2, 512 23.2 /
-// 24.8).
+// launches / resident: 64 nodes 10.5 / 3.1, 256 15.5 / 8.7, 384 18.0 / 15.9, 448 20.0 / 19.4,
+// 512 23.2 / 24.8).
 constexpr int32_t kResidentPlain = 448;
+// And the most superedges, whose rows one compute unit takes against all of them: by nodes, the
+// lines lie under the measured crossings (64 nodes about 40,000, 128 55,000, 160 41,000, 192
+// 35,000, 224 21,000, 256 20,000, 320 17,000, 384 12,000, 448 8,000; weighted, whose entries
+// are twice as long and never in LDS, 18,000, 27,000, 27,000, 25,000, 20,000, 17,000, 14,000,
+// 9,000, 1,800).  Every pair of 448 nodes: 20.9 us per iteration by launches, 35 resident;
+// every pair eight times 20.7 and 114.  With fewer than 64 nodes fewer rows share the work.
+static int64_t resident_superedges(int32_t K, bool weighted) {
+    const int64_t k = K, few = std::min<int64_t>(k, 64);
+    if (weighted) return std::min(few * 20000 / 64, 35000 - 75 * k);
+    return std::min(few * 40000 / 64, std::max(72000 - 230 * k, 32000 - 53 * k));
+}
 constexpr int32_t kResidentIters = 4096;  // iterations per launch at most (tens of milliseconds)
 
 template <typename E, bool kShare>
@@ -1876,7 +1887,8 @@ bgv_status bgv::fa2_layout_run(int32_t K, int64_t E, const int32_t *edges, const
     if (may_fork && !p->exact && w.csr.cols && K > 1 && p->iters > 0) st.open(side_stream(s));
     w.csr.beside = st.side != nullptr;
     const float *m = nullptr;
-    const bool resident = p->exact && K <= kResidentPlain;  // takes whole rows
+    // takes whole rows
+    const bool resident = p->exact && K <= kResidentPlain && E <= resident_superedges(K, attr_w != nullptr);
     BGV_TRY(build_csr(K, E, edges, attr_w, mass, w.csr, s, &m, !resident));
     if (!p->exact) {
         BGV_TRY(fill<uint32_t>(w.bh.icount, 0u, bh_force_blocks(K), s));

@@ -45,3 +45,18 @@ def test_batched_440_no_longer_than_500(bgv, wg_threads):
         ms.append(shortest(lambda: bgv.batched(edges, noff, eoff, 32 * n, wl, c1, c1, pos.clone(),
                                                wg_threads=wg_threads)))
     assert ms[0] <= 1.3 * ms[1], ms
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("K", [192, 448])
+def test_dense_layout_of_one_graph(bgv, K, weighted):
+    """Every pair eight times: one workgroup took two to twelve times as long as three launches
+    per iteration, which 449 supernodes have always taken."""
+    ms = []
+    for n in (K, 449):
+        u, v = np.triu_indices(n, 1)
+        se = torch.from_numpy(np.tile(np.stack([u, v], 1), (8, 1)).astype(np.int32)).cuda()
+        w = torch.full((se.shape[0],), 0.5, device="cuda") if weighted else None
+        pos = torch.from_numpy(np.random.default_rng(1).uniform(-1, 1, (n, 2)).astype(np.float32)).cuda()
+        ms.append(shortest(lambda: bgv.fa2_layout(se, pos.clone(), 100, exact=True, attr_w=w)))
+    assert ms[0] <= 1.3 * ms[1], ms

@@ -429,11 +429,17 @@ constexpr int kSkResolveThreads = 1024;
 // different addresses, is the quicker (whole call, 2M edges, 5 rows: 10 buckets 455 us, by
 // atomics 397; 20 buckets 402 and 402; 40 buckets 384 and 396; 10M edges: 1,147 and 1,051,
 // 924 and 1,067.  40 buckets, 200,000 edges: 255 and 245; 320 buckets, 2M edges: 348 and
-// 415).  A sketch that fits LDS takes the adds there (k_sg_sketch_pairs_lds).
+// 415).  With few rows it is the edges that count, not the additions (2M edges, 1 row, 2^20
+// and 2^22 cells: grouped 263 and 268, by atomics 276 and 284; 600,000 edges, 4 rows, 2^18 and
+// 2^22 cells: 239 and 227, 210 and 226).  Those are streams with three or four edges to a
+// pair; where every edge is a pair of its own the atomics are four times as many, and the line
+// would lie lower (the last: 317 and 292, 334 and 358).  A sketch that fits LDS takes the adds
+// there (k_sg_sketch_pairs_lds).
 constexpr int64_t kSkMinCells = 1 << 18;
-constexpr int64_t kSkMinAdds = 1 << 22;
 inline bool sk_grouped(int64_t m, int32_t rows, int64_t cells) {
-    return cells >= kSkMinCells && cells <= kSkMaxCells && m * rows >= kSkMinAdds;
+    if (cells < kSkMinCells || cells > kSkMaxCells) return false;
+    const int64_t adds = m * rows;
+    return m >= (1 << 20) || adds >= (1 << 22) || (adds >= (1 << 21) && cells >= (1 << 20));
 }
 
 inline int64_t sk_buckets(int64_t cells, int bits) { return (cells + (1ll << bits) - 1) >> bits; }

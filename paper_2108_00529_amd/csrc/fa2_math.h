@@ -551,9 +551,6 @@ __device__ __forceinline__ void fa2_combine_tile(int32_t bx, int32_t K, int32_t 
     if (threadIdx.x == 0) part[bx] = st;
 }
 
-// Global speed from part[0, nparts) (every tile reduces them in the same order; tile 0
-// stores it), then local speeds and displacement of the nodes bx*256 + t + q*stride.
-// Returns the thread's bounding box (xmin, xmax, ymin, ymax) of the moved positions.
 // The global speed from part[0, nparts) by one 256-thread block (fixed order); every
 // thread gets it.
 __device__ __forceinline__ float fa2_speed_of_parts(const double2 *__restrict__ part, int32_t nparts,

@@ -138,7 +138,7 @@ __global__ void __launch_bounds__(kCdThreads) k_cd_finish(const int32_t *__restr
         const int2 s = *reinterpret_cast<const int2 *>(st + kRecInts * v);
         labels[v] = s.y;
         degree[v] = s.x;
-        if (volume && s.x) vs_add(tab, volume, s.y, (unsigned long long)s.x);
+        if (volume && s.x) vs_add_node(tab, volume, v, s.y, (unsigned long long)s.x);
     }
     __syncthreads();
     if (volume) vs_flush(tab, volume);
@@ -206,7 +206,7 @@ __global__ void __launch_bounds__(kCdThreads) k_cd_finish_b(const int32_t *__res
         const int32_t d = cnt[v], l = lab[v];
         labels[v] = l;
         degree[v] = d;
-        if (volume && d) vs_add(tab, volume, l, (unsigned long long)d);
+        if (volume && d) vs_add_node(tab, volume, v, l, (unsigned long long)d);
     }
     __syncthreads();
     if (volume) vs_flush(tab, volume);
@@ -691,7 +691,7 @@ __global__ void __launch_bounds__(kCdThreads) k_vr_finish(const int32_t *__restr
         const int32_t d = r.x / passes, l = r.y;
         labels[v] = l;
         degree[v] = d;
-        if (volume && d) vs_add(tab, volume, l, (unsigned long long)d);
+        if (volume && d) vs_add_node(tab, volume, v, l, (unsigned long long)d);
     }
     __syncthreads();
     if (volume) vs_flush(tab, volume);

@@ -393,7 +393,7 @@ __global__ void __launch_bounds__(1024) k_sq_finish(const uint2 *__restrict__ wr
         const int32_t l = b.y > b.x ? (int32_t)(jv[b.y - 1] >> 32) : lab0 ? lab0[v] : (int32_t)v;
         labels[v] = l;
         const int32_t d = volume ? degree[v] : 0;
-        if (d) vs_add(tab, volume, l, (unsigned long long)d);
+        if (d) vs_add_node(tab, volume, v, l, (unsigned long long)d);
     }
     __syncthreads();
     if (volume) vs_flush(tab, volume);

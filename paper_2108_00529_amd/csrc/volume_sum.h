@@ -51,6 +51,16 @@ __device__ __forceinline__ void vs_add(VolumeTable &t, unsigned long long *vol, 
     atomicAdd(&vol[lab], v);
 }
 
+// Adds v at the label lab of node `node`.  The id a label is named after meets it once: that
+// node's own value goes straight to memory, so that streams whose nodes mostly keep their own
+// labels neither probe nor fill the table for them (683,000 nodes that all keep theirs: call
+// 138 -> 113 us, 111 with one atomic per node).
+__device__ __forceinline__ void vs_add_node(VolumeTable &t, unsigned long long *vol, int64_t node, int32_t lab,
+                                            unsigned long long v) {
+    if (lab == (int32_t)node) atomicAdd(&vol[lab], v);
+    else vs_add(t, vol, lab, v);
+}
+
 // After a barrier behind the last vs_add.
 __device__ __forceinline__ void vs_flush(const VolumeTable &t, unsigned long long *vol) {
     for (int q = threadIdx.x; q < kVsSlots; q += blockDim.x)
